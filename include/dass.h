@@ -419,9 +419,9 @@ dass_status dass_dynamic_mask(dass_ctx ctx, const dass_camera* cams, int32_t n_v
 typedef enum {
   DASS_STAGE_PROJECT = 0,     /* per-Gaussian projection, all views                 */
   DASS_STAGE_DEPTH_SORT = 1,  /* per-view depth order                                */
-  DASS_STAGE_BINNING = 2,     /* records into depth order, scan, tile-key emission   */
-  DASS_STAGE_KEY_SORT = 3,    /* stable sort of tile keys                            */
-  DASS_STAGE_RANGES = 4,      /* per-tile ranges                                     */
+  DASS_STAGE_BINNING = 2,     /* tile lists and ranges from the depth order          */
+  DASS_STAGE_KEY_SORT = 3,    /* (no launches: the tile lists need no sort)          */
+  DASS_STAGE_RANGES = 4,      /* (no launches: part of the binning)                  */
   DASS_STAGE_BLEND_FWD = 5,   /* front-to-back blend                                 */
   DASS_STAGE_BLEND_BWD = 6,   /* adjoint of the blend                                */
   DASS_STAGE_PROJECT_BWD = 7, /* adjoint of the projection                           */

@@ -38,7 +38,6 @@ struct dass_ctx_s {
   int fwd_n = 0, fwd_nv = 0, fwd_stride = 0;
   int64_t fwd_tiles = 0;
   int fwd_tw = kTile, fwd_th = kTile, fwd_sub = kTile;
-  int fwd_key_buf = 0;
   CamsK fwd_cams{};
   float fwd_bg[3] = {0.f, 0.f, 0.f};
 };
@@ -154,15 +153,13 @@ dass_status allocate(dass_ctx ctx, const dass_limits& l) {
   ALLOC(w.dval[0], vn);
   ALLOC(w.dval[1], vn);
   ALLOC(w.rect_s, vn);
-  ALLOC(w.tt_s, vn);
-  ALLOC(w.off_s, vn + 1);
   ALLOC(w.g2d, vn * 9);
   ALLOC(w.vis, vn);
-  ALLOC(w.keys[0], w.cap_keys > 0 ? w.cap_keys : 1);
-  ALLOC(w.keys[1], w.cap_keys > 0 ? w.cap_keys : 1);
-  ALLOC(w.vals[0], w.cap_keys > 0 ? w.cap_keys : 1);
-  ALLOC(w.vals[1], w.cap_keys > 0 ? w.cap_keys : 1);
+  ALLOC(w.vals, w.cap_keys > 0 ? w.cap_keys : 1);
   ALLOC(w.ranges, w.cap_tiles > 0 ? w.cap_tiles : 1);
+  ALLOC(w.tile_tot, w.cap_tiles + 4);
+  w.cap_bin = bin_hist_elems(w.cap_tiles);
+  ALLOC(w.bin_hist, w.cap_bin);
   ALLOC(w.hist, 2048 * 1024 + 2048);  // [radix][max sort blocks] counts + radix digit totals
   ALLOC(w.scan_tmp, scan_tmp_elems(vn));
   ALLOC(w.counters, 16);
@@ -237,10 +234,9 @@ dass_status make_cams(dass_ctx ctx, const dass_camera* cams, int nv, int tw, int
                 (long long)ctx->ws.cap_tiles);
   int64_t max_view_tiles = 1;
   for (int v = 0; v < nv; v++) max_view_tiles = std::max(max_view_tiles, (int64_t)out.c[v].TX * out.c[v].TY);
-  out.local_bits = bit_width((uint64_t)(max_view_tiles - 1));
-  if (out.local_bits > 31 || out.local_bits + bit_width((uint64_t)(nv - 1)) > 32)
+  const int local_bits = bit_width((uint64_t)(max_view_tiles - 1));
+  if (local_bits > 31 || local_bits + bit_width((uint64_t)(nv - 1)) > 32)
     return fail(ctx, DASS_E_CAPACITY, "%lld tiles per view do not fit a 32-bit tile key", (long long)max_view_tiles);
-  for (int v = 0; v < nv; v++) out.c[v].key_base = (uint32_t)v << out.local_bits;
   return DASS_OK;
 }
 
@@ -466,25 +462,14 @@ dass_status render_fwd_impl(dass_ctx ctx, const dass_gaussians* g, const dass_ca
                                   ws.hist, sort_blocks_for(vn), st);
   ws.gid_s = ws.dval[dcur];
   stage_end(ctx, DASS_STAGE_DEPTH_SORT, st);
-  // 3. records into depth order; tile keys in that order; stable sort on the tile id
+  // 3. tile lists in depth order
   stage_begin(ctx, DASS_STAGE_BINNING, st);
-  launch_gather_sorted(g->n, vn, ws.gid_s, ws, st);
-  launch_emit_keys(g->n, vn, ck, ws, st);
+  launch_binning(g->n, n_views, ck, total_tiles, ws, st);
   stage_end(ctx, DASS_STAGE_BINNING, st);
-  stage_begin(ctx, DASS_STAGE_KEY_SORT, st);
-  // keys arrive in view order, so the tile within the view is the only part left to sort.  An
-  // 11-bit digit costs the scatter twice a 10-bit one's per-batch digit work: over the keys of a
-  // multi-view call two narrower passes are faster, over one view's keys the single pass is
-  const int kcur = radix_sort_u32(ws.keys, ws.vals, ws.counters, ws.cap_keys, 0, ck.local_bits, ws.hist,
-                                  sort_blocks_for(ws.cap_keys), st, n_views > 1 ? 10 : 11);
-  stage_end(ctx, DASS_STAGE_KEY_SORT, st);
-  stage_begin(ctx, DASS_STAGE_RANGES, st);
-  launch_ranges(ws.keys[kcur], total_tiles, ck, n_views, ws, st);
-  stage_end(ctx, DASS_STAGE_RANGES, st);
   // 4. blend
   if (count_pairs) launch_fill_u32(reinterpret_cast<uint32_t*>(ws.pairs), 0u, 4, st);
   stage_begin(ctx, DASS_STAGE_BLEND_FWD, st);
-  launch_blend_fwd(io, n_views, total_tiles, bg, ws, ws.vals[kcur], count_pairs, l1 != nullptr, st);
+  launch_blend_fwd(io, n_views, total_tiles, bg, ws, count_pairs, l1 != nullptr, st);
   stage_end(ctx, DASS_STAGE_BLEND_FWD, st);
   if (l1) {
     stage_begin(ctx, DASS_STAGE_L1, st);
@@ -500,7 +485,6 @@ dass_status render_fwd_impl(dass_ctx ctx, const dass_gaussians* g, const dass_ca
   ctx->fwd_tw = tw;
   ctx->fwd_th = th;
   ctx->fwd_sub = sub;
-  ctx->fwd_key_buf = kcur;
   ctx->fwd_cams = ck;
   for (int c = 0; c < 3; c++) ctx->fwd_bg[c] = bg[c];
   return DASS_OK;
@@ -528,7 +512,7 @@ static bool matches_fwd(const dass_ctx ctx, const dass_gaussians* g, int n_views
   if (!ctx->have_fwd || ctx->fwd_n != g->n || ctx->fwd_nv != n_views || ctx->fwd_tiles != total_tiles ||
       ctx->fwd_stride != g->capacity || ctx->fwd_tw != tw || ctx->fwd_th != th)
     return false;
-  static_assert(sizeof(CamK) == 27 * 4, "CamK holds 4-byte fields only (no padding), compared bytewise");
+  static_assert(sizeof(CamK) == 26 * 4, "CamK holds 4-byte fields only (no padding), compared bytewise");
   return std::memcmp(ctx->fwd_cams.c, ck.c, sizeof(CamK) * (size_t)n_views) == 0;
 }
 
@@ -576,7 +560,7 @@ dass_status render_bwd(dass_ctx ctx, const dass_gaussians* g, const dass_camera*
   const int64_t vn = (int64_t)n_views * g->n;
   launch_fill_u32(reinterpret_cast<uint32_t*>(ws.g2d), 0u, vn * 9, st);
   stage_begin(ctx, DASS_STAGE_BLEND_BWD, st);
-  launch_blend_bwd(io, n_views, total_tiles, bg, ws, ws.vals[ctx->fwd_key_buf], g->n, st);
+  launch_blend_bwd(io, n_views, total_tiles, bg, ws, st);
   stage_end(ctx, DASS_STAGE_BLEND_BWD, st);
   stage_begin(ctx, DASS_STAGE_PROJECT_BWD, st);
   launch_preprocess_bwd(scene_of(g), ck, n_views, ws, *grads, gradnorm_sum, grad_count, st);
@@ -816,7 +800,7 @@ dass_status dass_render_features(dass_ctx ctx, const dass_gaussians* g, const da
   HIP_TRY(ctx, hipSetDevice(ctx->device));
   hipStream_t st = (hipStream_t)stream;
   stage_begin(ctx, DASS_STAGE_BLEND_FWD, st);
-  launch_blend_feat(io, n_views, total_tiles, fo, ctx->ws, ctx->ws.vals[ctx->fwd_key_buf], st);
+  launch_blend_feat(io, n_views, total_tiles, fo, ctx->ws, st);
   stage_end(ctx, DASS_STAGE_BLEND_FWD, st);
   return check_launch(ctx, "dass_render_features");
 }
@@ -1106,8 +1090,7 @@ dass_status dass_debug_keys(dass_ctx ctx, int32_t view, uint64_t* keys, uint32_t
   const int nt = c.TX * c.TY;
   std::vector<uint2> r(nt);
   HIP_TRY(ctx, hipMemcpy(r.data(), ctx->ws.ranges + c.tile_base, nt * sizeof(uint2), hipMemcpyDeviceToHost));
-  // the view's tiles are runs of the sorted keys (runs of all views interleave); concatenated in
-  // tile order they are the view's key list
+  // the view's tile lists, concatenated in tile order, are the view's key list
   std::vector<int64_t> rel(2 * (size_t)nt, 0);
   int64_t cnt = 0;
   for (int t = 0; t < nt; t++)
@@ -1122,8 +1105,8 @@ dass_status dass_debug_keys(dass_ctx ctx, int32_t view, uint64_t* keys, uint32_t
   HIP_TRY(ctx, hipMemcpy(ranges, rel.data(), rel.size() * sizeof(int64_t), hipMemcpyHostToDevice));
   for (int t = 0; t < nt; t++)
     if (r[t].y > r[t].x)
-      launch_debug_keys(view, ctx->fwd_n, ctx->ws, ctx->ws.keys[ctx->fwd_key_buf], ctx->ws.vals[ctx->fwd_key_buf],
-                        r[t].x, r[t].y - r[t].x, c, keys + rel[2 * t], vals + rel[2 * t], nullptr);
+      launch_debug_keys(view, ctx->fwd_n, ctx->ws, (uint32_t)t, r[t].x, r[t].y - r[t].x, keys + rel[2 * t],
+                        vals + rel[2 * t], nullptr);
   HIP_TRY(ctx, hipDeviceSynchronize());
   return check_launch(ctx, "dass_debug_keys");
 }

@@ -37,15 +37,15 @@ struct CamK {
   float campos[3];
   int W, H, TX, TY;
   int tw, th;     // tile size in pixels
-  int tile_base;      // first global tile index of this view
-  uint32_t key_base;  // view << CamsK::local_bits: the view's part of a tile key
+  int tile_base;  // first global tile index of this view
 };
-// Tile keys are (view << local_bits) | tile within the view, local_bits wide enough for every
-// view's tiles: keys are emitted in view order, so a stable sort of the low local_bits alone
-// groups each (view, tile) into one run.
 struct CamsK {
   CamK c[DASS_MAX_VIEWS];
-  int local_bits;
+};
+// What the binning needs of the views.
+struct BinViews {
+  int TX[DASS_MAX_VIEWS], TY[DASS_MAX_VIEWS], tile_base[DASS_MAX_VIEWS];
+  uint32_t cap;  // key budget
 };
 
 struct SceneK {
@@ -196,22 +196,21 @@ struct Workspace {
   uint32_t* dval[2] = {nullptr, nullptr};
   // per sorted position p (view-major, depth order)
   uint2* rect_s = nullptr;
-  uint32_t* tt_s = nullptr;        // tiles touched, sorted order
-  uint64_t* off_s = nullptr;       // exclusive prefix of tiles touched, [cap_vn + 1]
   uint32_t* gid_s = nullptr;       // gid of sorted position p
-  // tile keys carry the record index v * n + g as their value
   float* g2d = nullptr;            // [cap_vn][9], row v * n + g: blend-backward sums (moments of
                                    // dL/d(exponent) over the offsets, d opacity, d rgb)
   uint8_t* vis = nullptr;          // [cap_vn], row v * n + g: bit 3 visible, bit c colour channel c
                                    // above its clamp at 0 (the colour adjoint's only record reads)
-  // keys
-  uint32_t* keys[2] = {nullptr, nullptr};
-  uint32_t* vals[2] = {nullptr, nullptr};
+  // tile lists: record indices v * n + g, [cap_keys], each tile's in depth order
+  uint32_t* vals = nullptr;
   uint2* ranges = nullptr;         // [cap_tiles]
+  uint32_t* tile_tot = nullptr;    // [cap_tiles] keys per tile
+  uint32_t* bin_hist = nullptr;    // [cap_bin] keys per (chunk of Gaussians, tile)
+  int64_t cap_bin = 0;
   // scratch
   uint32_t* hist = nullptr;        // sort histograms
   uint64_t* scan_tmp = nullptr;    // scan block sums
-  uint32_t* counters = nullptr;    // [0] = key count (clamped), [1] = densify |S|, [2] = depth-sort count
+  uint32_t* counters = nullptr;    // [1] = densify |S|, [2] = depth-sort count, [4..5] = keys of the call (u64)
   unsigned long long* pairs = nullptr;  // [0] evaluated, [1] blended (pair counting only)
   float* loss_slots = nullptr;          // [kLossSlots] partial sums of the fused L1 loss
   float* field_part = nullptr;          // [kFieldMaxBlocks][field_part_stride] weight-gradient partials
@@ -248,24 +247,25 @@ int radix_sort_u32(uint32_t* keys[2], uint32_t* vals[2], const uint32_t* d_count
                    int digit_cap = 11);
 int sort_blocks_for(int64_t max_count);
 
+// binning.hip
+int64_t bin_hist_elems(int64_t max_tiles);
+// tile lists (ws.vals, ws.ranges) from the depth order (ws.gid_s) and the rectangles (ws.rect_u)
+void launch_binning(int n, int nv, const CamsK& cams, int64_t total_tiles, Workspace& ws, hipStream_t st);
+
 // raster.hip
-void launch_gather_sorted(int n, int64_t vn, const uint32_t* sorted_gid, Workspace& ws, hipStream_t st);
-// emits keys into ws.keys[0]/ws.vals[0] and writes the clamped key count to ws.counters[0]
-void launch_emit_keys(int n, int64_t vn, const CamsK& cams, Workspace& ws, hipStream_t st);
-void launch_ranges(const uint32_t* keys, int64_t total_tiles, const CamsK& cams, int nv, Workspace& ws, hipStream_t st);
 void launch_blend_fwd(const ViewsIO& io, int nv, int64_t total_tiles, const float bg[3],
-                      const Workspace& ws, const uint32_t* vals, bool count_pairs, bool l1, hipStream_t st);
+                      const Workspace& ws, bool count_pairs, bool l1, hipStream_t st);
 // Adds the loss partial sums and `add` to *loss (fixed order) and clears the sums.
 void launch_loss_finish(float* slots, float* loss, float add, hipStream_t st);
 // accumulates the per-(view, Gaussian) 2D gradients into ws.g2d[(v * n + g) * 9 + k]
 void launch_blend_bwd(const ViewsIO& io, int nv, int64_t total_tiles, const float bg[3],
-                      const Workspace& ws, const uint32_t* vals, int n, hipStream_t st);
+                      const Workspace& ws, hipStream_t st);
 void launch_fill_u32(uint32_t* p, uint32_t v, int64_t n, hipStream_t st);
 // identity features of the last render's lists (same weights as its colour blend)
 void launch_blend_feat(const ViewsIO& io, int nv, int64_t total_tiles, const FeatIO& fo, const Workspace& ws,
-                       const uint32_t* vals, hipStream_t st);
-void launch_debug_keys(int view, int n, const Workspace& ws, const uint32_t* keys_sorted, const uint32_t* vals_sorted,
-                       uint32_t lo, uint32_t cnt, const CamK& cam, uint64_t* kout, uint32_t* vout, hipStream_t st);
+                       hipStream_t st);
+void launch_debug_keys(int view, int n, const Workspace& ws, uint32_t tile, uint32_t lo, uint32_t cnt, uint64_t* kout,
+                       uint32_t* vout, hipStream_t st);
 
 // update.hip
 void launch_shift_fwd(const SceneK& in, float* out_mean, float* out_quat, const int32_t* dyn_idx,

@@ -1,10 +1,5 @@
-// Tile binning and the front-to-back blend with its adjoint (App. A.1).
-//
-// Binning.  After the per-view depth sort of (view, depth bits, index), the tile counts and
-// rectangles are gathered into that order.  Keys are then just global tile ids (view tile base
-// + ty*TX + tx), emitted in (view, depth) order with the record index (view * n + Gaussian) as
-// value and sorted stably on the tile bits only; the stable order inside a tile is the depth
-// order.  Ranges are the [first, last+1) of each tile id.
+// The front-to-back blend with its adjoint (App. A.1), over each tile's list of record indices
+// (view * n + Gaussian) in depth order.
 //
 // Blend.  One wave per sub-tile of a tile (16x16 with four pixels per lane, one in each 8x8
 // quadrant, or 8x8 with one pixel per lane, for small images where the lists are walked by few
@@ -32,135 +27,6 @@ __global__ void k_fill_u32(uint32_t* __restrict__ p, uint32_t v, int64_t n) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t j = i; j < n; j += stride) p[j] = v;
-}
-
-// Tile rectangle and tiles touched (the rectangle's area) of each (view, Gaussian) in (view,
-// depth) order, for the scan and the key emission: one gathered 8-byte rectangle per position;
-// the records themselves stay where the projection wrote them.
-__global__ __launch_bounds__(256) void k_gather_sorted(int n, int64_t vn, const uint32_t* __restrict__ sorted_gid,
-                                                       const uint2* __restrict__ rect_u, uint32_t* __restrict__ tt_s,
-                                                       uint2* __restrict__ rect_s) {
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= vn) return;
-  const int64_t v = p / n;
-  const uint2 r = rect_u[v * n + sorted_gid[p]];
-  tt_s[p] = ((r.y & 0xFFFFu) - (r.x & 0xFFFFu)) * ((r.y >> 16) - (r.x >> 16));
-  rect_s[p] = r;
-}
-
-// Each wave takes 64 consecutive sorted positions (Gaussian-views) and writes all their keys
-// (value: the record index of the Gaussian-view) with the keys spread evenly over the lanes: lane l writes keys l, l + 64, ... of the wave's
-// run, finding the owning Gaussian by a binary search over the run's end offsets in LDS.  The
-// stores of a wave are consecutive, whatever the tile counts.
-__global__ __launch_bounds__(256) void k_emit_keys(int n, int64_t vn, CamsK cams, const uint32_t* __restrict__ tt_s,
-                                                   const uint2* __restrict__ rect_s, const uint32_t* __restrict__ sorted_gid,
-                                                   const uint64_t* __restrict__ off, int64_t cap,
-                                                   uint32_t* __restrict__ keys, uint32_t* __restrict__ vals,
-                                                   uint32_t* __restrict__ err) {
-  __shared__ uint32_t s_end[4][64];   // end of each Gaussian's keys, relative to the wave's first key
-  __shared__ uint4 s_g[4][64];        // key of the rectangle's first tile, TX, width, 1/width
-  __shared__ uint32_t s_rec[4][64];   // record index (view * n + Gaussian) = the keys' value
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t p0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) - lane;  // first position of this wave
-  if (p0 >= vn) return;  // uniform over the wave
-  const int64_t pm = p0 + lane;
-  const bool valid = pm < vn;
-  uint32_t my_tt = 0;
-  uint64_t my_off = 0;
-  if (valid) {
-    my_tt = tt_s[pm];
-    my_off = off[pm];
-    if (my_off + my_tt > (uint64_t)cap) atomicOr(err, kErrKeyOverflow);
-    const uint2 r = rect_s[pm];
-    const int v = (int)(pm / n);
-    const int x0 = r.x & 0xFFFF, y0 = r.x >> 16, x1 = r.y & 0xFFFF;
-    const int w = max(x1 - x0, 1);
-    const int TX = cams.c[v].TX;
-    s_g[wave][lane] = make_uint4(cams.c[v].key_base + (uint32_t)(y0 * TX + x0), (uint32_t)TX, (uint32_t)w,
-                                 __float_as_uint(1.0f / (float)w));
-    s_rec[wave][lane] = (uint32_t)((int64_t)v * n + sorted_gid[pm]);
-  }
-  const uint64_t first = __shfl(my_off, 0, 64);
-  const uint32_t end = valid ? (uint32_t)(my_off - first) + my_tt : 0xFFFFFFFFu;  // non-decreasing over lanes
-  s_end[wave][lane] = end;
-  const int last = (int)min((int64_t)63, vn - 1 - p0);
-  const uint32_t total = __shfl(end, last, 64);
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  for (uint32_t k = lane; k < total; k += 64) {
-    int src = 0;  // number of Gaussians whose keys end at or before k
-#pragma unroll
-    for (int step = 32; step > 0; step >>= 1)
-      if (s_end[wave][src + step - 1] <= k) src += step;
-    const uint32_t i = k - (src ? s_end[wave][src - 1] : 0u);  // key index within the Gaussian
-    const uint4 gg = s_g[wave][src];
-    // i / width by a float reciprocal, corrected to the exact quotient (i < 2^24)
-    uint32_t q = (uint32_t)((float)i * __uint_as_float(gg.w));
-    int32_t r = (int32_t)(i - q * gg.z);
-    if (r < 0) {
-      q--;
-      r += (int32_t)gg.z;
-    } else if (r >= (int32_t)gg.z) {
-      q++;
-      r -= (int32_t)gg.z;
-    }
-    const uint64_t kk = first + k;
-    if (kk < (uint64_t)cap) {
-      keys[kk] = gg.x + q * gg.y + (uint32_t)r;
-      vals[kk] = s_rec[wave][src];
-    }
-  }
-}
-
-__global__ void k_clamp_count(const uint64_t* __restrict__ total, int64_t cap, uint32_t* __restrict__ count) {
-  const uint64_t t = *total;
-  *count = (uint32_t)(t < (uint64_t)cap ? t : (uint64_t)cap);
-}
-
-// Global tile index of a key: the view's first tile plus the tile within the view.
-struct KeyTiles {
-  int tile_base[DASS_MAX_VIEWS];
-  int local_bits, nv;
-  uint32_t total_tiles;
-};
-
-// Per-tile ranges of the sorted keys: four consecutive keys per thread (one 16-byte load) and
-// their two neighbours; a key that differs from its predecessor starts a range, one that differs
-// from its successor ends it.  Ranges are stored by global tile index.
-__global__ __launch_bounds__(256) void k_ranges(const uint32_t* __restrict__ keys, const uint32_t* __restrict__ d_count,
-                                                const KeyTiles kt, uint2* __restrict__ ranges) {
-  const int64_t count = *d_count;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x * 4;
-  for (int64_t i0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 4; i0 < count; i0 += stride) {
-    uint32_t k[6];  // keys i0 - 1 .. i0 + 4 (entries outside [0, count) unused)
-    if (i0 + 4 <= count) {
-      const uint4 v = *reinterpret_cast<const uint4*>(keys + i0);
-      k[1] = v.x;
-      k[2] = v.y;
-      k[3] = v.z;
-      k[4] = v.w;
-    } else {
-#pragma unroll
-      for (int j = 0; j < 4; j++) k[1 + j] = i0 + j < count ? keys[i0 + j] : 0u;
-    }
-    k[0] = i0 > 0 ? keys[i0 - 1] : 0u;
-    k[5] = i0 + 4 < count ? keys[i0 + 4] : 0u;
-#pragma unroll
-    for (int j = 0; j < 4; j++) {
-      const int64_t i = i0 + j;
-      if (i >= count) break;
-      const uint32_t key = k[1 + j];
-      const bool starts = i == 0 || k[j] != key, ends = i == count - 1 || k[2 + j] != key;
-      if (!starts && !ends) continue;
-      const uint32_t v = key >> kt.local_bits;
-      if (v >= (uint32_t)kt.nv) continue;  // not reached: every key below the count was emitted
-      const uint32_t t = (uint32_t)kt.tile_base[v] + (key & ((1u << kt.local_bits) - 1u));
-      if (t >= kt.total_tiles) continue;
-      if (starts) ranges[t].x = (uint32_t)i;
-      if (ends) ranges[t].y = (uint32_t)(i + 1);
-    }
-  }
 }
 
 __device__ __forceinline__ int view_of(const ViewsIO& io, int nv, int b) {
@@ -783,14 +649,13 @@ __global__ __launch_bounds__(kLanes) void k_blend_feat(ViewsIO io, int nv, int t
   }
 }
 
-__global__ void k_debug_keys(uint32_t key_base, uint32_t row0, const uint32_t* __restrict__ keys,
-                             const uint32_t* __restrict__ vals, const Rec* __restrict__ rec, uint32_t lo,
-                             uint32_t cnt, uint64_t* __restrict__ kout, uint32_t* __restrict__ vout) {
+__global__ void k_debug_keys(uint32_t tile, uint32_t row0, const uint32_t* __restrict__ vals,
+                             const Rec* __restrict__ rec, uint32_t lo, uint32_t cnt, uint64_t* __restrict__ kout,
+                             uint32_t* __restrict__ vout) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= cnt) return;
-  const uint32_t k = keys[lo + i];
   const uint32_t p = vals[lo + i];  // record index of the view's Gaussian
-  kout[i] = ((uint64_t)(k - key_base) << 32) | (uint64_t)__float_as_uint(rec[p].r2.w);
+  kout[i] = ((uint64_t)tile << 32) | (uint64_t)__float_as_uint(rec[p].r2.w);
   vout[i] = p - row0;
 }
 
@@ -803,63 +668,35 @@ void launch_fill_u32(uint32_t* p, uint32_t v, int64_t n, hipStream_t st) {
   k_fill_u32<<<(unsigned)blocks, 256, 0, st>>>(p, v, n);
 }
 
-void launch_gather_sorted(int n, int64_t vn, const uint32_t* sorted_gid, Workspace& ws, hipStream_t st) {
-  if (vn == 0) return;
-  k_gather_sorted<<<(unsigned)((vn + 255) / 256), 256, 0, st>>>(n, vn, sorted_gid, ws.rect_u, ws.tt_s,
-                                                                 ws.rect_s);
-}
-
-void launch_emit_keys(int n, int64_t vn, const CamsK& cams, Workspace& ws, hipStream_t st) {
-  scan_u32_to_u64(ws.tt_s, ws.off_s, vn, ws.scan_tmp, st);
-  if (vn > 0)
-    k_emit_keys<<<(unsigned)((vn + 255) / 256), 256, 0, st>>>(n, vn, cams, ws.tt_s, ws.rect_s, ws.gid_s, ws.off_s,
-                                                               ws.cap_keys, ws.keys[0], ws.vals[0], ws.err);
-  k_clamp_count<<<1, 1, 0, st>>>(ws.off_s + vn, ws.cap_keys, ws.counters);
-}
-
-void launch_ranges(const uint32_t* keys, int64_t total_tiles, const CamsK& cams, int nv, Workspace& ws,
-                   hipStream_t st) {
-  launch_fill_u32(reinterpret_cast<uint32_t*>(ws.ranges), 0u, 2 * total_tiles, st);
-  KeyTiles kt{};
-  for (int v = 0; v < nv; v++) kt.tile_base[v] = cams.c[v].tile_base;
-  kt.local_bits = cams.local_bits;
-  kt.nv = nv;
-  kt.total_tiles = (uint32_t)total_tiles;
-  int64_t blocks = (ws.cap_keys + 1023) / 1024;
-  if (blocks > 8192) blocks = 8192;
-  if (blocks < 1) blocks = 1;
-  k_ranges<<<(unsigned)blocks, 256, 0, st>>>(keys, ws.counters, kt, ws.ranges);
-}
-
 static inline int per_xcd(int64_t total_tiles) { return (int)((total_tiles + kNumXcd - 1) / kNumXcd); }
 
 // One wave per (tile, sub-tile); the sub-tiles of a tile are consecutive logical blocks, so they
 // run on the same XCD and share its L2 for the tile's list and records.
 template <bool COUNT, bool L1, int B>
 void blend_fwd_batch(const ViewsIO& io, int nv, int total, int per, const float bg[3], const Workspace& ws,
-                     const uint32_t* vals, hipStream_t st) {
+                     hipStream_t st) {
   const dim3 grid(per * kNumXcd), block(kLanes);
   if (io.sub == 8)
-    k_blend_fwd<COUNT, L1, 8, B><<<grid, block, 0, st>>>(io, nv, total, per, bg[0], bg[1], bg[2], ws.ranges, vals,
+    k_blend_fwd<COUNT, L1, 8, B><<<grid, block, 0, st>>>(io, nv, total, per, bg[0], bg[1], bg[2], ws.ranges, ws.vals,
                                                         ws.rec_u, ws.pairs, ws.loss_slots);
   else
-    k_blend_fwd<COUNT, L1, 16, B><<<grid, block, 0, st>>>(io, nv, total, per, bg[0], bg[1], bg[2], ws.ranges, vals,
+    k_blend_fwd<COUNT, L1, 16, B><<<grid, block, 0, st>>>(io, nv, total, per, bg[0], bg[1], bg[2], ws.ranges, ws.vals,
                                                          ws.rec_u, ws.pairs, ws.loss_slots);
 }
 
 template <bool COUNT, bool L1>
 void blend_fwd_variant(const ViewsIO& io, int nv, int total, int per, const float bg[3], const Workspace& ws,
-                       const uint32_t* vals, hipStream_t st) {
+                       hipStream_t st) {
   if (io.batch == 64)
-    blend_fwd_batch<COUNT, L1, 64>(io, nv, total, per, bg, ws, vals, st);
+    blend_fwd_batch<COUNT, L1, 64>(io, nv, total, per, bg, ws, st);
   else if (io.batch == 256)
-    blend_fwd_batch<COUNT, L1, 256>(io, nv, total, per, bg, ws, vals, st);
+    blend_fwd_batch<COUNT, L1, 256>(io, nv, total, per, bg, ws, st);
   else
-    blend_fwd_batch<COUNT, L1, 128>(io, nv, total, per, bg, ws, vals, st);
+    blend_fwd_batch<COUNT, L1, 128>(io, nv, total, per, bg, ws, st);
 }
 
 void launch_blend_fwd(const ViewsIO& io, int nv, int64_t total_tiles, const float bg[3], const Workspace& ws,
-                      const uint32_t* vals, bool count_pairs, bool l1, hipStream_t st) {
+                      bool count_pairs, bool l1, hipStream_t st) {
   const int64_t total = total_tiles * io.sn;
   if (total == 0) return;
   const int per = per_xcd(total);
@@ -867,14 +704,14 @@ void launch_blend_fwd(const ViewsIO& io, int nv, int64_t total_tiles, const floa
   iov.err = ws.err;
   if (count_pairs) {
     if (l1)
-      blend_fwd_variant<true, true>(iov, nv, (int)total, per, bg, ws, vals, st);
+      blend_fwd_variant<true, true>(iov, nv, (int)total, per, bg, ws, st);
     else
-      blend_fwd_variant<true, false>(iov, nv, (int)total, per, bg, ws, vals, st);
+      blend_fwd_variant<true, false>(iov, nv, (int)total, per, bg, ws, st);
   } else {
     if (l1)
-      blend_fwd_variant<false, true>(iov, nv, (int)total, per, bg, ws, vals, st);
+      blend_fwd_variant<false, true>(iov, nv, (int)total, per, bg, ws, st);
     else
-      blend_fwd_variant<false, false>(iov, nv, (int)total, per, bg, ws, vals, st);
+      blend_fwd_variant<false, false>(iov, nv, (int)total, per, bg, ws, st);
   }
 }
 
@@ -892,14 +729,14 @@ __global__ __launch_bounds__(256) void k_feat_rows(const float* __restrict__ fea
 }
 
 void launch_blend_feat(const ViewsIO& io, int nv, int64_t total_tiles, const FeatIO& fo, const Workspace& ws,
-                       const uint32_t* vals, hipStream_t st) {
+                       hipStream_t st) {
   if (fo.n > 0)
     k_feat_rows<<<(fo.n + 255) / 256, 256, 0, st>>>(fo.feat, fo.stride, fo.C, fo.n, reinterpret_cast<float4*>(fo.feat16));
   const int64_t total = total_tiles * io.sn;
   if (total == 0) return;
   const int per = per_xcd(total);
   const dim3 grid(per * kNumXcd), block(kLanes);
-#define DASS_FEAT(SUBT, BT) k_blend_feat<SUBT, BT><<<grid, block, 0, st>>>(io, nv, (int)total, per, fo, ws.ranges, vals, ws.rec_u)
+#define DASS_FEAT(SUBT, BT) k_blend_feat<SUBT, BT><<<grid, block, 0, st>>>(io, nv, (int)total, per, fo, ws.ranges, ws.vals, ws.rec_u)
   if (io.sub == 8) {
     if (io.batch == 64) DASS_FEAT(8, 64);
     else if (io.batch == 256) DASS_FEAT(8, 256);
@@ -931,13 +768,13 @@ void launch_loss_finish(float* slots, float* loss, float add, hipStream_t st) {
 }
 
 void launch_blend_bwd(const ViewsIO& io, int nv, int64_t total_tiles, const float bg[3], const Workspace& ws,
-                      const uint32_t* vals, int n, hipStream_t st) {
+                      hipStream_t st) {
   const int64_t total = total_tiles * io.sn;
   if (total == 0) return;
   const int per = per_xcd(total);
   const dim3 grid(per * kNumXcd), block(kLanes);
 #define DASS_BWD(SUBT, BT)                                                                                     \
-  k_blend_bwd<SUBT, BT><<<grid, block, 0, st>>>(io, nv, (int)total, per, bg[0], bg[1], bg[2], ws.ranges, vals, \
+  k_blend_bwd<SUBT, BT><<<grid, block, 0, st>>>(io, nv, (int)total, per, bg[0], bg[1], bg[2], ws.ranges, ws.vals, \
                                                 ws.rec_u, ws.g2d)
   if (io.sub == 8) {
     if (io.batch == 64) DASS_BWD(8, 64);
@@ -951,11 +788,11 @@ void launch_blend_bwd(const ViewsIO& io, int nv, int64_t total_tiles, const floa
 #undef DASS_BWD
 }
 
-void launch_debug_keys(int view, int n, const Workspace& ws, const uint32_t* keys_sorted, const uint32_t* vals_sorted,
-                       uint32_t lo, uint32_t cnt, const CamK& cam, uint64_t* kout, uint32_t* vout, hipStream_t st) {
+void launch_debug_keys(int view, int n, const Workspace& ws, uint32_t tile, uint32_t lo, uint32_t cnt, uint64_t* kout,
+                       uint32_t* vout, hipStream_t st) {
   if (cnt > 0)
-    k_debug_keys<<<(cnt + 255) / 256, 256, 0, st>>>(cam.key_base, (uint32_t)((int64_t)view * n), keys_sorted,
-                                                     vals_sorted, ws.rec_u, lo, cnt, kout, vout);
+    k_debug_keys<<<(cnt + 255) / 256, 256, 0, st>>>(tile, (uint32_t)((int64_t)view * n), ws.vals, ws.rec_u, lo, cnt,
+                                                     kout, vout);
 }
 
 }  // namespace dass

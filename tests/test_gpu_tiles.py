@@ -199,3 +199,29 @@ def test_backward_rejects_another_subtile_size_than_the_forwards():
     with pytest.raises(DassError, match="DASS_E_INVALID"):
         ctx.render_bwd(g, cams, BG, out, [torch.as_tensor(d, device="cuda") for d in dls], g.zeros_like())
     ctx.sync()
+
+
+@pytest.mark.parametrize("n,log_scale", [(1, -2.0), (63, -4.0), (64, -1.0), (65, -4.0), (513, -4.0), (1100, -2.0)])
+@pytest.mark.parametrize("tile", [(16, 16), (64, 64)])
+def test_tile_lists_at_group_chunk_and_window_edges(n, log_scale, tile):
+    """The binning places 64 Gaussians at a time (by key, or by tile where most rectangles cover most
+    of their common box), in chunks of up to 512 and windows of at most 256 (count: 1,024) tiles: Gaussian counts
+    around 64 and 512, narrow and wide footprints, views of 1,408 and 30 tiles and one 1,040 tiles
+    wide.  Lists and ranges of every view bit-exact against the oracle."""
+    scene, _ = synth.frustum_scene(90 + n, n, 0, log_scale, 0.5)
+    cams = [synth.make_camera(np.eye(3), (0.0, 0.0, 0.0), w, h) for w, h in ((700, 500), (90, 75), (16640, 40))]
+    log(f"[lists] n {n} log-scale {log_scale} tile {tile}")
+    g = to_gpu(scene)
+    ctx = make_ctx(scene.n, cams, keys_per_gaussian=4200)
+    ctx.tile = tile
+    ctx.render_fwd(g, cams, BG)
+    ctx.sync()
+    for v, cam in enumerate(cams):
+        p = oracle.project(scene, cam, tile)
+        assert not np.any(p.flags & oracle.FLAG_RADIUS)
+        k, val, r = oracle.keys(p, cam, tile)
+        TX, TY = oracle.tiles_of(cam, tile)
+        gk, gv, gr = ctx.debug_keys(v, k.size + 16, TX * TY)
+        np.testing.assert_array_equal(gk, k)
+        np.testing.assert_array_equal(gv, val)
+        np.testing.assert_array_equal(gr, r)
