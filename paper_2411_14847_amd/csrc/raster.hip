@@ -524,6 +524,280 @@ __global__ __launch_bounds__(kLanes) void k_blend_bwd(ViewsIO io, int nv, int to
   }
 }
 
+// ---- one wave per quadrant ------------------------------------------------------------------
+// The same blend with a workgroup of four waves per 16x16 sub-tile, wave k taking quadrant k (one
+// pixel per lane), for calls of few sub-tiles: there the time is that of one wave walking its list,
+// entry after entry, and here a list is walked by four waves, each over the entries that reach
+// its own quadrant only.  The four stage a batch together (one entry per thread, not compacted:
+// a 64-bit mask per quadrant and 64 entries says which to walk) and read the next entry from LDS
+// while they blend the current one.  Pixels see the operations of the kernels above in the same
+// order, so the images, n_contrib and, up to the order of the sums, the gradients are the same.
+constexpr int kQB = 256;  // threads per workgroup = entries per batch
+
+template <bool L1>
+__global__ __launch_bounds__(kQB) void k_blend_fwd_q(ViewsIO io, int nv, int total_blocks, int per, float bg0, float bg1,
+                                                     float bg2, const uint2* __restrict__ ranges,
+                                                     const uint32_t* __restrict__ vals, const Rec* __restrict__ rec,
+                                                     float* __restrict__ loss_slots) {
+  __shared__ FwdStage s_st[kQB];
+  __shared__ uint64_t s_q[4][4];  // [quadrant][64 entries]
+  const int lb = xcd_logical(blockIdx.x, per);
+  if (lb >= total_blocks) return;
+  const int b = lb / io.sn, sub = lb - b * io.sn;
+  const int v = view_of(io, nv, b);
+  const ViewIO& V = io.v[v];
+  const int t = b - V.tile_base;
+  const int tx = t % V.TX, ty = t / V.TX;
+  const int ox = tx * io.tw + (sub % io.sx) * 16, oy = ty * io.th + (sub / io.sx) * 16;
+  if (ox >= V.W || oy >= V.H) return;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int k = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int qx = lane & 7, qy = lane >> 3;
+  const int px = ox + qx + 8 * (k & 1), py = oy + qy + 8 * (k >> 1);
+  const float kx = (float)(8 * (k & 1)), ky = (float)(8 * (k >> 1));
+  const float fx0 = (float)ox, fy0 = (float)oy;
+  const uint2 r = ranges[b];
+  if (r.y - r.x > (uint32_t)kPosMask) {
+    if (tid == 0) atomicOr(io.err, kErrListTooLong);
+    return;
+  }
+  float T = 1.f, thr = (px < V.W && py < V.H) ? kAlphaMin : kNever, c0 = 0.f, c1 = 0.f, c2 = 0.f;
+  uint32_t last = 0;
+  bool alive = __ballot(thr < 1.f) != 0;  // uniform over the wave
+  for (uint32_t start = r.x; start < r.y; start += kQB) {
+    if (!__syncthreads_or(alive)) break;  // also: the batch before has been walked
+    uint32_t qm = 0;
+    if (start + tid < r.y) {
+      const Rec R = rec[vals[start + tid]];
+      const float2 xy = make_float2((R.r0.x - fx0) + R.r0.z, (R.r0.y - fy0) + R.r0.w);
+      qm = quad_mask<2>(xy.x, xy.y, R.r1.x, R.r1.y, R.r1.z, R.r1.w);
+      if (qm) {
+        s_st[tid].xy = xy;
+        s_st[tid].co = make_float4(-0.5f * kLog2e * R.r1.x, -kLog2e * R.r1.y, -0.5f * kLog2e * R.r1.z, __log2f(R.r1.w));
+        s_st[tid].rgb = make_float4(R.r2.x, R.r2.y, R.r2.z, __uint_as_float((uint32_t)(start - r.x) + tid + 1));
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+      const uint64_t m = __ballot((qm >> i) & 1u);
+      if (lane == 0) s_q[i][k] = m;
+    }
+    __syncthreads();
+    for (int g = 0; g < 4 && alive; g++) {
+      const uint64_t mv = s_q[k][g];
+      uint64_t m = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)mv) |
+                   ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(mv >> 32)) << 32);
+      if (m == 0) continue;
+      const FwdStage* st = s_st + g * 64;
+      int j = __builtin_ctzll(m);
+      float2 xy = st[j].xy;
+      float4 co = st[j].co, c = st[j].rgb;
+      while (m != 0 && alive) {
+        m &= m - 1;
+        const int jn = m ? (int)__builtin_ctzll(m) : j;
+        const float2 xy_n = st[jn].xy;  // the next entry, read while this one is blended
+        const float4 co_n = st[jn].co, c_n = st[jn].rgb;
+        const float dx = (xy.x - (float)qx) - kx, dy = (xy.y - (float)qy) - ky;
+        // the operations of k_blend_fwd
+        const float pw = fmaf(dx, fmaf(co.x, dx, co.y * dy), fmaf(co.z * dy, dy, co.w));
+        const float a = fminf(kAlphaMax, __builtin_amdgcn_exp2f(pw));
+        const bool ok = a >= thr;
+        float wgt = ok ? a * T : 0.f;
+        T -= wgt;
+        bool take = ok;
+        const bool stop = T < kTStop;
+        if (__builtin_expect(__ballot(stop) != 0, 0)) {
+          T = stop ? T + wgt : T;
+          wgt = stop ? 0.f : wgt;
+          take = ok && !stop;
+          thr = stop ? kNever : thr;
+          alive = __ballot(thr < 1.f) != 0;
+        }
+        c0 = fmaf(c.x, wgt, c0);
+        c1 = fmaf(c.y, wgt, c1);
+        c2 = fmaf(c.z, wgt, c2);
+        last = take ? __float_as_uint(c.w) : last;
+        xy = xy_n;
+        co = co_n;
+        c = c_n;
+      }
+    }
+  }
+  float l1sum = 0.f;
+  if (px < V.W && py < V.H) {
+    const int64_t hw = (int64_t)V.W * V.H;
+    const int64_t pix = (int64_t)py * V.W + px;
+    const float col[3] = {c0 + T * bg0, c1 + T * bg1, c2 + T * bg2};
+    if (!L1 || V.rgb) {
+#pragma unroll
+      for (int c = 0; c < 3; c++) V.rgb[c * hw + pix] = col[c];
+    }
+    V.t_final[pix] = T;
+    V.n_contrib[pix] = (int)last;
+    if (L1) {
+      const float sc = V.l1_scale;
+      float e = 0.f;
+#pragma unroll
+      for (int c = 0; c < 3; c++) {
+        const float d = col[c] - V.target[c * hw + pix];
+        V.dl_out[c * hw + pix] = d > 0.f ? sc : (d < 0.f ? -sc : 0.f);
+        e += fabsf(d);
+      }
+      if (V.err) V.err[pix] = e * (1.0f / 3.0f);
+      l1sum = e;
+    }
+  }
+  if (L1) {
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) l1sum += __shfl_xor(l1sum, d, 64);
+    if (lane == 0) atomicAdd(&loss_slots[(lb * 4 + k) % kLossSlots], l1sum * V.l1_scale);
+  }
+}
+
+// The adjoint: an entry's nine sums over a quadrant are added to the batch's rows in LDS, and the
+// batch's rows go to global memory once for the four quadrants.
+__global__ __launch_bounds__(kQB) void k_blend_bwd_q(ViewsIO io, int nv, int total_blocks, int per, float bg0, float bg1,
+                                                     float bg2, const uint2* __restrict__ ranges,
+                                                     const uint32_t* __restrict__ vals, const Rec* __restrict__ rec,
+                                                     float* __restrict__ g2d) {
+  __shared__ BwdStage s_st[kQB];
+  __shared__ float s_acc[kQB * 9];
+  __shared__ uint64_t s_q[4][4];
+  __shared__ int s_last[4];
+  const int lb = xcd_logical(blockIdx.x, per);
+  if (lb >= total_blocks) return;
+  const int b = lb / io.sn, sub = lb - b * io.sn;
+  const int v = view_of(io, nv, b);
+  const ViewIO& V = io.v[v];
+  const int t = b - V.tile_base;
+  const int tx = t % V.TX, ty = t / V.TX;
+  const int ox = tx * io.tw + (sub % io.sx) * 16, oy = ty * io.th + (sub / io.sx) * 16;
+  if (ox >= V.W || oy >= V.H) return;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int k = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int qx = lane & 7, qy = lane >> 3;
+  const int px = ox + qx + 8 * (k & 1), py = oy + qy + 8 * (k >> 1);
+  const float kx = (float)(8 * (k & 1)), ky = (float)(8 * (k >> 1));
+  const float fx0 = (float)ox, fy0 = (float)oy;
+  const uint2 r = ranges[b];
+  if (r.y - r.x > (uint32_t)kPosMask) return;
+  const int64_t hw = (int64_t)V.W * V.H;
+  float T = 1.f, dC0 = 0.f, dC1 = 0.f, dC2 = 0.f;
+  int last = 0;
+  if (px < V.W && py < V.H) {
+    const int64_t pix = (int64_t)py * V.W + px;
+    T = V.t_final[pix];
+    last = V.n_contrib[pix];
+    dC0 = V.dl[pix];
+    dC1 = V.dl[hw + pix];
+    dC2 = V.dl[2 * hw + pix];
+  }
+  float nS = -(bg0 * dC0 + bg1 * dC1 + bg2 * dC2);
+  int mx = last;
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) mx = max(mx, __shfl_xor(mx, d, 64));
+  if (lane == 0) s_last[k] = mx;
+  __syncthreads();
+  int qlast[4], max_all = 0;
+#pragma unroll
+  for (int i = 0; i < 4; i++) {
+    qlast[i] = s_last[i];
+    max_all = max(max_all, qlast[i]);
+  }
+  const int max_last = __builtin_amdgcn_readfirstlane(min(max_all, (int)(r.y - r.x)));
+  if (max_last <= 0) return;  // uniform over the workgroup
+  const int slot = kRedSlot[lane >> 2];
+  const bool writes = (lane & 3) == 0 && slot >= 0;
+  for (int bi = (max_last + kQB - 1) / kQB - 1; bi >= 0; bi--) {
+    const int idx0 = bi * kQB;
+    uint32_t qm = 0;
+    if (idx0 + tid < max_last) {
+      const uint32_t p = vals[r.x + (uint32_t)(idx0 + tid)];
+      const Rec R = rec[p];
+      const float2 xy = make_float2((R.r0.x - fx0) + R.r0.z, (R.r0.y - fy0) + R.r0.w);
+      const float4 cn = R.r1;
+      qm = quad_mask<2>(xy.x, xy.y, cn.x, cn.y, cn.z, cn.w);
+#pragma unroll
+      for (int i = 0; i < 4; i++)
+        if (idx0 + tid >= qlast[i]) qm &= ~(1u << i);
+      if (qm) {
+        s_st[tid].xy = xy;
+        s_st[tid].co = make_float4(-0.5f * kLog2e * cn.x, -kLog2e * cn.y, -0.5f * kLog2e * cn.z, __log2f(cn.w));
+        s_st[tid].rgb = make_float4(R.r2.x, R.r2.y, R.r2.z, __uint_as_float(cn.w >= kAlphaMax ? kClampBit : 0u));
+        s_st[tid].p = p;
+        s_st[tid].io = 1.0f / cn.w;
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 9; i++) s_acc[i * kQB + tid] = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+      const uint64_t m = __ballot((qm >> i) & 1u);
+      if (lane == 0) s_q[i][k] = m;
+    }
+    __syncthreads();
+    for (int g = 3; g >= 0; g--) {
+      const uint64_t mv = s_q[k][g];
+      uint64_t m = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)mv) |
+                   ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(mv >> 32)) << 32);
+      if (m == 0) continue;
+      const BwdStage* st = s_st + g * 64;
+      int j = 63 - __builtin_clzll(m);
+      float2 xy = st[j].xy;
+      float4 co = st[j].co, c = st[j].rgb;
+      float iop = st[j].io;
+      while (m != 0) {
+        m &= ~(1ull << j);
+        const int jn = m ? 63 - (int)__builtin_clzll(m) : j;
+        const float2 xy_n = st[jn].xy;
+        const float4 co_n = st[jn].co, c_n = st[jn].rgb;
+        const float iop_n = st[jn].io;
+        const float dx = (xy.x - (float)qx) - kx, dy = (xy.y - (float)qy) - ky;
+        // the operations of k_blend_bwd
+        const float pw = fmaf(dx, fmaf(co.x, dx, co.y * dy), fmaf(co.z * dy, dy, co.w));
+        const float araw = __builtin_amdgcn_exp2f(pw);
+        const float a = fminf(kAlphaMax, araw);
+        const bool take = (idx0 + g * 64 + j < last) && (a >= kAlphaMin);
+        if (__ballot(take) != 0) {
+          const float ae = take ? a : 0.f;
+          T = T * __builtin_amdgcn_rcpf(1.f - ae);
+          const float wgt = ae * T;
+          float s[9];
+          s[6] = wgt * dC0;
+          s[7] = wgt * dC1;
+          s[8] = wgt * dC2;
+          const float ed = fmaf(c.x, dC0, fmaf(c.y, dC1, fmaf(c.z, dC2, nS)));
+          nS = fmaf(-ae, ed, nS);
+          float dP = wgt * ed;
+          if (__float_as_uint(c.w) != 0u) dP = araw < kAlphaMax ? dP : 0.f;
+          s[5] = dP * iop;
+          s[0] = dP * dx;
+          s[1] = dP * dy;
+          s[2] = s[0] * dx;
+          s[3] = s[0] * dy;
+          s[4] = s[1] * dy;
+          const float tot = wave_reduce9(s);
+          if (writes) atomicAdd(&s_acc[(g * 64 + j) * 9 + slot], tot);
+        }
+        xy = xy_n;
+        co = co_n;
+        c = c_n;
+        iop = iop_n;
+        j = jn;
+      }
+    }
+    __syncthreads();
+    // nine consecutive threads per entry: one 36-byte row
+#pragma unroll
+    for (int i = 0; i < 9; i++) {
+      const int x = i * kQB + tid;
+      const float val = s_acc[x];
+      if (val != 0.f) atomicAdd(&g2d[(int64_t)s_st[x / 9].p * 9 + x % 9], val);
+    }
+    __syncthreads();
+  }
+}
+
 // Identity-feature render: the forward's walk (same lists, culling, alpha, transmittance and
 // stop, so the weights alpha_i T_i are the colour render's) accumulating up to kFeatMaxC
 // per-Gaussian features instead of colours, with no background.
@@ -668,6 +942,18 @@ void launch_fill_u32(uint32_t* p, uint32_t v, int64_t n, hipStream_t st) {
   k_fill_u32<<<(unsigned)blocks, 256, 0, st>>>(p, v, n);
 }
 
+// Whether a call's 16x16 sub-tiles are walked by one wave per quadrant: up to where the chip's
+// 1,024 SIMDs hold about six (forward) or four (backward) of the four-quadrant waves each, so the
+// longest list sets the time.  Measured, us forward / backward, four quadrants per wave -> one:
+// 64 sub-tiles (2k Gaussians at 128x128) 65 -> 22 / 125 -> 40; 1,280 (7k, 20 views at 128x128)
+// 243 -> 84 / 484 -> 182; 2,760 (200k at 960x720) 126 -> 83 / 195 -> 174; 5,632 (200k at 1352x1014)
+// 108 -> 95 / 205 -> 229; 8,160 115 -> 119 / 237 -> 295; 22,528 233 -> 292 / 512 -> 763 (there the
+// LDS reads, one entry per quadrant instead of per four, and the reductions bound it).
+constexpr int64_t kByQuadrantFwd = 6144, kByQuadrantBwd = 4096;
+static inline bool by_quadrant(const ViewsIO& io, int64_t sub_tiles, int64_t most) {
+  return io.sub == 16 && sub_tiles <= most;
+}
+
 static inline int per_xcd(int64_t total_tiles) { return (int)((total_tiles + kNumXcd - 1) / kNumXcd); }
 
 // One wave per (tile, sub-tile); the sub-tiles of a tile are consecutive logical blocks, so they
@@ -702,6 +988,16 @@ void launch_blend_fwd(const ViewsIO& io, int nv, int64_t total_tiles, const floa
   const int per = per_xcd(total);
   ViewsIO iov = io;
   iov.err = ws.err;
+  if (by_quadrant(io, total, kByQuadrantFwd) && !count_pairs) {
+    const dim3 grid(per * kNumXcd);
+    if (l1)
+      k_blend_fwd_q<true><<<grid, kQB, 0, st>>>(iov, nv, (int)total, per, bg[0], bg[1], bg[2], ws.ranges, ws.vals,
+                                                ws.rec_u, ws.loss_slots);
+    else
+      k_blend_fwd_q<false><<<grid, kQB, 0, st>>>(iov, nv, (int)total, per, bg[0], bg[1], bg[2], ws.ranges, ws.vals,
+                                                 ws.rec_u, ws.loss_slots);
+    return;
+  }
   if (count_pairs) {
     if (l1)
       blend_fwd_variant<true, true>(iov, nv, (int)total, per, bg, ws, st);
@@ -773,6 +1069,11 @@ void launch_blend_bwd(const ViewsIO& io, int nv, int64_t total_tiles, const floa
   if (total == 0) return;
   const int per = per_xcd(total);
   const dim3 grid(per * kNumXcd), block(kLanes);
+  if (by_quadrant(io, total, kByQuadrantBwd)) {
+    k_blend_bwd_q<<<grid, kQB, 0, st>>>(io, nv, (int)total, per, bg[0], bg[1], bg[2], ws.ranges, ws.vals, ws.rec_u,
+                                        ws.g2d);
+    return;
+  }
 #define DASS_BWD(SUBT, BT)                                                                                     \
   k_blend_bwd<SUBT, BT><<<grid, block, 0, st>>>(io, nv, (int)total, per, bg[0], bg[1], bg[2], ws.ranges, ws.vals, \
                                                 ws.rec_u, ws.g2d)
