@@ -160,6 +160,8 @@ dass_status allocate(dass_ctx ctx, const dass_limits& l) {
   ALLOC(w.tile_tot, w.cap_tiles + 4);
   w.cap_bin = bin_hist_elems(w.cap_tiles);
   ALLOC(w.bin_hist, w.cap_bin);
+  ALLOC(w.depth_hist, depth_hist_elems(l.max_views));
+  ALLOC(w.far, DASS_MAX_VIEWS);
   ALLOC(w.hist, 2048 * 1024 + 2048);  // [radix][max sort blocks] counts + radix digit totals
   ALLOC(w.scan_tmp, scan_tmp_elems(vn));
   ALLOC(w.counters, 16);
@@ -176,7 +178,8 @@ dass_status allocate(dass_ctx ctx, const dass_limits& l) {
   ALLOC(w.field_tpart, (size_t)kFieldPartialFloats);
   ALLOC(w.err, 1);
 #undef ALLOC
-  w.gid_s = w.dval[0];
+  w.gid_s = w.dval[1];
+  HIP_TRY(ctx, hipMemset(w.far, 0, DASS_MAX_VIEWS * sizeof(uint32_t)));
   HIP_TRY(ctx, hipMemset(w.counters, 0, 16 * sizeof(uint32_t)));
   HIP_TRY(ctx, hipMemset(w.err, 0, sizeof(uint32_t)));
   HIP_TRY(ctx, hipMemset(w.pairs, 0, 2 * sizeof(unsigned long long)));
@@ -449,18 +452,14 @@ dass_status render_fwd_impl(dass_ctx ctx, const dass_gaussians* g, const dass_ca
   hipStream_t st = (hipStream_t)stream;
   Workspace& ws = ctx->ws;
   const SceneK sc = scene_of(g);
-  const int64_t vn = (int64_t)n_views * g->n;
   const bool count_pairs = opts && (opts->flags & DASS_FLAG_COUNT_PAIRS);
   // 1. projection
   stage_begin(ctx, DASS_STAGE_PROJECT, st);
   launch_preprocess(sc, ck, n_views, ws, st);
   stage_end(ctx, DASS_STAGE_PROJECT, st);
-  // 2. per-view depth order: sort (view << 31 | depth bits, index)
+  // 2. per-view depth order
   stage_begin(ctx, DASS_STAGE_DEPTH_SORT, st);
-  launch_fill_u32(ws.counters + 2, (uint32_t)vn, 1, st);
-  const int dcur = radix_sort_u64(ws.dkey, ws.dval, ws.counters + 2, vn, 0, 31 + bit_width((uint64_t)(n_views - 1)),
-                                  ws.hist, sort_blocks_for(vn), st);
-  ws.gid_s = ws.dval[dcur];
+  launch_depth_sort(g->n, n_views, ws.dkey, ws.dval, ws.depth_hist, ws.far, st);
   stage_end(ctx, DASS_STAGE_DEPTH_SORT, st);
   // 3. tile lists in depth order
   stage_begin(ctx, DASS_STAGE_BINNING, st);
@@ -1067,7 +1066,7 @@ dass_status densify_append(dass_ctx ctx, dass_gaussians* g, const float* const* 
   launch_fill_u32(ws.counters + 1, 0u, 1, st);
   // members packed in index order into u32 keys (the depth-sort buffers, free here), the score key
   // staged in the second buffer; a stable 32-bit sort ranks by score, ties by index
-  uint32_t* k32[2] = {reinterpret_cast<uint32_t*>(ws.dkey[0]), reinterpret_cast<uint32_t*>(ws.dkey[1])};
+  uint32_t* k32[2] = {ws.dkey[0], ws.dkey[1]};
   launch_densify_select(sc, a, gradnorm_sum, grad_count, g->n_base, ws.keep, ws.keep_scan, ws.scan_tmp, k32[1], k32[0],
                         ws.dval[0], ws.counters + 1, st);
   const int cur = radix_sort_u32(k32, ws.dval, ws.counters + 1, g->n_base, 0, 32, ws.hist, sort_blocks_for(g->n_base),

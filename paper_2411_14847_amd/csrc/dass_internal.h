@@ -192,11 +192,14 @@ struct Workspace {
   // per (view, gaussian), view-major, unsorted
   Rec* rec_u = nullptr;
   uint2* rect_u = nullptr;         // (x0 | y0 << 16, x1 | y1 << 16)
-  uint64_t* dkey[2] = {nullptr, nullptr};
+  uint32_t* dkey[2] = {nullptr, nullptr};  // depth keys
   uint32_t* dval[2] = {nullptr, nullptr};
   // per sorted position p (view-major, depth order)
   uint2* rect_s = nullptr;
-  uint32_t* gid_s = nullptr;       // gid of sorted position p
+  uint32_t* gid_s = nullptr;       // gid of sorted position p (dval[1])
+  uint32_t* depth_hist = nullptr;  // depth sort: digit counts per view and block
+  uint32_t* far = nullptr;         // [DASS_MAX_VIEWS] the view has depths whose key needs more than 27
+                                   // bits (set by the projection, cleared by the depth sort)
   float* g2d = nullptr;            // [cap_vn][9], row v * n + g: blend-backward sums (moments of
                                    // dL/d(exponent) over the offsets, d opacity, d rgb)
   uint8_t* vis = nullptr;          // [cap_vn], row v * n + g: bit 3 visible, bit c colour channel c
@@ -210,7 +213,7 @@ struct Workspace {
   // scratch
   uint32_t* hist = nullptr;        // sort histograms
   uint64_t* scan_tmp = nullptr;    // scan block sums
-  uint32_t* counters = nullptr;    // [1] = densify |S|, [2] = depth-sort count, [4..5] = keys of the call (u64)
+  uint32_t* counters = nullptr;    // [1] = densify |S|, [4..5] = keys of the call (u64)
   unsigned long long* pairs = nullptr;  // [0] evaluated, [1] blended (pair counting only)
   float* loss_slots = nullptr;          // [kLossSlots] partial sums of the fused L1 loss
   float* field_part = nullptr;          // [kFieldMaxBlocks][field_part_stride] weight-gradient partials
@@ -240,12 +243,19 @@ size_t scan_tmp_elems(int64_t n);
 // LSD radix sort of (key, value) pairs on bits [begin_bit, end_bit); the element count is read
 // from device memory (*d_count) and must not exceed max_count.  Keys and values ping-pong
 // between buffer 0 and 1; returns the index of the buffer holding the result.
-int radix_sort_u64(uint64_t* keys[2], uint32_t* vals[2], const uint32_t* d_count, int64_t max_count,
-                   int begin_bit, int end_bit, uint32_t* hist, int blocks, hipStream_t st);
 int radix_sort_u32(uint32_t* keys[2], uint32_t* vals[2], const uint32_t* d_count, int64_t max_count,
                    int begin_bit, int end_bit, uint32_t* hist, int blocks, hipStream_t st,
                    int digit_cap = 11);
 int sort_blocks_for(int64_t max_count);
+// Depth keys: float32 bits of a visible Gaussian's depth less those of the near plane, or
+// kDepthInvisible.
+constexpr uint32_t kDepthNearBits = 0x3E4CCCCDu;  // 0.2f
+constexpr uint32_t kDepthInvisible = 0x7FFFFFFFu;
+constexpr uint32_t kDepthFar = 0x7FFFFFFu;        // from here on a key needs more than 27 bits
+size_t depth_hist_elems(int max_views);
+// Orders the n Gaussians of every view by depth, ties by index: keys[0] -> indices in vals[1].
+void launch_depth_sort(int n, int nv, uint32_t* const keys[2], uint32_t* const vals[2], uint32_t* hist, uint32_t* far,
+                       hipStream_t st);
 
 // binning.hip
 int64_t bin_hist_elems(int64_t max_tiles);

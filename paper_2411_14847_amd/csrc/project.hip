@@ -315,8 +315,8 @@ __device__ __forceinline__ void colour(const GT& G, const CamK& cam, const float
 template <int DEG>
 __global__ __launch_bounds__(256) void k_preprocess(SceneK sc, CamsK cams, int nv, Rec* __restrict__ rec,
                                                     uint2* __restrict__ rect,
-                                                    uint8_t* __restrict__ vis, uint64_t* __restrict__ dkey,
-                                                    uint32_t* __restrict__ dval) {
+                                                    uint8_t* __restrict__ vis, uint32_t* __restrict__ dkey,
+                                                    uint32_t* __restrict__ far) {
   constexpr int K = (DEG + 1) * (DEG + 1);
   __shared__ ClipTable s_clip;
   fill_clip_table(cams, nv, s_clip);
@@ -352,9 +352,10 @@ __global__ __launch_bounds__(256) void k_preprocess(SceneK sc, CamsK cams, int n
       rect[i] = make_uint2(0, 0);
     }
     rec[i] = r;
-    // the depth is a positive float (or the all-ones sentinel), so 31 bits order it
-    dkey[i] = ((uint64_t)v << 31) | (uint64_t)(V.depth_bits & 0x7FFFFFFFu);
-    dval[i] = (uint32_t)g;
+    // a visible depth is a float not below the near plane's, so its bits order it
+    const uint32_t dk = V.visible ? V.depth_bits - kDepthNearBits : kDepthInvisible;
+    dkey[i] = dk;
+    if (V.visible && dk >= kDepthFar) atomicOr(&far[v], 1u);
   }
 }
 
@@ -647,16 +648,16 @@ void launch_preprocess(const SceneK& s, const CamsK& cams, int nv, Workspace& ws
   dim3 grid(blocks_g, vs), block(256);
   switch (s.deg) {
     case 0: k_preprocess<0><<<grid, block, 0, st>>>(s, cams, nv, ws.rec_u, ws.rect_u, ws.vis, ws.dkey[0],
-                                                     ws.dval[0]);
+                                                     ws.far);
       break;
     case 1: k_preprocess<1><<<grid, block, 0, st>>>(s, cams, nv, ws.rec_u, ws.rect_u, ws.vis, ws.dkey[0],
-                                                     ws.dval[0]);
+                                                     ws.far);
       break;
     case 2: k_preprocess<2><<<grid, block, 0, st>>>(s, cams, nv, ws.rec_u, ws.rect_u, ws.vis, ws.dkey[0],
-                                                     ws.dval[0]);
+                                                     ws.far);
       break;
     default: k_preprocess<3><<<grid, block, 0, st>>>(s, cams, nv, ws.rec_u, ws.rect_u, ws.vis, ws.dkey[0],
-                                                     ws.dval[0]);
+                                                     ws.far);
       break;
   }
 }

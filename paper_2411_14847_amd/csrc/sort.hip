@@ -277,6 +277,362 @@ __global__ __launch_bounds__(kSortThreads) void k_scatter(const K* __restrict__ 
   }
 }
 
+// ---- per-view depth order --------------------------------------------------------------------
+// The depth keys of a view are the float32 bits of its Gaussians' depths less those of the near
+// plane (positive floats order as their bits), so below 2^27 - 1 for depths up to about 13,000,
+// and kDepthInvisible for a Gaussian that is not drawn.  The sort is stable: equal depths keep
+// index order.
+// Bound: a pass reads and writes 8 bytes per Gaussian-view (4 in the upsweep); with 4M of them the
+// scatter moves 64 MB in 33 us, short of the copy rate by the latency of its chain (digit counts, keys, 16 ranks,
+// two reorderings in LDS).  Against four 9-bit passes over 64-bit (view, depth) keys: 20 views of
+// 200k 0.209 -> 0.127 ms, 4 of 1M 0.214 -> 0.178, one of 200k 65 -> 65 us in 7 instead of 13
+// launches; small views (12 launches before) 20 x 12k 0.084 -> 0.032 ms, 1 x 2k 50 -> 12 us.
+constexpr int kDepthBits = 9;  // digit
+constexpr int kDepthR = 1 << kDepthBits;
+
+// Rank of a lane's digit among the lanes of the wave, and the count of the digits before: the lanes
+// of a digit meet in the digit's mask (zero between calls), its last lane advances the count.
+__device__ __forceinline__ uint32_t wave_rank(uint64_t* mask, uint16_t* count, uint32_t d, bool valid, int lane,
+                                              uint64_t lt) {
+  if (valid) atomicOr(reinterpret_cast<unsigned long long*>(&mask[d]), 1ull << lane);
+  wave_lds_sync();
+  const uint64_t m = mask[d];
+  const uint32_t base = count[d];
+  wave_lds_sync();
+  if (valid && (m >> lane) == 1ull) {
+    count[d] = (uint16_t)(base + __popcll(m));
+    mask[d] = 0ull;
+  }
+  wave_lds_sync();
+  return base + __popcll(m & lt);
+}
+
+// Views of few Gaussians: the whole view in LDS, one workgroup per view.  Thread t of wave w
+// holds elements 64 (IT w + s) + t, s < IT, in registers between passes; the passes cover the
+// range of the view's own visible keys, 9 bits each.
+constexpr int kDepthLdsThreads = 1024, kDepthLdsWaves = 16;
+template <int IT>
+__global__ __launch_bounds__(kDepthLdsThreads) void k_depth_lds(int n, const uint32_t* __restrict__ keys,
+                                                                uint32_t* __restrict__ out,
+                                                                uint32_t* __restrict__ far) {
+  __shared__ uint32_t s_x[IT * kDepthLdsThreads];  // in digit order: the keys, then the values
+  __shared__ uint64_t s_mask[kDepthLdsWaves][kDepthR];
+  __shared__ uint16_t s_wc[kDepthLdsWaves][kDepthR];
+  __shared__ uint32_t s_off[kDepthR];
+  __shared__ uint32_t s_red[2][kDepthLdsWaves];
+  const int v = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int64_t row = (int64_t)v * n;
+  const int first = wave * 64 * IT + lane;  // element of slot 0
+  uint32_t key[IT], val[IT];
+  uint32_t lo = 0xFFFFFFFFu, hi = 0;
+#pragma unroll
+  for (int s = 0; s < IT; s++) {
+    const int i = first + s * 64;
+    key[s] = i < n ? keys[row + i] : kDepthInvisible;
+    val[s] = (uint32_t)i;
+    if (key[s] != kDepthInvisible) {
+      lo = min(lo, key[s]);
+      hi = max(hi, key[s]);
+    }
+  }
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) {
+    lo = min(lo, (uint32_t)__shfl_xor((int)lo, d, 64));
+    hi = max(hi, (uint32_t)__shfl_xor((int)hi, d, 64));
+  }
+  if (lane == 0) {
+    s_red[0][wave] = lo;
+    s_red[1][wave] = hi;
+  }
+  if (tid == 0) far[v] = 0;  // the other path's flag: not needed here
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < kDepthLdsWaves; w++) {
+    lo = min(lo, s_red[0][w]);
+    hi = max(hi, s_red[1][w]);
+  }
+  const uint32_t top = hi >= lo ? hi - lo + 1 : 0u;  // the key of what is not drawn
+  const int bits = 32 - __builtin_clz(top | 1u);
+#pragma unroll
+  for (int s = 0; s < IT; s++) key[s] = key[s] == kDepthInvisible ? top : key[s] - lo;
+  const uint64_t lt = lanemask_lt();
+  for (int d = lane; d < kDepthR; d += 64) s_mask[wave][d] = 0;
+  for (int shift = 0; shift < bits; shift += kDepthBits) {
+    for (int d = lane; d < kDepthR; d += 64) s_wc[wave][d] = 0;
+    wave_lds_sync();
+    uint32_t rank[IT];
+#pragma unroll
+    for (int s = 0; s < IT; s++)  // (elements past n stay out: their order is the last)
+      rank[s] = wave_rank(s_mask[wave], s_wc[wave], (key[s] >> shift) & (kDepthR - 1), first + s * 64 < n, lane, lt);
+    __syncthreads();
+    if (tid < kDepthR) {  // digit tid: prefix over the waves, its count in s_off
+      uint32_t run = 0;
+#pragma unroll
+      for (int w = 0; w < kDepthLdsWaves; w++) {
+        const uint32_t x = s_wc[w][tid];
+        s_wc[w][tid] = (uint16_t)run;
+        run += x;
+      }
+      const uint32_t inc = wave_incl_scan(run);
+      s_off[tid] = inc - run;
+      if (lane == 63) s_red[0][wave] = inc;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < IT; s++)
+      if (first + s * 64 < n) {
+        const uint32_t d = (key[s] >> shift) & (kDepthR - 1);
+        rank[s] += s_off[d] + s_wc[wave][d];
+#pragma unroll
+        for (int w = 0; w < kDepthR / 64; w++) rank[s] += (uint32_t)w < d / 64 ? s_red[0][w] : 0u;
+        s_x[rank[s]] = key[s];
+      }
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < IT; s++)
+      if (first + s * 64 < n) key[s] = s_x[first + s * 64];
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < IT; s++)
+      if (first + s * 64 < n) s_x[rank[s]] = val[s];
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < IT; s++)
+      if (first + s * 64 < n) val[s] = s_x[first + s * 64];
+  }
+#pragma unroll
+  for (int s = 0; s < IT; s++)
+    if (first + s * 64 < n) out[row + first + s * 64] = val[s];
+}
+
+// Larger views: least-significant-digit radix sort of every view by itself (blockIdx.y), three
+// 9-bit digits of the keys' low 27 bits.  A pass is an upsweep (each block's digit counts) and a
+// scatter, whose blocks add up the counts of the blocks before them by themselves.
+constexpr int kDepthIt = 16;                           // pairs per thread and batch
+constexpr int kDepthBatch = kSortThreads * kDepthIt;     // 4,096
+constexpr int kDepthBlocks = 64;                       // blocks per view at most
+
+// View v and block b of it that a workgroup takes, and the block's part [lo, hi) of the view.  Each
+// XCD gets a contiguous part of the (view, block) order (workgroups are dealt to the XCDs
+// round-robin), so the short runs that neighbouring blocks write to a digit merge in one L2.
+__device__ __forceinline__ bool depth_piece(int n, int nv, int blocks, int& v, int& b, int& lo, int& hi) {
+  const int total = nv * blocks, per = (total + kNumXcd - 1) / kNumXcd;
+  const int i = (int)(blockIdx.x % kNumXcd) * per + (int)(blockIdx.x / kNumXcd);
+  if (i >= total) return false;
+  v = i / blocks;
+  b = i % blocks;
+  const int chunk = (n + blocks - 1) / blocks;
+  lo = min(b * chunk, n);
+  hi = min(lo + chunk, n);
+  return true;
+}
+
+__global__ __launch_bounds__(kSortThreads) void k_depth_upsweep(int n, int nv, int blocks, int shift,
+                                                                const uint32_t* __restrict__ keys,
+                                                                uint32_t* __restrict__ hist) {
+  __shared__ uint32_t s_h[4][kDepthR];
+  const int tid = threadIdx.x, wave = tid >> 6;
+  for (int i = tid; i < 4 * kDepthR; i += kSortThreads) (&s_h[0][0])[i] = 0;
+  __syncthreads();
+  int v, b, lo, hi;
+  if (!depth_piece(n, nv, blocks, v, b, lo, hi)) return;
+  const uint32_t* __restrict__ k = keys + (int64_t)v * n;
+  int i = lo + tid;
+  for (; i + (kDepthIt - 1) * kSortThreads < hi; i += kDepthIt * kSortThreads) {
+    uint32_t x[kDepthIt];
+#pragma unroll
+    for (int u = 0; u < kDepthIt; u++) x[u] = k[i + u * kSortThreads];
+#pragma unroll
+    for (int u = 0; u < kDepthIt; u++) atomicAdd(&s_h[wave][(x[u] >> shift) & (kDepthR - 1)], 1u);
+  }
+  for (; i < hi; i += kSortThreads) atomicAdd(&s_h[wave][(k[i] >> shift) & (kDepthR - 1)], 1u);
+  __syncthreads();
+  for (int d = tid; d < kDepthR; d += kSortThreads)
+    hist[((int64_t)v * blocks + b) * kDepthR + d] = s_h[0][d] + s_h[1][d] + s_h[2][d] + s_h[3][d];
+}
+
+// FIRST: the values are the positions themselves.  LAST: the keys are written only if the view has
+// far depths (a fourth digit follows).
+template <bool FIRST, bool LAST>
+__global__ __launch_bounds__(kSortThreads) void k_depth_scatter(int n, int nv, int blocks, int shift,
+                                                                const uint32_t* __restrict__ kin,
+                                                                const uint32_t* __restrict__ vin,
+                                                                uint32_t* __restrict__ kout, uint32_t* __restrict__ vout,
+                                                                const uint32_t* __restrict__ hist,
+                                                                const uint32_t* __restrict__ far) {
+  constexpr int D = kDepthR / kSortThreads;  // digits owned per thread
+  constexpr int kRun = kDepthIt * 64;        // consecutive pairs ranked by one wave per batch
+  __shared__ uint32_t s_base[kDepthR], s_boff[kDepthR], s_tmp[4];
+  __shared__ uint16_t s_wc[4][kDepthR];
+  __shared__ uint64_t s_mask[4][kDepthR];
+  for (int i = threadIdx.x; i < 4 * kDepthR; i += kSortThreads) (&s_mask[0][0])[i] = 0;
+  __shared__ uint32_t s_x[kDepthBatch];  // the batch in digit order: its keys, then its values
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  int v, blk, lo, hi;
+  if (!depth_piece(n, nv, blocks, v, blk, lo, hi) || lo >= hi) return;  // uniform over the workgroup
+  const int64_t row = (int64_t)v * n;
+  const bool write_keys = !LAST || far[v] != 0;
+  {  // first position of each digit: the digit's counts in the blocks before, after all smaller digits
+    const uint2* __restrict__ h = reinterpret_cast<const uint2*>(hist + (int64_t)v * blocks * kDepthR) + tid;
+    static_assert(D == 2, "two digits per thread");
+    uint2 before = make_uint2(0u, 0u), total = make_uint2(0u, 0u);
+    constexpr int kAhead = 8;
+    for (int b = 0; b < blocks; b += kAhead) {
+      uint2 x[kAhead];
+#pragma unroll
+      for (int u = 0; u < kAhead; u++)
+        x[u] = b + u < blocks ? h[(int64_t)(b + u) * kSortThreads] : make_uint2(0u, 0u);
+#pragma unroll
+      for (int u = 0; u < kAhead; u++) {
+        total.x += x[u].x;
+        total.y += x[u].y;
+        if (b + u < blk) {
+          before.x += x[u].x;
+          before.y += x[u].y;
+        }
+      }
+    }
+    const uint32_t tv[D] = {total.x, total.y};
+    const uint32_t run = block_excl_scan_digits<D>(tv, s_tmp, nullptr);
+    s_base[tid * 2] = run + before.x;
+    s_base[tid * 2 + 1] = run + total.x + before.y;
+  }
+  const uint64_t lt = lanemask_lt();
+  for (int batch = lo; batch < hi; batch += kDepthBatch) {
+    const int nb = min(kDepthBatch, hi - batch);
+    const int wbase = batch + wave * kRun;
+    for (int d = lane; d < kDepthR; d += 64) s_wc[wave][d] = 0;
+    uint32_t key[kDepthIt], val[kDepthIt], rank[kDepthIt];
+#pragma unroll
+    for (int s = 0; s < kDepthIt; s++) {
+      const int i = wbase + s * 64 + lane;
+      if (i < hi) {
+        key[s] = kin[row + i];
+        val[s] = FIRST ? (uint32_t)i : vin[row + i];
+      }
+    }
+    wave_lds_sync();
+#pragma unroll
+    for (int s = 0; s < kDepthIt; s++) {
+      const bool valid = wbase + s * 64 + lane < hi;
+      const uint32_t d = valid ? (key[s] >> shift) & (kDepthR - 1) : 0u;
+      rank[s] = wave_rank(s_mask[wave], s_wc[wave], d, valid, lane, lt);
+    }
+    __syncthreads();
+    uint32_t c[D];
+#pragma unroll
+    for (int i = 0; i < D; i++) {
+      uint32_t run = 0;
+#pragma unroll
+      for (int w = 0; w < 4; w++) {
+        const uint32_t x = s_wc[w][tid * D + i];
+        s_wc[w][tid * D + i] = (uint16_t)run;
+        run += x;
+      }
+      c[i] = run;
+    }
+    {
+      uint32_t run = block_excl_scan_digits<D>(c, s_tmp, nullptr);
+#pragma unroll
+      for (int i = 0; i < D; i++) {
+        s_boff[tid * D + i] = run;
+        run += c[i];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < kDepthIt; s++)
+      if (wbase + s * 64 + lane < hi) {
+        const uint32_t d = (key[s] >> shift) & (kDepthR - 1);
+        rank[s] += s_boff[d] + s_wc[wave][d];  // position in the ordered batch
+        s_x[rank[s]] = key[s];
+      }
+    __syncthreads();
+    uint32_t to[kDepthIt];  // where the batch's elements tid, tid + 256, ... go
+#pragma unroll
+    for (int s = 0; s < kDepthIt; s++) {
+      const int j = s * kSortThreads + tid;
+      if (j < nb) {
+        const uint32_t k = s_x[j];
+        const uint32_t d = (k >> shift) & (kDepthR - 1);
+        to[s] = s_base[d] + ((uint32_t)j - s_boff[d]);  // below n for a consistent histogram
+        if (write_keys && to[s] < (uint32_t)n) kout[row + to[s]] = k;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < kDepthIt; s++)
+      if (wbase + s * 64 + lane < hi) s_x[rank[s]] = val[s];
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < kDepthIt; s++) {
+      const int j = s * kSortThreads + tid;
+      if (j < nb && to[s] < (uint32_t)n) vout[row + to[s]] = s_x[j];
+    }
+    if (batch + kDepthBatch >= hi) break;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < D; i++) s_base[tid * D + i] += c[i];
+    __syncthreads();
+  }
+}
+
+// The fourth digit (bits 27 to 30) of the views that have depths beyond the low 27 bits (float
+// depths from 13,107 on, of which a scene has none as a rule): a stable counting sort of the whole view by one
+// workgroup, and the view's flag back to zero.
+__global__ __launch_bounds__(1024) void k_depth_far(int n, const uint32_t* __restrict__ keys, uint32_t* __restrict__ vals,
+                                                    uint32_t* __restrict__ tmp, uint32_t* __restrict__ far) {
+  __shared__ uint32_t s_base[16], s_wc[16][16];
+  const int v = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const bool any = far[v] != 0;
+  __syncthreads();
+  if (!any) return;  // uniform over the workgroup
+  if (tid == 0) far[v] = 0;
+  const int64_t row = (int64_t)v * n;
+  if (tid < 16) s_base[tid] = 0;
+  __syncthreads();
+  for (int i = tid; i < n; i += 1024) atomicAdd(&s_base[(keys[row + i] >> 27) & 15u], 1u);
+  __syncthreads();
+  if (tid == 0) {
+    uint32_t run = 0;
+    for (int d = 0; d < 16; d++) {
+      const uint32_t x = s_base[d];
+      s_base[d] = run;
+      run += x;
+    }
+  }
+  __syncthreads();
+  const uint64_t lt = lanemask_lt();
+  for (int b = 0; b < n; b += 1024) {
+    const int i = b + tid;
+    const bool valid = i < n;
+    const uint32_t d = valid ? (keys[row + i] >> 27) & 15u : 0u;
+    const uint32_t val = valid ? vals[row + i] : 0u;
+    uint64_t peers = __ballot(valid);
+#pragma unroll
+    for (int k = 0; k < 4; k++) {
+      const uint64_t m = __ballot((d >> k) & 1);
+      peers &= ((d >> k) & 1) ? m : ~m;
+    }
+    if (lane < 16) s_wc[wave][lane] = 0;
+    wave_lds_sync();
+    const uint32_t rw = __popcll(peers & lt);
+    if (valid && rw == 0) s_wc[wave][d] = __popcll(peers);
+    __syncthreads();
+    if (valid) {
+      uint32_t o = s_base[d] + rw;
+      for (int w = 0; w < wave; w++) o += s_wc[w][d];
+      tmp[row + o] = val;
+    }
+    __syncthreads();
+    if (tid < 16)
+      for (int w = 0; w < 16; w++) s_base[tid] += s_wc[w][tid];
+    __syncthreads();
+  }
+  __threadfence_block();
+  for (int i = tid; i < n; i += 1024) vals[row + i] = tmp[row + i];
+}
+
 // ---- scan of uint32 -> uint64 (exclusive), 3 phases ----------------------------------------
 constexpr int kScanThreads = 256;
 constexpr int kScanItems = 16;
@@ -394,18 +750,42 @@ int sort_blocks_for(int64_t max_count) {
   return (int)b;
 }
 
-int radix_sort_u64(uint64_t* keys[2], uint32_t* vals[2], const uint32_t* d_count, int64_t max_count, int begin_bit,
-                   int end_bit, uint32_t* hist, int blocks, hipStream_t st) {
-  // digits of at most 9 bits: over the 4M 36-bit (view, depth) keys of a 200k-Gaussian, 20-view
-  // call four 9-bit passes take 0.219 ms in 2,048-pair batches and 0.205 in 4,096-pair ones, five
-  // 8-bit ones 0.233 and four 10-bit ones 0.249 (with 1,024 digits a batch leaves about two pairs
-  // per digit run, so the scatter's stores barely coalesce)
-  return radix_sort_impl<uint64_t>(keys, vals, d_count, max_count, begin_bit, end_bit, hist, blocks, st, 9);
-}
-
 int radix_sort_u32(uint32_t* keys[2], uint32_t* vals[2], const uint32_t* d_count, int64_t max_count, int begin_bit,
                    int end_bit, uint32_t* hist, int blocks, hipStream_t st, int digit_cap) {
   return radix_sort_impl<uint32_t>(keys, vals, d_count, max_count, begin_bit, end_bit, hist, blocks, st, digit_cap);
+}
+
+size_t depth_hist_elems(int max_views) { return (size_t)max_views * kDepthBlocks * kDepthR; }
+
+void launch_depth_sort(int n, int nv, uint32_t* const keys[2], uint32_t* const vals[2], uint32_t* hist, uint32_t* far,
+                       hipStream_t st) {
+  if (n <= 0) return;
+  // a view in LDS as long as one workgroup's registers hold it: 16,384 Gaussians in 43 us, against
+  // 46 (1 view) to 51 us (20) for the radix passes at 17,000; 12,000 in 32, 4,000 in 16 us
+  if (n <= 2 * kDepthLdsThreads)
+    k_depth_lds<2><<<nv, kDepthLdsThreads, 0, st>>>(n, keys[0], vals[1], far);
+  else if (n <= 4 * kDepthLdsThreads)
+    k_depth_lds<4><<<nv, kDepthLdsThreads, 0, st>>>(n, keys[0], vals[1], far);
+  else if (n <= 8 * kDepthLdsThreads)
+    k_depth_lds<8><<<nv, kDepthLdsThreads, 0, st>>>(n, keys[0], vals[1], far);
+  else if (n <= 12 * kDepthLdsThreads)
+    k_depth_lds<12><<<nv, kDepthLdsThreads, 0, st>>>(n, keys[0], vals[1], far);
+  else if (n <= 16 * kDepthLdsThreads)
+    k_depth_lds<16><<<nv, kDepthLdsThreads, 0, st>>>(n, keys[0], vals[1], far);
+  else {
+    const int blocks = std::min(kDepthBlocks, (n + kDepthBatch - 1) / kDepthBatch);
+    const unsigned grid = (unsigned)((blocks * nv + kNumXcd - 1) / kNumXcd * kNumXcd);
+    k_depth_upsweep<<<grid, kSortThreads, 0, st>>>(n, nv, blocks, 0, keys[0], hist);
+    k_depth_scatter<true, false><<<grid, kSortThreads, 0, st>>>(n, nv, blocks, 0, keys[0], nullptr, keys[1], vals[1], hist,
+                                                                far);
+    k_depth_upsweep<<<grid, kSortThreads, 0, st>>>(n, nv, blocks, 9, keys[1], hist);
+    k_depth_scatter<false, false><<<grid, kSortThreads, 0, st>>>(n, nv, blocks, 9, keys[1], vals[1], keys[0], vals[0], hist,
+                                                                 far);
+    k_depth_upsweep<<<grid, kSortThreads, 0, st>>>(n, nv, blocks, 18, keys[0], hist);
+    k_depth_scatter<false, true><<<grid, kSortThreads, 0, st>>>(n, nv, blocks, 18, keys[0], vals[0], keys[1], vals[1], hist,
+                                                                far);
+    k_depth_far<<<nv, 1024, 0, st>>>(n, keys[1], vals[1], vals[0], far);
+  }
 }
 
 size_t scan_tmp_elems(int64_t n) { return (size_t)((n + kScanTile - 1) / kScanTile) + 1; }

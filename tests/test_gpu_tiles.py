@@ -256,3 +256,35 @@ def test_blend_by_quadrant_matches_blend_by_subtile(make):
         scale = float(a.abs().max())
         assert scale > 0.0
         assert float((b / 12.0 - a).abs().max()) <= 1e-5 * scale
+
+
+@pytest.mark.parametrize("n", [1, 63, 1025, 2048, 2049, 4097, 8193, 12289, 16384, 16385, 40000])
+@pytest.mark.parametrize("depths", ["far", "ties", "hidden"])
+def test_depth_order_at_the_sorts_edges(n, depths):
+    """The depth sort holds a view of up to 16,384 Gaussians in LDS (2,048 to 16,384 slots) and sorts
+    larger ones in three 9-bit digits, a fourth where a depth lies beyond 13,107: depths over
+    six decades (far), a few distinct depths (ties, index order) and none visible in view 1 (hidden).
+    Lists bit-exact against the oracle."""
+    rng = np.random.default_rng(n)
+    scene, _ = synth.frustum_scene(17 + n, n, 0, -4.0, 0.5)
+    z = np.exp(rng.uniform(np.log(0.21), np.log(3e5), n)) if depths == "far" else rng.choice([2.0, 2.5, 3.0, 70.0], n)
+    scene.mean[2] = z.astype(np.float32)
+    scene.mean[:2] = (rng.uniform(-0.4, 0.4, (2, n)) * z).astype(np.float32)
+    scene.log_scale[:] = (np.log(0.004 * z) + rng.normal(0, 0.3, (3, n))).astype(np.float32)
+    cams = [synth.make_camera(np.eye(3), (0.0, 0.0, 0.0), 320, 200),
+            synth.make_camera(np.diag([1.0, -1.0, -1.0]) if depths == "hidden" else np.eye(3), (0.05, 0.0, 0.0), 64, 64)]
+    log(f"[depth order] n {n} {depths}")
+    g = to_gpu(scene)
+    ctx = make_ctx(scene.n, cams)
+    for _ in range(2):  # the second call starts from what the first left behind
+        ctx.render_fwd(g, cams, BG)
+    ctx.sync()
+    for v, cam in enumerate(cams):
+        p = oracle.project(scene, cam, (16, 16))
+        assert not np.any(p.flags & oracle.FLAG_RADIUS)
+        k, val, r = oracle.keys(p, cam, (16, 16))
+        TX, TY = oracle.tiles_of(cam, (16, 16))
+        gk, gv, gr = ctx.debug_keys(v, k.size + 16, TX * TY)
+        np.testing.assert_array_equal(gk, k)
+        np.testing.assert_array_equal(gv, val)
+        np.testing.assert_array_equal(gr, r)
