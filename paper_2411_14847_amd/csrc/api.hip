@@ -943,7 +943,7 @@ namespace {
 // NULL.
 const char* ssim_args(const dass_camera* cams, int32_t n_views, const float* const* render,
                       const float* const* target, float lambda, float* const* dl_drgb, float* const* err,
-                      float* const* scratch, SsimArgs& a, int64_t& blocks) {
+                      float* const* scratch, SsimArgs& a) {
   std::memset(&a, 0, sizeof(a));
   a.nv = n_views;
   {
@@ -951,7 +951,6 @@ const char* ssim_args(const dass_camera* cams, int32_t n_views, const float* con
     for (int k = 0; k < 11; k++) sum += (g[k] = std::exp(-((k - 5.0) * (k - 5.0)) / (2.0 * 1.5 * 1.5)));
     for (int k = 0; k < 11; k++) a.w[k] = (float)(g[k] / sum);
   }
-  blocks = 0;
   for (int v = 0; v < n_views; v++) {
     if (!render[v] || !target[v] || !dl_drgb[v] || !scratch[v]) return "NULL buffer";
     if (cams[v].width <= 0 || cams[v].height <= 0) return "bad size";
@@ -963,9 +962,6 @@ const char* ssim_args(const dass_camera* cams, int32_t n_views, const float* con
     V.scratch = scratch[v];
     V.W = cams[v].width;
     V.H = cams[v].height;
-    V.TX = (V.W + ssim_tile_edge() - 1) / ssim_tile_edge();
-    V.block_begin = blocks;
-    blocks += ssim_tiles(V.W, V.H);
     const double n = 3.0 * (double)V.W * (double)V.H * (double)n_views;
     a.gS[v] = (float)(-(double)lambda / n);
     a.l1_scale[v] = (float)((1.0 - (double)lambda) / n);
@@ -987,13 +983,12 @@ dass_status dass_fidelity_loss_grad(dass_ctx ctx, const dass_camera* cams, int32
   if (!cams || !render || !target || !dl_drgb || !scratch || n_views < 1 || n_views > DASS_MAX_VIEWS)
     return fail(ctx, DASS_E_INVALID, "bad arguments");
   SsimArgs a;
-  int64_t blocks = 0;
-  if (const char* why = ssim_args(cams, n_views, render, target, lambda, dl_drgb, err, scratch, a, blocks))
+  if (const char* why = ssim_args(cams, n_views, render, target, lambda, dl_drgb, err, scratch, a))
     return fail(ctx, DASS_E_INVALID, "%s", why);
   HIP_TRY(ctx, hipSetDevice(ctx->device));
   hipStream_t st = (hipStream_t)stream;
   stage_begin(ctx, DASS_STAGE_L1, st);
-  launch_ssim(a, blocks, ctx->ws.loss_slots, st);
+  launch_ssim(a, ctx->ws.loss_slots, st);
   launch_loss_finish(ctx->ws.loss_slots, loss, lambda, st);  // + lambda: the 1 of 1 - SSIM, over views
   stage_end(ctx, DASS_STAGE_L1, st);
   return check_launch(ctx, "dass_fidelity_loss_grad");

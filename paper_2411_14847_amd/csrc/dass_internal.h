@@ -317,15 +317,19 @@ struct L1Args {
 };
 void launch_l1(const L1Args& a, int64_t total_blocks, float* loss, hipStream_t st);
 
-// D-SSIM term of the fidelity loss (loss.hip): one workgroup per ssim_tile_edge()^2 pixel tile.
+// D-SSIM term of the fidelity loss (loss.hip); the launch fills in how the views are cut into
+// tiles (two passes, small calls) or strips of columns whose rows are dealt to the waves (one pass).
 struct SsimView {
   const float* render;  // [3][H][W]
   const float* target;  // [3][H][W]
   float* dl;            // [3][H][W] written
   float* err;           // [H][W] or NULL
-  float* scratch;       // [3 channels][3 maps][H][W]
-  int W, H, TX;         // TX = tiles per row
-  int64_t block_begin;
+  float* scratch;       // [3 channels][3 maps][H][W] (two passes only)
+  int W, H;
+  int TX;               // tiles per row
+  int64_t block_begin;  // tiles of the views before
+  int strips;
+  int64_t row_begin;    // rows of all strips and channels of the views before
 };
 struct SsimArgs {
   SsimView v[DASS_MAX_VIEWS];
@@ -333,12 +337,10 @@ struct SsimArgs {
   float l1_scale[DASS_MAX_VIEWS];  // (1 - lambda) / (3 H W V)
   float w[11];                     // normalised Gaussian window, sigma 1.5
   int nv;
+  int64_t rows, total_rows;        // per wave; of all views
 };
-int64_t ssim_tiles(int W, int H);
-int ssim_tile_edge();
-// Forward (SSIM map, its derivatives into scratch, loss partials) then backward (dL/drgb, error
-// map, L1 partials); the partials go to loss_slots.
-void launch_ssim(const SsimArgs& a, int64_t total_blocks, float* loss_slots, hipStream_t st);
+// dL/drgb, the error maps and the loss partials (to loss_slots).
+void launch_ssim(SsimArgs& a, float* loss_slots, hipStream_t st);
 
 struct DensifyArgs {
   const float* err[DASS_MAX_VIEWS];

@@ -222,6 +222,33 @@ def test_fidelity_loss_with_dssim_fullsize():
     assert float(loss.item()) == pytest.approx(total, rel=1e-5)
 
 
+def test_fidelity_loss_with_dssim_one_pass_strips():
+    """A call large enough for the one-pass form, with views at the edges of its strips (108 columns,
+    rows dealt to the waves in equal runs across strips, channels and views): widths of one strip,
+    one column more, two strips and one column, heights below the window and runs that end inside
+    a view.  Every element against the oracle, with the tolerances of the two-pass tests above."""
+    rng = np.random.default_rng(33)
+    sizes = ((1352, 800), (108, 11), (109, 53), (217, 7), (1352, 801), (5, 300), (1, 40), (1351, 799))
+    cams = [synth.make_camera(np.eye(3), (0, 0, 0), w, h) for w, h in sizes]
+    R = [rng.uniform(size=(3, c.height, c.width)).astype(np.float32) for c in cams]
+    T = [np.clip(r + rng.normal(0, 0.05, size=r.shape), 0, 1).astype(np.float32) for r in R]
+    ctx = make_ctx(10, cams[1:2] * len(cams))
+    dl = [torch.full((3, c.height, c.width), 7.0, device="cuda") for c in cams]
+    err = [torch.full((c.height, c.width), 7.0, device="cuda") for c in cams]
+    loss = torch.zeros(1, device="cuda")
+    ctx.fidelity_loss_grad(cams, [dev(r) for r in R], [dev(t) for t in T], 0.2, dl, err, loss)
+    ctx.sync()
+    V, total = len(cams), 0.0
+    for v in range(V):
+        lv, dv, ev = oracle.fidelity_loss_grad(R[v][None], T[v][None], 0.2)
+        total += lv / V
+        o = dv[0] / V
+        got = dl[v].cpu().numpy()
+        assert not (np.abs(got - o) > 1e-3 * np.abs(o) + 1e-4 * np.abs(o).max()).any(), sizes[v]
+        np.testing.assert_allclose(err[v].cpu().numpy(), ev[0], rtol=1e-6, atol=1e-7)
+    assert float(loss.item()) == pytest.approx(total, rel=1e-5)
+
+
 def _densify_case(seed, n, views, k_max, extra_cap, tau_pos, tau_err, gamma):
     rng = np.random.default_rng(seed)
     scene, cams, _ = synth.multiview_scene(seed, n=n, n_views=views, width=96, height=72, with_grads=False)
