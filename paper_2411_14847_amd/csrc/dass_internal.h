@@ -128,9 +128,12 @@ struct FieldGradsK {
 };
 constexpr int64_t kFieldPartialFloats = int64_t(1) << 24;  // per-query-part table-gradient slices (64 MB)
 struct SliceMap {
-  int begin[kFieldMaxLevels];              // first slice of each level
-  int64_t level_floats[kFieldMaxLevels];   // floats of the level's table that can be touched
-  int n_slices, n_qparts, features;
+  int begin[kFieldMaxLevels];      // level's first workgroup (slice-major, then query part)
+  int slices[kFieldMaxLevels];     // slices of the level
+  int parts[kFieldMaxLevels];      // query parts of the level
+  int slot_begin[kFieldMaxLevels];  // level's first slot of the partial buffer (levels of several parts)
+  int sum_begin[kFieldMaxLevels];  // level's first slice among those of the levels of several parts
+  uint32_t rows[kFieldMaxLevels];  // rows of the level's table that can be touched
 };
 // Per-query rows of the field backward, feature-major over the m queries of the call ([R][m]).
 struct FieldRows {

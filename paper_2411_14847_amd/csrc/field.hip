@@ -13,11 +13,11 @@
 //     feature-major.
 //  2. weight gradients: each workgroup sums a contiguous part of the queries through LDS and
 //     writes one partial row; the partials are then added in a fixed order.
-//  3. table gradients without global atomics: each workgroup owns one slice (up to 128 KB) of
-//     one level's table, accumulates every query's corner contributions that fall in it with
-//     LDS atomics, then adds the slice to the gradient.  (Float atomics to global memory from
-//     every query -- L x 8 x F per query -- ran at ~1.5e10 per second here, and many queries hit
-//     the same rows of the coarse levels.)
+//  3. table gradients without global atomics: each workgroup owns one slice (up to 20,480 values,
+//     held as doubles) of one level's table, accumulates every query's corner contributions that
+//     fall in it with LDS atomics, then adds the slice to the gradient.  (Float atomics to global
+//     memory from every query -- L x 8 x F per query -- ran at ~1.5e10 per second here, and many
+//     queries hit the same rows of the coarse levels.)
 #include <algorithm>
 
 #include "dass_internal.h"
@@ -27,9 +27,9 @@ namespace {
 
 constexpr uint32_t kPrimeY = 2654435761u;  // the encoding's spatial-hash primes (x: 1)
 constexpr uint32_t kPrimeZ = 805459861u;
-constexpr int kSliceFloats = 32768;  // table-gradient slice held in LDS (128 KB)
+constexpr int kSliceVals = 20480;  // table-gradient slice held in LDS as doubles (all 160 KB)
 constexpr int kSliceThreads = 1024;
-constexpr int kSliceTargetBlocks = 512;
+constexpr int kSliceTargetBlocks = 256;  // one workgroup per CU (its LDS)
 constexpr int kSliceBatch = 4;
 
 template <int F>
@@ -65,25 +65,30 @@ __device__ __forceinline__ void normalised(const FieldK& f, const QueryK& q, int
   }
 }
 
+// The cell of p at resolution N and the position in it.
+__device__ __forceinline__ void level_cell(int N, const double p[3], uint32_t c[3], float fr[3]) {
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    const double x = p[d] * (double)N;
+    const int i = min((int)floor(x), N - 1);
+    c[d] = (uint32_t)i;
+    fr[d] = (float)(x - (double)i);
+  }
+}
+
 // Calls fn(corner, row of the level's table, trilinear weight) for the 8 corners of level l's
 // cell around p.
 template <class Fn>
 __device__ __forceinline__ void level_corners(const FieldK& f, int l, const double p[3], Fn&& fn) {
   const int N = f.res[l];
-  int c[3];
+  uint32_t c[3];
   float fr[3];
-#pragma unroll
-  for (int d = 0; d < 3; ++d) {
-    const double x = p[d] * (double)N;
-    c[d] = min((int)floor(x), N - 1);
-    fr[d] = (float)(x - (double)c[d]);
-  }
+  level_cell(N, p, c, fr);
   const bool dense = (f.dense >> l) & 1u;
   const uint32_t mask = (1u << f.log2T) - 1u;
 #pragma unroll
   for (int k = 0; k < 8; ++k) {
-    const uint32_t x = (uint32_t)(c[0] + (k & 1)), y = (uint32_t)(c[1] + ((k >> 1) & 1)),
-                   z = (uint32_t)(c[2] + ((k >> 2) & 1));
+    const uint32_t x = c[0] + (k & 1), y = c[1] + ((k >> 1) & 1), z = c[2] + ((k >> 2) & 1);
     const uint32_t row = dense ? x + (uint32_t)(N + 1) * (y + (uint32_t)(N + 1) * z)
                                : (x ^ (y * kPrimeY) ^ (z * kPrimeZ)) & mask;
     const float w = ((k & 1) ? fr[0] : 1.f - fr[0]) * ((k & 2) ? fr[1] : 1.f - fr[1]) *
@@ -434,32 +439,51 @@ __global__ __launch_bounds__(kWgThreads) void k_field_wgrad(const FieldK f, int 
   if (t < 7 * 16 && (t % 16) == 0) P[HID * LF + 8 * HID + t / 16] = b2s;
 }
 
-// Level, first float and end of slice b of the table (slice_begin: prefix over levels).
-__device__ __forceinline__ void slice_of(const FieldK& f, const SliceMap& sm, int b, int& l, int64_t& lo,
-                                         int64_t& hi) {
-  l = 0;
-  while (l + 1 < f.L && sm.begin[l + 1] <= b) ++l;
-  lo = (int64_t)(b - sm.begin[l]) * kSliceFloats;
-  hi = min(lo + kSliceFloats, sm.level_floats[l]);
+// Where slice k of level l lies: rows [row0, row0 + rows) of the level's table.
+template <int F>
+__device__ __forceinline__ void slice_of(const SliceMap& sm, int l, int k, uint32_t& row0, uint32_t& rows) {
+  row0 = (uint32_t)k * (kSliceVals / F);
+  rows = min((uint32_t)(kSliceVals / F), sm.rows[l] - row0);
 }
 
-// Table gradient of one slice [lo, hi) (float offsets) of level l's table over the queries
-// [m q_part / n_qparts, m (q_part + 1) / n_qparts), with (slice, q_part) from the workgroup
-// index.  One query part: added to the gradient; several: written to partial[q_part][slice].
+// Where the partial sums of slice k, query part qp of level l lie (in slices).
+__device__ __forceinline__ int part_slot(const SliceMap& sm, int l, int k, int qp) {
+  return sm.slot_begin[l] + k * sm.parts[l] + qp;
+}
+
+// Table gradient of one slice of one level's table over one part of the queries (part qp of P: the
+// queries [m qp / P, m (qp + 1) / P)).  A level of one part: added to the gradient; of several: written
+// to its slot of partial.
+//
+// The sums are doubles: an LDS atomic add of 64 random floats takes a CU 170 cycles here (the lanes
+// are served one by one), of 64 doubles 19.  Half as many values fit, so more workgroups look at each
+// query; what bounds them is that look.  The four corner pairs (x, x + 1) of a query are one test
+// each -- the two rows are near each other, so mostly in the same slice -- and a lane's hits are then
+// taken one after the other, so a wave runs as often as its busiest lane has hits and not eight times.
+// 20k queries, F = 4, 2^16 rows: 239 us with float sums and the query parts alike for all levels, 51
+// now; 180k, F = 2, 2^14 rows: 245 -> 83.
 template <int F>
 __global__ __launch_bounds__(kSliceThreads) void k_field_table_grad(const FieldK f, int m,
                                                                    const double* __restrict__ pn,
                                                                    const float* __restrict__ denc,
                                                                    SliceMap sm, float* __restrict__ gtable,
                                                                    float* __restrict__ partial) {
-  __shared__ float s_g[kSliceFloats];
-  const int b = blockIdx.x % sm.n_slices, qp = blockIdx.x / sm.n_slices;
-  int l;
-  int64_t lo, hi;
-  slice_of(f, sm, b, l, lo, hi);
-  const int q0 = (int)((int64_t)m * qp / sm.n_qparts), q1 = (int)((int64_t)m * (qp + 1) / sm.n_qparts);
-  for (int i = threadIdx.x; i < kSliceFloats; i += kSliceThreads) s_g[i] = 0.f;
+  __shared__ double s_g[kSliceVals];
+  int l = 0;
+  while (l + 1 < f.L && sm.begin[l + 1] <= (int)blockIdx.x) ++l;
+  const int parts = sm.parts[l], k = ((int)blockIdx.x - sm.begin[l]) / parts,
+            qp = ((int)blockIdx.x - sm.begin[l]) % parts;
+  uint32_t row0, rows;
+  slice_of<F>(sm, l, k, row0, rows);
+  const int n = (int)rows * F;
+  const int q0 = (int)((int64_t)m * qp / parts), q1 = (int)((int64_t)m * (qp + 1) / parts);
+  for (int i = threadIdx.x; i < n; i += kSliceThreads) s_g[i] = 0.0;
   __syncthreads();
+  const int N = f.res[l];
+  const bool dense = (f.dense >> l) & 1u;
+  const uint32_t mask = (1u << f.log2T) - 1u;
+  // the row of the corner with first coordinate x on the grid line of yz (level_corners' rows)
+  auto row_of = [&](uint32_t x, uint32_t yz) { return (dense ? x + yz : (x ^ yz) & mask) - row0; };
   // kSliceBatch queries per thread at a time: their loads are issued together
   for (int q = q0 + threadIdx.x; q < q1; q += kSliceThreads * kSliceBatch) {
     double p[kSliceBatch][3];
@@ -476,38 +500,66 @@ __global__ __launch_bounds__(kSliceThreads) void k_field_table_grad(const FieldK
 #pragma unroll
     for (int u = 0; u < kSliceBatch; ++u) {
       if (q + u * kSliceThreads >= q1) break;
-      level_corners(f, l, p[u], [&](int, uint32_t row, float w) {
-        const int64_t off = (int64_t)row * F;
-        if (off >= lo && off < hi) {
+      uint32_t c[3];
+      float fr[3];
+      level_cell(N, p[u], c, fr);
+      uint32_t y[2], z[2];
 #pragma unroll
-          for (int i = 0; i < F; ++i) atomicAdd(&s_g[off - lo + i], w * dv[u][i]);
+      for (int d = 0; d < 2; ++d) {
+        y[d] = dense ? (uint32_t)(N + 1) * (c[1] + d) : (c[1] + d) * kPrimeY;
+        z[d] = dense ? (uint32_t)(N + 1) * (uint32_t)(N + 1) * (c[2] + d) : (c[2] + d) * kPrimeZ;
+      }
+      auto line = [&](uint32_t a, uint32_t b) { return dense ? a + b : a ^ b; };
+      uint32_t hit = 0;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const uint32_t yz = line(y[j & 1], z[j >> 1]);
+        const bool h = row_of(c[0], yz) < rows || row_of(c[0] + 1u, yz) < rows;
+        hit |= h ? 1u << j : 0u;
+      }
+      while (hit) {
+        const uint32_t j = (uint32_t)__builtin_ctz(hit);
+        hit &= hit - 1u;
+        const uint32_t yz = line((j & 1u) ? y[1] : y[0], (j & 2u) ? z[1] : z[0]);
+        const float wy = (j & 1u) ? fr[1] : 1.f - fr[1], wz = (j & 2u) ? fr[2] : 1.f - fr[2];
+#pragma unroll
+        for (int dx = 0; dx < 2; ++dx) {
+          const uint32_t r = row_of(c[0] + dx, yz);
+          const float w = (dx ? fr[0] : 1.f - fr[0]) * wy * wz;
+          if (r < rows) {
+#pragma unroll
+            for (int i = 0; i < F; ++i) atomicAdd(&s_g[r * F + i], (double)(w * dv[u][i]));
+          }
         }
-      });
+      }
     }
   }
   __syncthreads();
-  if (sm.n_qparts == 1) {
-    float* __restrict__ dst = gtable + ((size_t)l << f.log2T) * F + lo;
-    for (int i = threadIdx.x; i < hi - lo; i += kSliceThreads) dst[i] += s_g[i];
+  if (parts == 1) {
+    float* __restrict__ dst = gtable + (((size_t)l << f.log2T) + row0) * F;
+    for (int i = threadIdx.x; i < n; i += kSliceThreads) dst[i] += (float)s_g[i];
   } else {
-    float* __restrict__ dst = partial + ((size_t)qp * sm.n_slices + b) * kSliceFloats;
-    for (int i = threadIdx.x; i < hi - lo; i += kSliceThreads) dst[i] = s_g[i];
+    float* __restrict__ dst = partial + (size_t)part_slot(sm, l, k, qp) * kSliceVals;
+    for (int i = threadIdx.x; i < n; i += kSliceThreads) dst[i] = (float)s_g[i];
   }
 }
 
 // gradient += the query parts' partial slices, added in part order
+template <int F>
 __global__ __launch_bounds__(256) void k_field_table_sum(const FieldK f, SliceMap sm, const float* __restrict__ partial,
                                                          float* __restrict__ gtable) {
-  constexpr int kBlocksPerSlice = kSliceFloats / 256;
-  const int b = blockIdx.x / kBlocksPerSlice;
-  const int i = (blockIdx.x % kBlocksPerSlice) * 256 + threadIdx.x;
-  int l;
-  int64_t lo, hi;
-  slice_of(f, sm, b, l, lo, hi);
-  if (i >= hi - lo) return;
+  constexpr int kBlocksPerSlice = kSliceVals / 256;
+  const int b = blockIdx.x / kBlocksPerSlice, i = (blockIdx.x % kBlocksPerSlice) * 256 + threadIdx.x;
+  int l = 0;
+  while (l + 1 < f.L && sm.sum_begin[l + 1] <= b) ++l;
+  const int k = b - sm.sum_begin[l], parts = sm.parts[l];
+  uint32_t row0, rows;
+  slice_of<F>(sm, l, k, row0, rows);
+  if (i >= (int)rows * F) return;
+  const float* __restrict__ src = partial + (size_t)part_slot(sm, l, k, 0) * kSliceVals + i;
   float s = 0.f;
-  for (int qp = 0; qp < sm.n_qparts; ++qp) s += partial[((size_t)qp * sm.n_slices + b) * kSliceFloats + i];
-  gtable[((size_t)l << f.log2T) * sm.features + lo + i] += s;
+  for (int qp = 0; qp < parts; ++qp) s += src[(size_t)qp * kSliceVals];
+  gtable[(((size_t)l << f.log2T) + row0) * F + i] += s;
 }
 
 // grad += sum over the workgroups' partials (fixed order): a workgroup takes kRedCols columns,
@@ -582,6 +634,56 @@ void bwd_f(int F, int blocks, const FieldK& f, const QueryK& q, const float* d_d
   }
 }
 
+template <int F>
+void table_grad(const FieldK& f, int m, const FieldScratch& ws, float* gtable, hipStream_t st) {
+  constexpr int64_t kRows = kSliceVals / F;
+  constexpr int64_t kSlots = kFieldPartialFloats / kSliceVals;
+  SliceMap sm{};
+  int64_t blocks = 0, slots = 0;
+  float work[kFieldMaxLevels];  // of a slice's workgroup over all the queries
+  for (int l = 0; l < f.L; l++) {
+    const int64_t N1 = (int64_t)f.res[l] + 1;
+    const bool dense = (f.dense >> l) & 1u;
+    const int64_t rows = dense ? N1 * N1 * N1 : (int64_t(1) << f.log2T);
+    sm.rows[l] = (uint32_t)rows;
+    sm.slices[l] = (int)((rows + kRows - 1) / kRows);
+    sm.parts[l] = 1;
+    blocks += sm.slices[l];
+    // The look at a query is 1; the adds of a hit were 1 as well per feature in a dense level, whose
+    // queries lie close together, so that one slice may have nearly all and they meet in the same rows
+    // (20k queries, F = 4: 200 us against 43 of a hashed level's slice); hashed rows spread evenly.
+    work[l] = dense ? 1.f + F : 1.f + 0.33f * F * (float)std::min(1.0, (double)kRows / (double)rows);
+  }
+  // Workgroups up to a whole number of rounds over the CUs go, one query part at a time, to the level
+  // whose workgroups have most to do; a part keeps at least kSliceThreads queries, and the partial
+  // buffer bounds the levels of more than one part.
+  const int64_t target = (blocks + kSliceTargetBlocks - 1) / kSliceTargetBlocks * kSliceTargetBlocks;
+  const int max_parts = std::max(1, m / kSliceThreads);
+  for (;;) {
+    int b = 0;
+    for (int l = 1; l < f.L; l++)
+      if (work[l] / sm.parts[l] > work[b] / sm.parts[b]) b = l;
+    const int64_t more = sm.parts[b] == 1 ? 2 * sm.slices[b] : sm.slices[b];
+    if (sm.parts[b] >= max_parts || blocks + sm.slices[b] > target || slots + more > kSlots) break;
+    blocks += sm.slices[b];
+    slots += more;
+    ++sm.parts[b];
+  }
+  int begin = 0, slot = 0, sum = 0;
+  for (int l = 0; l < f.L; l++) {
+    sm.begin[l] = begin;
+    sm.slot_begin[l] = slot;
+    sm.sum_begin[l] = sum;
+    begin += sm.slices[l] * sm.parts[l];
+    if (sm.parts[l] > 1) {
+      slot += sm.slices[l] * sm.parts[l];
+      sum += sm.slices[l];
+    }
+  }
+  k_field_table_grad<F><<<(unsigned)begin, kSliceThreads, 0, st>>>(f, m, ws.rows.pn, ws.rows.denc, sm, gtable, ws.tpart);
+  if (sum) k_field_table_sum<F><<<(unsigned)sum * (kSliceVals / 256), 256, 0, st>>>(f, sm, ws.tpart, gtable);
+}
+
 }  // namespace
 
 void launch_field_fwd(const FieldK& f, int F, int hidden, const QueryK& q, float* dpos, float* drot,
@@ -609,33 +711,12 @@ void launch_field_bwd(const FieldK& f, int F, int hidden, const QueryK& q, const
   k_field_reduce<<<(stride + kRedCols - 1) / kRedCols, kRedCols * kRedGroups, 0, st>>>(
       ws.part, blocks, stride, hidden * LF, hidden, g.w1, g.b1, g.w2, g.b2);
   if (g.table) {
-    SliceMap sm{};
-    int total = 0;
-    for (int l = 0; l < f.L; l++) {
-      const int64_t N1 = (int64_t)f.res[l] + 1;
-      const int64_t rows = ((f.dense >> l) & 1u) ? N1 * N1 * N1 : (int64_t(1) << f.log2T);
-      sm.begin[l] = total;
-      sm.level_floats[l] = rows * F;
-      total += (int)((rows * F + kSliceFloats - 1) / kSliceFloats);
-    }
-    // split the queries so that about kSliceTargetBlocks workgroups run, within the partial buffer
-    // and with at least kSliceThreads queries per workgroup
-    int64_t parts = (kSliceTargetBlocks + total - 1) / total;
-    parts = std::min<int64_t>(parts, kFieldPartialFloats / ((int64_t)total * kSliceFloats));
-    parts = std::min<int64_t>(parts, (q.m + kSliceThreads - 1) / kSliceThreads);
-    if (parts < 1) parts = 1;
-    sm.n_slices = total;
-    sm.n_qparts = (int)parts;
-    sm.features = F;
-    const unsigned grid = (unsigned)(total * parts);
     switch (F) {
-      case 1: k_field_table_grad<1><<<grid, kSliceThreads, 0, st>>>(f, q.m, ws.rows.pn, ws.rows.denc, sm, g.table, ws.tpart); break;
-      case 2: k_field_table_grad<2><<<grid, kSliceThreads, 0, st>>>(f, q.m, ws.rows.pn, ws.rows.denc, sm, g.table, ws.tpart); break;
-      case 4: k_field_table_grad<4><<<grid, kSliceThreads, 0, st>>>(f, q.m, ws.rows.pn, ws.rows.denc, sm, g.table, ws.tpart); break;
-      default: k_field_table_grad<8><<<grid, kSliceThreads, 0, st>>>(f, q.m, ws.rows.pn, ws.rows.denc, sm, g.table, ws.tpart); break;
+      case 1: table_grad<1>(f, q.m, ws, g.table, st); break;
+      case 2: table_grad<2>(f, q.m, ws, g.table, st); break;
+      case 4: table_grad<4>(f, q.m, ws, g.table, st); break;
+      default: table_grad<8>(f, q.m, ws, g.table, st); break;
     }
-    if (parts > 1)
-      k_field_table_sum<<<(unsigned)total * (kSliceFloats / 256), 256, 0, st>>>(f, sm, ws.tpart, g.table);
   }
 }
 

@@ -269,3 +269,17 @@ def test_streaming_with_hash_fields(use_graph):
         ns.append(st["n"])
     ctx.sync()
     assert ns[0] == scene.n + 80 and ns[1] == scene.n + 80 and ns[2] == scene.n + 160
+
+
+@pytest.mark.parametrize("L,F,lt,nmax,m", [
+    (4, 4, 12, 256, 1),        # one slice a level, one query
+    (5, 4, 13, 256, 1023),     # hashed levels of two slices, the second ragged; queries below a workgroup's
+    (6, 2, 14, 512, 2047),     # a query part takes at least 1024: still one part
+    (6, 2, 14, 512, 2049),     # two parts, partial slices added
+    (16, 1, 15, 2048, 5000),   # two slices a level, as many parts as the queries give
+    (8, 8, 16, 1024, 4500),    # 26 slices a hashed level, parts for the dense ones only
+    (8, 8, 18, 1024, 2500),    # more slices than workgroups of one round
+])
+def test_field_table_gradient_at_slice_and_part_edges(monkeypatch, L, F, lt, nmax, m):
+    monkeypatch.setitem(CONFIGS, "edge", (L, F, lt, 64, nmax))
+    run_case("edge", 2 * m + 10, m, 5)
