@@ -186,6 +186,25 @@ __device__ __forceinline__ float wave_reduce9(const float* v) {
   d += dppf<0x4E>(d);
   return d;
 }
+// Two entries' nine values at once, in fewer steps than twice the above: bit 5 -> entry (v0 below lane
+// 32, v1 above), bits 4..1 = m -> value kRedSlot18[m] (-1: a duplicate).  `odd` = lane bit 1.
+__device__ __forceinline__ float wave_reduce18(const float* v0, const float* v1, bool odd) {
+  float c[9];
+#pragma unroll
+  for (int i = 0; i < 9; i++) c[i] = swap32_sum(v0[i], v1[i]);
+  // bit 4 -> 0 1 2 3 4 or 5 6 7 8 4
+  const float b0 = swap16_sum(c[0], c[5]), b1 = swap16_sum(c[1], c[6]), b2 = swap16_sum(c[2], c[7]);
+  const float b3 = swap16_sum(c[3], c[8]), b4 = swap16_sum(c[4], c[4]);
+  // bit 3 -> 0 1 2 or 3 4 2
+  const float d0 = dpp_pair8(b0, b3), d1 = dpp_pair8(b1, b4), d2 = b2 + dppf<0x128>(b2);
+  // bit 2 -> 0 2 or 1 2
+  float e0 = dpp_pair4(d0, d1), e1 = dpp_pair4(d2, d2);
+  e0 += dppf<0x4E>(e0);  // bit 1 -> 0 or 2
+  e1 += dppf<0x4E>(e1);
+  const float f = odd ? e1 : e0;
+  return f + dppf<0xB1>(f);
+}
+__constant__ int kRedSlot18[16] = {0, 2, 1, -1, 3, -1, 4, -1, 5, 7, 6, -1, 8, -1, -1, -1};
 __constant__ int kRedSlot[16] = {0, 1, 2, -1, 3, 4, -1, -1, 5, 6, 7, -1, 8, -1, -1, -1};
 
 // A staged list entry in LDS: one 48-byte row, so a wave reads an entry's fields from one address.
@@ -529,19 +548,49 @@ __global__ __launch_bounds__(kLanes) void k_blend_bwd(ViewsIO io, int nv, int to
 // pixel per lane), for calls of few sub-tiles: there the time is that of one wave walking its list,
 // entry after entry, and here a list is walked by four waves, each over the entries that reach
 // its own quadrant only.  The four stage a batch together (one entry per thread, not compacted:
-// a 64-bit mask per quadrant and 64 entries says which to walk) and read the next entry from LDS
-// while they blend the current one.  Pixels see the operations of the kernels above in the same
+// a 64-bit mask per quadrant and 64 entries says which to walk).  A wave blends two entries at a
+// time, whose alphas (and, in the adjoint, whose sums over the lanes) do not wait for each other, and
+// reads the next two from LDS meanwhile.  Pixels see the operations of the kernels above in the same
 // order, so the images, n_contrib and, up to the order of the sums, the gradients are the same.
+// Entries one by one -> two at a time, us forward / backward: one view of 2k Gaussians at 128x128 21 -> 17
+// / 40 -> 34; 20 views of 7k at 128x128 116 -> 90 / 179 -> 166.
 constexpr int kQB = 256;  // threads per workgroup = entries per batch
+constexpr float kLogNone = -1000.f;  // log2 of no opacity (alpha 0)
+
+// The sub-tile of a workgroup.  All workgroups of such a call are on the CUs at once, so how long lists
+// are spread over them counts: by_view views of one size are taken in turn for each sub-tile, since the
+// crowded ones, mostly in the middle of each view, otherwise come in a stride that lands on the same CUs
+// (20 views of 64 sub-tiles: 124 -> 116 us forward, 235 -> 179 backward).  One view, or views of several
+// sizes: neighbours on the same XCD.
+__device__ __forceinline__ int q_block(int w, int total, int per, int by_view) {
+  if (by_view == 0) return xcd_logical(w, per);
+  return w < total ? (w % by_view) * (total / by_view) + w / by_view : total;
+}
+
+// The next two of the 64 staged entries that mask m holds, in list order or against it, 64 (the entry
+// of opacity 0) when there is none; taken from m.  The scalar find of a zero mask gives -1.
+__device__ __forceinline__ int q_first(uint64_t& m) {
+  int j;
+  asm("s_ff1_i32_b64 %0, %1" : "=s"(j) : "s"(m));
+  m &= ~(1ull << (j & 63));
+  return (int)min((uint32_t)j, 64u);
+}
+__device__ __forceinline__ int q_last(uint64_t& m) {
+  int j;
+  asm("s_flbit_i32_b64 %0, %1" : "=s"(j) : "s"(m));
+  j ^= 63;
+  m &= ~(1ull << (j & 63));
+  return (int)min((uint32_t)j, 64u);
+}
 
 template <bool L1>
-__global__ __launch_bounds__(kQB) void k_blend_fwd_q(ViewsIO io, int nv, int total_blocks, int per, float bg0, float bg1,
-                                                     float bg2, const uint2* __restrict__ ranges,
+__global__ __launch_bounds__(kQB) void k_blend_fwd_q(ViewsIO io, int nv, int total_blocks, int per, int by_view,
+                                                     float bg0, float bg1, float bg2, const uint2* __restrict__ ranges,
                                                      const uint32_t* __restrict__ vals, const Rec* __restrict__ rec,
                                                      float* __restrict__ loss_slots) {
-  __shared__ FwdStage s_st[kQB];
+  __shared__ FwdStage s_st[4][65];  // [64]: an entry of opacity 0
   __shared__ uint64_t s_q[4][4];  // [quadrant][64 entries]
-  const int lb = xcd_logical(blockIdx.x, per);
+  const int lb = q_block(blockIdx.x, total_blocks, per, by_view);
   if (lb >= total_blocks) return;
   const int b = lb / io.sn, sub = lb - b * io.sn;
   const int v = view_of(io, nv, b);
@@ -561,6 +610,11 @@ __global__ __launch_bounds__(kQB) void k_blend_fwd_q(ViewsIO io, int nv, int tot
     if (tid == 0) atomicOr(io.err, kErrListTooLong);
     return;
   }
+  if (lane == 0) {
+    s_st[k][64].xy = make_float2(0.f, 0.f);
+    s_st[k][64].co = make_float4(0.f, 0.f, 0.f, kLogNone);
+    s_st[k][64].rgb = make_float4(0.f, 0.f, 0.f, 0.f);
+  }
   float T = 1.f, thr = (px < V.W && py < V.H) ? kAlphaMin : kNever, c0 = 0.f, c1 = 0.f, c2 = 0.f;
   uint32_t last = 0;
   bool alive = __ballot(thr < 1.f) != 0;  // uniform over the wave
@@ -572,9 +626,9 @@ __global__ __launch_bounds__(kQB) void k_blend_fwd_q(ViewsIO io, int nv, int tot
       const float2 xy = make_float2((R.r0.x - fx0) + R.r0.z, (R.r0.y - fy0) + R.r0.w);
       qm = quad_mask<2>(xy.x, xy.y, R.r1.x, R.r1.y, R.r1.z, R.r1.w);
       if (qm) {
-        s_st[tid].xy = xy;
-        s_st[tid].co = make_float4(-0.5f * kLog2e * R.r1.x, -kLog2e * R.r1.y, -0.5f * kLog2e * R.r1.z, __log2f(R.r1.w));
-        s_st[tid].rgb = make_float4(R.r2.x, R.r2.y, R.r2.z, __uint_as_float((uint32_t)(start - r.x) + tid + 1));
+        s_st[k][lane].xy = xy;
+        s_st[k][lane].co = make_float4(-0.5f * kLog2e * R.r1.x, -kLog2e * R.r1.y, -0.5f * kLog2e * R.r1.z, __log2f(R.r1.w));
+        s_st[k][lane].rgb = make_float4(R.r2.x, R.r2.y, R.r2.z, __uint_as_float((uint32_t)(start - r.x) + tid + 1));
       }
     }
 #pragma unroll
@@ -588,38 +642,63 @@ __global__ __launch_bounds__(kQB) void k_blend_fwd_q(ViewsIO io, int nv, int tot
       uint64_t m = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)mv) |
                    ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(mv >> 32)) << 32);
       if (m == 0) continue;
-      const FwdStage* st = s_st + g * 64;
-      int j = __builtin_ctzll(m);
-      float2 xy = st[j].xy;
-      float4 co = st[j].co, c = st[j].rgb;
-      while (m != 0 && alive) {
-        m &= m - 1;
-        const int jn = m ? (int)__builtin_ctzll(m) : j;
-        const float2 xy_n = st[jn].xy;  // the next entry, read while this one is blended
-        const float4 co_n = st[jn].co, c_n = st[jn].rgb;
-        const float dx = (xy.x - (float)qx) - kx, dy = (xy.y - (float)qy) - ky;
-        // the operations of k_blend_fwd
-        const float pw = fmaf(dx, fmaf(co.x, dx, co.y * dy), fmaf(co.z * dy, dy, co.w));
-        const float a = fminf(kAlphaMax, __builtin_amdgcn_exp2f(pw));
-        const bool ok = a >= thr;
-        float wgt = ok ? a * T : 0.f;
-        T -= wgt;
-        bool take = ok;
-        const bool stop = T < kTStop;
-        if (__builtin_expect(__ballot(stop) != 0, 0)) {
-          T = stop ? T + wgt : T;
-          wgt = stop ? 0.f : wgt;
-          take = ok && !stop;
-          thr = stop ? kNever : thr;
-          alive = __ballot(thr < 1.f) != 0;
+      const FwdStage* st = s_st[g];
+      int ja = q_first(m), jb = q_first(m);
+      FwdStage A = st[ja], B = st[jb];
+      auto blend2 = [&](const FwdStage& A, const FwdStage& B) {
+        // the operations of k_blend_fwd, the two alphas side by side
+        float aa, ab;
+        {
+          const float dx = (A.xy.x - (float)qx) - kx, dy = (A.xy.y - (float)qy) - ky;
+          const float pw = fmaf(dx, fmaf(A.co.x, dx, A.co.y * dy), fmaf(A.co.z * dy, dy, A.co.w));
+          aa = fminf(kAlphaMax, __builtin_amdgcn_exp2f(pw));
         }
-        c0 = fmaf(c.x, wgt, c0);
-        c1 = fmaf(c.y, wgt, c1);
-        c2 = fmaf(c.z, wgt, c2);
-        last = take ? __float_as_uint(c.w) : last;
-        xy = xy_n;
-        co = co_n;
-        c = c_n;
+        {
+          const float dx = (B.xy.x - (float)qx) - kx, dy = (B.xy.y - (float)qy) - ky;
+          const float pw = fmaf(dx, fmaf(B.co.x, dx, B.co.y * dy), fmaf(B.co.z * dy, dy, B.co.w));
+          ab = fminf(kAlphaMax, __builtin_amdgcn_exp2f(pw));
+        }
+        bool ta = aa >= thr, tb = ab >= thr;
+        float wa = ta ? aa * T : 0.f;
+        const float T1 = T - wa;
+        float wb = tb ? ab * T1 : 0.f;
+        const float T2 = T1 - wb;
+        if (__builtin_expect(__ballot(T2 < kTStop) != 0, 0)) {  // T1 >= T2: some pixel stops at one of them
+          const bool stop_a = T1 < kTStop;
+          T = stop_a ? T1 + wa : T1;
+          wa = stop_a ? 0.f : wa;
+          ta = ta && !stop_a;
+          thr = stop_a ? kNever : thr;
+          tb = ab >= thr;
+          wb = tb ? ab * T : 0.f;
+          T -= wb;
+          const bool stop_b = T < kTStop;
+          T = stop_b ? T + wb : T;
+          wb = stop_b ? 0.f : wb;
+          tb = tb && !stop_b;
+          thr = stop_b ? kNever : thr;
+          alive = __ballot(thr < 1.f) != 0;
+        } else {
+          T = T2;
+        }
+        c0 = fmaf(B.rgb.x, wb, fmaf(A.rgb.x, wa, c0));
+        c1 = fmaf(B.rgb.y, wb, fmaf(A.rgb.y, wa, c1));
+        c2 = fmaf(B.rgb.z, wb, fmaf(A.rgb.z, wa, c2));
+        last = ta ? __float_as_uint(A.rgb.w) : last;
+        last = tb ? __float_as_uint(B.rgb.w) : last;
+      };
+      for (;;) {  // two pairs in turn: the next is read while one is blended
+        bool more = m != 0;
+        ja = q_first(m), jb = q_first(m);
+        FwdStage An = st[ja], Bn = st[jb];
+        blend2(A, B);
+        if (!more || !alive) break;
+        more = m != 0;
+        ja = q_first(m), jb = q_first(m);
+        A = st[ja];
+        B = st[jb];
+        blend2(An, Bn);
+        if (!more || !alive) break;
       }
     }
   }
@@ -656,15 +735,15 @@ __global__ __launch_bounds__(kQB) void k_blend_fwd_q(ViewsIO io, int nv, int tot
 
 // The adjoint: an entry's nine sums over a quadrant are added to the batch's rows in LDS, and the
 // batch's rows go to global memory once for the four quadrants.
-__global__ __launch_bounds__(kQB) void k_blend_bwd_q(ViewsIO io, int nv, int total_blocks, int per, float bg0, float bg1,
-                                                     float bg2, const uint2* __restrict__ ranges,
+__global__ __launch_bounds__(kQB) void k_blend_bwd_q(ViewsIO io, int nv, int total_blocks, int per, int by_view,
+                                                     float bg0, float bg1, float bg2, const uint2* __restrict__ ranges,
                                                      const uint32_t* __restrict__ vals, const Rec* __restrict__ rec,
                                                      float* __restrict__ g2d) {
-  __shared__ BwdStage s_st[kQB];
+  __shared__ BwdStage s_st[4][65];  // [64]: an entry of opacity 0
   __shared__ float s_acc[kQB * 9];
   __shared__ uint64_t s_q[4][4];
   __shared__ int s_last[4];
-  const int lb = xcd_logical(blockIdx.x, per);
+  const int lb = q_block(blockIdx.x, total_blocks, per, by_view);
   if (lb >= total_blocks) return;
   const int b = lb / io.sn, sub = lb - b * io.sn;
   const int v = view_of(io, nv, b);
@@ -682,6 +761,12 @@ __global__ __launch_bounds__(kQB) void k_blend_bwd_q(ViewsIO io, int nv, int tot
   const uint2 r = ranges[b];
   if (r.y - r.x > (uint32_t)kPosMask) return;
   const int64_t hw = (int64_t)V.W * V.H;
+  if (lane == 0) {
+    s_st[k][64].xy = make_float2(0.f, 0.f);
+    s_st[k][64].co = make_float4(0.f, 0.f, 0.f, kLogNone);
+    s_st[k][64].rgb = make_float4(0.f, 0.f, 0.f, 0.f);
+    s_st[k][64].io = 0.f;
+  }
   float T = 1.f, dC0 = 0.f, dC1 = 0.f, dC2 = 0.f;
   int last = 0;
   if (px < V.W && py < V.H) {
@@ -706,8 +791,8 @@ __global__ __launch_bounds__(kQB) void k_blend_bwd_q(ViewsIO io, int nv, int tot
   }
   const int max_last = __builtin_amdgcn_readfirstlane(min(max_all, (int)(r.y - r.x)));
   if (max_last <= 0) return;  // uniform over the workgroup
-  const int slot = kRedSlot[lane >> 2];
-  const bool writes = (lane & 3) == 0 && slot >= 0;
+  const int slot = kRedSlot18[(lane >> 1) & 15];
+  const bool writes = (lane & 1) == 0 && slot >= 0, odd = (lane & 2) != 0;
   for (int bi = (max_last + kQB - 1) / kQB - 1; bi >= 0; bi--) {
     const int idx0 = bi * kQB;
     uint32_t qm = 0;
@@ -721,11 +806,11 @@ __global__ __launch_bounds__(kQB) void k_blend_bwd_q(ViewsIO io, int nv, int tot
       for (int i = 0; i < 4; i++)
         if (idx0 + tid >= qlast[i]) qm &= ~(1u << i);
       if (qm) {
-        s_st[tid].xy = xy;
-        s_st[tid].co = make_float4(-0.5f * kLog2e * cn.x, -kLog2e * cn.y, -0.5f * kLog2e * cn.z, __log2f(cn.w));
-        s_st[tid].rgb = make_float4(R.r2.x, R.r2.y, R.r2.z, __uint_as_float(cn.w >= kAlphaMax ? kClampBit : 0u));
-        s_st[tid].p = p;
-        s_st[tid].io = 1.0f / cn.w;
+        s_st[k][lane].xy = xy;
+        s_st[k][lane].co = make_float4(-0.5f * kLog2e * cn.x, -kLog2e * cn.y, -0.5f * kLog2e * cn.z, __log2f(cn.w));
+        s_st[k][lane].rgb = make_float4(R.r2.x, R.r2.y, R.r2.z, __uint_as_float(cn.w >= kAlphaMax ? kClampBit : 0u));
+        s_st[k][lane].p = p;
+        s_st[k][lane].io = 1.0f / cn.w;
       }
     }
 #pragma unroll
@@ -741,58 +826,68 @@ __global__ __launch_bounds__(kQB) void k_blend_bwd_q(ViewsIO io, int nv, int tot
       uint64_t m = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)mv) |
                    ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(mv >> 32)) << 32);
       if (m == 0) continue;
-      const BwdStage* st = s_st + g * 64;
-      int j = 63 - __builtin_clzll(m);
-      float2 xy = st[j].xy;
-      float4 co = st[j].co, c = st[j].rgb;
-      float iop = st[j].io;
-      while (m != 0) {
-        m &= ~(1ull << j);
-        const int jn = m ? 63 - (int)__builtin_clzll(m) : j;
-        const float2 xy_n = st[jn].xy;
-        const float4 co_n = st[jn].co, c_n = st[jn].rgb;
-        const float iop_n = st[jn].io;
-        const float dx = (xy.x - (float)qx) - kx, dy = (xy.y - (float)qy) - ky;
-        // the operations of k_blend_bwd
-        const float pw = fmaf(dx, fmaf(co.x, dx, co.y * dy), fmaf(co.z * dy, dy, co.w));
-        const float araw = __builtin_amdgcn_exp2f(pw);
-        const float a = fminf(kAlphaMax, araw);
-        const bool take = (idx0 + g * 64 + j < last) && (a >= kAlphaMin);
-        if (__ballot(take) != 0) {
-          const float ae = take ? a : 0.f;
-          T = T * __builtin_amdgcn_rcpf(1.f - ae);
-          const float wgt = ae * T;
-          float s[9];
-          s[6] = wgt * dC0;
-          s[7] = wgt * dC1;
-          s[8] = wgt * dC2;
-          const float ed = fmaf(c.x, dC0, fmaf(c.y, dC1, fmaf(c.z, dC2, nS)));
-          nS = fmaf(-ae, ed, nS);
-          float dP = wgt * ed;
-          if (__float_as_uint(c.w) != 0u) dP = araw < kAlphaMax ? dP : 0.f;
-          s[5] = dP * iop;
-          s[0] = dP * dx;
-          s[1] = dP * dy;
-          s[2] = s[0] * dx;
-          s[3] = s[0] * dy;
-          s[4] = s[1] * dy;
-          const float tot = wave_reduce9(s);
-          if (writes) atomicAdd(&s_acc[(g * 64 + j) * 9 + slot], tot);
+      const BwdStage* st = s_st[g];
+      int ja = q_last(m), jb = q_last(m);
+      BwdStage A = st[ja], B = st[jb];
+      auto blend2 = [&](const BwdStage& A, const BwdStage& B, int pa, int pb) {
+        // the operations of k_blend_bwd, the two alphas side by side
+        const float dxa = (A.xy.x - (float)qx) - kx, dya = (A.xy.y - (float)qy) - ky;
+        const float dxb = (B.xy.x - (float)qx) - kx, dyb = (B.xy.y - (float)qy) - ky;
+        const float ra = __builtin_amdgcn_exp2f(
+            fmaf(dxa, fmaf(A.co.x, dxa, A.co.y * dya), fmaf(A.co.z * dya, dya, A.co.w)));
+        const float rb = __builtin_amdgcn_exp2f(
+            fmaf(dxb, fmaf(B.co.x, dxb, B.co.y * dyb), fmaf(B.co.z * dyb, dyb, B.co.w)));
+        const float aa = fminf(kAlphaMax, ra), ab = fminf(kAlphaMax, rb);
+        const bool ta = (idx0 + g * 64 + pa < last) && (aa >= kAlphaMin);
+        const bool tb = (idx0 + g * 64 + pb < last) && (ab >= kAlphaMin);
+        if ((__ballot(ta) | __ballot(tb)) != 0) {
+          const float ea = ta ? aa : 0.f, eb = tb ? ab : 0.f;
+          const float ia = __builtin_amdgcn_rcpf(1.f - ea), ib = __builtin_amdgcn_rcpf(1.f - eb);
+          const float Ta = T * ia;
+          T = Ta * ib;
+          const float wa = ea * Ta, wb = eb * T;
+          const float da = fmaf(A.rgb.x, dC0, fmaf(A.rgb.y, dC1, fmaf(A.rgb.z, dC2, nS)));
+          nS = fmaf(-ea, da, nS);
+          const float db = fmaf(B.rgb.x, dC0, fmaf(B.rgb.y, dC1, fmaf(B.rgb.z, dC2, nS)));
+          nS = fmaf(-eb, db, nS);
+          float Pa = wa * da, Pb = wb * db;
+          const uint32_t wab = __float_as_uint(A.rgb.w) | __float_as_uint(B.rgb.w);
+          if (__builtin_expect(__builtin_amdgcn_readfirstlane((int)wab) != 0, 0)) {  // uniform, rare
+            __asm__ volatile("");
+            if (__float_as_uint(A.rgb.w) != 0u) Pa = ra < kAlphaMax ? Pa : 0.f;
+            if (__float_as_uint(B.rgb.w) != 0u) Pb = rb < kAlphaMax ? Pb : 0.f;
+          }
+          const float xa = Pa * dxa, ya = Pa * dya, xb = Pb * dxb, yb = Pb * dyb;
+          const float sa[9] = {xa, ya, xa * dxa, xa * dya, ya * dya, Pa * A.io, wa * dC0, wa * dC1, wa * dC2};
+          const float sb[9] = {xb, yb, xb * dxb, xb * dyb, yb * dyb, Pb * B.io, wb * dC0, wb * dC1, wb * dC2};
+          const float tot = wave_reduce18(sa, sb, odd);
+          const int pos = lane < 32 ? pa : pb;
+          if (writes && pos < 64) atomicAdd(&s_acc[(g * 64 + pos) * 9 + slot], tot);
         }
-        xy = xy_n;
-        co = co_n;
-        c = c_n;
-        iop = iop_n;
-        j = jn;
+      };
+      for (;;) {
+        bool more = m != 0;
+        int pa = ja, pb = jb;
+        ja = q_last(m), jb = q_last(m);
+        const BwdStage An = st[ja], Bn = st[jb];
+        blend2(A, B, pa, pb);
+        if (!more) break;
+        more = m != 0;
+        pa = ja, pb = jb;
+        ja = q_last(m), jb = q_last(m);
+        A = st[ja];
+        B = st[jb];
+        blend2(An, Bn, pa, pb);
+        if (!more) break;
       }
     }
     __syncthreads();
     // nine consecutive threads per entry: one 36-byte row
-#pragma unroll
+#pragma unroll 1
     for (int i = 0; i < 9; i++) {
       const int x = i * kQB + tid;
       const float val = s_acc[x];
-      if (val != 0.f) atomicAdd(&g2d[(int64_t)s_st[x / 9].p * 9 + x % 9], val);
+      if (val != 0.f) atomicAdd(&g2d[(int64_t)s_st[x / 9 / 64][x / 9 % 64].p * 9 + x % 9], val);
     }
     __syncthreads();
   }
@@ -943,15 +1038,23 @@ void launch_fill_u32(uint32_t* p, uint32_t v, int64_t n, hipStream_t st) {
 }
 
 // Whether a call's 16x16 sub-tiles are walked by one wave per quadrant: up to where the chip's
-// 1,024 SIMDs hold about six (forward) or four (backward) of the four-quadrant waves each, so the
+// 1,024 SIMDs hold about ten (forward) or four (backward) of the four-quadrant waves each, so the
 // longest list sets the time.  Measured, us forward / backward, four quadrants per wave -> one:
-// 64 sub-tiles (2k Gaussians at 128x128) 65 -> 22 / 125 -> 40; 1,280 (7k, 20 views at 128x128)
-// 243 -> 84 / 484 -> 182; 2,760 (200k at 960x720) 126 -> 83 / 195 -> 174; 5,632 (200k at 1352x1014)
-// 108 -> 95 / 205 -> 229; 8,160 115 -> 119 / 237 -> 295; 22,528 233 -> 292 / 512 -> 763 (there the
+// 1,280 sub-tiles (7k Gaussians, 20 views at 128x128) 244 -> 59 / 485 -> 118; 2,760 (200k at 960x720)
+// 127 -> 79 / 194 -> 185; 3,840 (300k at 1280x720) 195 -> 113 / 330 -> 272; 5,632 (200k at 1352x1014)
+// 110 -> 90 / 207 -> 245; 8,160 117 -> 111 / 243 -> 318; 11,264 150 -> 154 / 321 -> 454 (there the
 // LDS reads, one entry per quadrant instead of per four, and the reductions bound it).
-constexpr int64_t kByQuadrantFwd = 6144, kByQuadrantBwd = 4096;
+constexpr int64_t kByQuadrantFwd = 10240, kByQuadrantBwd = 4096;
 static inline bool by_quadrant(const ViewsIO& io, int64_t sub_tiles, int64_t most) {
   return io.sub == 16 && sub_tiles <= most;
+}
+
+// The number of views if there are several and all have as many tiles, else 0.
+static inline int views_alike(const ViewsIO& io, int nv, int64_t total_tiles) {
+  if (nv < 2 || total_tiles % nv) return 0;
+  for (int v = 1; v < nv; v++)
+    if (io.v[v].tile_base != v * (total_tiles / nv)) return 0;
+  return nv;
 }
 
 static inline int per_xcd(int64_t total_tiles) { return (int)((total_tiles + kNumXcd - 1) / kNumXcd); }
@@ -990,12 +1093,13 @@ void launch_blend_fwd(const ViewsIO& io, int nv, int64_t total_tiles, const floa
   iov.err = ws.err;
   if (by_quadrant(io, total, kByQuadrantFwd) && !count_pairs) {
     const dim3 grid(per * kNumXcd);
+    const int alike = views_alike(io, nv, total_tiles);
     if (l1)
-      k_blend_fwd_q<true><<<grid, kQB, 0, st>>>(iov, nv, (int)total, per, bg[0], bg[1], bg[2], ws.ranges, ws.vals,
+      k_blend_fwd_q<true><<<grid, kQB, 0, st>>>(iov, nv, (int)total, per, alike, bg[0], bg[1], bg[2], ws.ranges, ws.vals,
                                                 ws.rec_u, ws.loss_slots);
     else
-      k_blend_fwd_q<false><<<grid, kQB, 0, st>>>(iov, nv, (int)total, per, bg[0], bg[1], bg[2], ws.ranges, ws.vals,
-                                                 ws.rec_u, ws.loss_slots);
+      k_blend_fwd_q<false><<<grid, kQB, 0, st>>>(iov, nv, (int)total, per, alike, bg[0], bg[1], bg[2], ws.ranges,
+                                                 ws.vals, ws.rec_u, ws.loss_slots);
     return;
   }
   if (count_pairs) {
@@ -1070,8 +1174,8 @@ void launch_blend_bwd(const ViewsIO& io, int nv, int64_t total_tiles, const floa
   const int per = per_xcd(total);
   const dim3 grid(per * kNumXcd), block(kLanes);
   if (by_quadrant(io, total, kByQuadrantBwd)) {
-    k_blend_bwd_q<<<grid, kQB, 0, st>>>(io, nv, (int)total, per, bg[0], bg[1], bg[2], ws.ranges, ws.vals, ws.rec_u,
-                                        ws.g2d);
+    k_blend_bwd_q<<<grid, kQB, 0, st>>>(io, nv, (int)total, per, views_alike(io, nv, total_tiles), bg[0], bg[1], bg[2],
+                                        ws.ranges, ws.vals, ws.rec_u, ws.g2d);
     return;
   }
 #define DASS_BWD(SUBT, BT)                                                                                     \

@@ -230,32 +230,35 @@ def test_tile_lists_at_group_chunk_and_window_edges(n, log_scale, tile):
 @pytest.mark.parametrize("make", ["opaque", "ragged"])
 def test_blend_by_quadrant_matches_blend_by_subtile(make):
     """A call of few 16x16 sub-tiles is blended by one wave per 8x8 quadrant, one of many by one wave
-    per sub-tile.  The same view rendered alone (few) and twelve times over (more than 6,144 sub-tiles;
-    4,096 for the backward): images, T_final and n_contrib bit-identical; gradients of the
-    twelvefold call are twelve times the single one's up to the order of the float sums (1e-5 of
-    the tensor's largest, the sums having a few hundred terms of 2^-24 relative rounding each)."""
+    per sub-tile.  The same view rendered alone and three times over (few, the views' sub-tiles taken in
+    turn) and eighteen times (more than 10,240 sub-tiles; 4,096 for the backward): images, T_final and
+    n_contrib bit-identical; gradients of the k-fold call are k times the single one's up to the order of
+    the float sums (1e-5 of the tensor's largest, the sums having a few hundred terms of 2^-24 relative
+    rounding each)."""
     scene, cams, _ = (synth.opaque_scene(5, n=900, width=485, height=318, sh_degree=1) if make == "opaque"
                       else synth.tiny_scene(6, 1500, 489, 327, sh_degree=2, log_scale_mu=-2.2))
-    many = cams * 12
+    folds = (1, 3, 18)
     rng = np.random.default_rng(9)
     dl = torch.as_tensor(rng.normal(size=(3, cams[0].height, cams[0].width)).astype(np.float32), device="cuda")
     log(f"[by quadrant] {make}")
     g = to_gpu(scene)
     res = []
-    for cc in (cams, many):
+    for k in folds:
+        cc = cams * k
         ctx = make_ctx(scene.n, cc, keys_per_gaussian=700)
         out = ctx.render_fwd(g, cc, BG)
         grads = g.zeros_like()
         ctx.render_bwd(g, cc, BG, out, [dl] * len(cc), grads)
         ctx.sync()
         res.append((out, grads))
-    for o in res[1][0]:
-        assert torch.equal(o.rgb, res[0][0][0].rgb) and torch.equal(o.t_final, res[0][0][0].t_final)
-        assert torch.equal(o.n_contrib, res[0][0][0].n_contrib)
-    for a, b in zip(res[0][1].planes(), res[1][1].planes()):
-        scale = float(a.abs().max())
-        assert scale > 0.0
-        assert float((b / 12.0 - a).abs().max()) <= 1e-5 * scale
+    for k, (out, grads) in zip(folds[1:], res[1:]):
+        for o in out:
+            assert torch.equal(o.rgb, res[0][0][0].rgb) and torch.equal(o.t_final, res[0][0][0].t_final)
+            assert torch.equal(o.n_contrib, res[0][0][0].n_contrib)
+        for a, b in zip(res[0][1].planes(), grads.planes()):
+            scale = float(a.abs().max())
+            assert scale > 0.0
+            assert float((b / k - a).abs().max()) <= 1e-5 * scale
 
 
 @pytest.mark.parametrize("n", [1, 63, 1025, 2048, 2049, 4097, 8193, 12289, 16384, 16385, 40000])
