@@ -132,7 +132,7 @@ __device__ __forceinline__ float dppf(float x) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, true));
 }
 
-// Transposing reduction of 9 per-lane values over the wave: each step pairs values (x, y) and
+// Transposing reduction of nine per-lane values of two list entries over the wave: each step pairs values (x, y) and
 // adds every value to its copy on the partner lane across one lane bit, keeping x's pair total
 // on the lanes with that bit clear and y's on the lanes with it set, so the number of values
 // per lane halves at each step without selects.
@@ -169,25 +169,9 @@ __device__ __forceinline__ float dpp_pair4(float x, float y) {
   return o;
 }
 
-// Sums v[0..8] over the wave.  Afterwards lane 4 m + i (i < 4) holds the total of value
-// kRedSlot[m] (-1: a duplicate of another lane's total, or none).
-__device__ __forceinline__ float wave_reduce9(const float* v) {
-  // bit 5 -> upper half of the lanes holds values 5, 6, 7, 8, 4
-  const float a0 = swap32_sum(v[0], v[5]), a1 = swap32_sum(v[1], v[6]), a2 = swap32_sum(v[2], v[7]);
-  const float a3 = swap32_sum(v[3], v[8]), a4 = swap32_sum(v[4], v[4]);
-  // bit 4 -> (bit 5, bit 4) = 00: 0 1 2, 01: 3 4 2, 10: 5 6 7, 11: 8 4 7
-  const float b0 = swap16_sum(a0, a3), b1 = swap16_sum(a1, a4), b2 = swap16_sum(a2, a2);
-  // bit 3 -> (bits 5..3) = 000: 0 1, 001: 2 1, 010: 3 4, 011: 2 4, 100: 5 6, 101: 7 6, 110: 8 4, 111: 7 4
-  const float c0 = dpp_pair8(b0, b2);
-  const float c1 = b1 + dppf<0x128>(b1);  // row_ror 8
-  // bit 2 -> one value per lane (bits 5..2 = m, kRedSlot[m])
-  float d = dpp_pair4(c0, c1);
-  d += dppf<0xB1>(d);  // bits 1, 0: the four lanes of a bank (quad_perm 1,0,3,2 then 2,3,0,1)
-  d += dppf<0x4E>(d);
-  return d;
-}
-// Two entries' nine values at once, in fewer steps than twice the above: bit 5 -> entry (v0 below lane
-// 32, v1 above), bits 4..1 = m -> value kRedSlot18[m] (-1: a duplicate).  `odd` = lane bit 1.
+// Sums two entries' nine values v0, v1 over the wave.  Afterwards lane bit 5 is the entry and bits 4..1
+// = m the value kRedSlot[m] (-1: a duplicate of another lane's total); `odd` = lane bit 1.  41
+// instructions for the two (one entry at a time: 26 each, for a full wave that carries one).
 __device__ __forceinline__ float wave_reduce18(const float* v0, const float* v1, bool odd) {
   float c[9];
 #pragma unroll
@@ -195,17 +179,16 @@ __device__ __forceinline__ float wave_reduce18(const float* v0, const float* v1,
   // bit 4 -> 0 1 2 3 4 or 5 6 7 8 4
   const float b0 = swap16_sum(c[0], c[5]), b1 = swap16_sum(c[1], c[6]), b2 = swap16_sum(c[2], c[7]);
   const float b3 = swap16_sum(c[3], c[8]), b4 = swap16_sum(c[4], c[4]);
-  // bit 3 -> 0 1 2 or 3 4 2
+  // bit 3 -> (bits 4, 3) = 00: 0 1 2, 01: 3 4 2, 10: 5 6 7, 11: 8 4 7
   const float d0 = dpp_pair8(b0, b3), d1 = dpp_pair8(b1, b4), d2 = b2 + dppf<0x128>(b2);
-  // bit 2 -> 0 2 or 1 2
+  // bit 2 -> the first or the second of these, and the third
   float e0 = dpp_pair4(d0, d1), e1 = dpp_pair4(d2, d2);
-  e0 += dppf<0x4E>(e0);  // bit 1 -> 0 or 2
+  e0 += dppf<0x4E>(e0);  // quad_perm 2, 3, 0, 1
   e1 += dppf<0x4E>(e1);
   const float f = odd ? e1 : e0;
-  return f + dppf<0xB1>(f);
+  return f + dppf<0xB1>(f);  // quad_perm 1, 0, 3, 2
 }
-__constant__ int kRedSlot18[16] = {0, 2, 1, -1, 3, -1, 4, -1, 5, 7, 6, -1, 8, -1, -1, -1};
-__constant__ int kRedSlot[16] = {0, 1, 2, -1, 3, 4, -1, -1, 5, 6, 7, -1, 8, -1, -1, -1};
+__constant__ int kRedSlot[16] = {0, 2, 1, -1, 3, -1, 4, -1, 5, 7, 6, -1, 8, -1, -1, -1};
 
 // A staged list entry in LDS: one 48-byte row, so a wave reads an entry's fields from one address.
 struct FwdStage {
@@ -436,8 +419,8 @@ __global__ __launch_bounds__(kLanes) void k_blend_bwd(ViewsIO io, int nv, int to
   }
   const int max_last = min(max_all, (int)(r.y - r.x));  // n_contrib never exceeds the list length
   if (max_last <= 0) return;
-  const int slot = kRedSlot[lane >> 2];
-  const bool writes = (lane & 3) == 0 && slot >= 0;
+  const int slot = kRedSlot[(lane >> 1) & 15];
+  const bool writes = (lane & 1) == 0 && slot >= 0, odd = (lane & 2) != 0;
   const int nbatch = (max_last + B - 1) / B;
   for (int bi = nbatch - 1; bi >= 0; bi--) {
     const uint32_t start = r.x + (uint32_t)bi * B;
@@ -479,7 +462,8 @@ __global__ __launch_bounds__(kLanes) void k_blend_bwd(ViewsIO io, int nv, int to
       n_kept += __popcll(m);
     }
     __syncthreads();
-    for (int j = n_kept - 1; j >= 0; j--) {
+    // one entry over the sub-tile's quadrants: whether any pixel blended it
+    auto entry = [&](int j, float* __restrict__ m) {
       const float2 xy = s_st[j].xy;
       const float4 co = s_st[j].co;
       const float4 c = s_st[j].rgb;
@@ -490,7 +474,6 @@ __global__ __launch_bounds__(kLanes) void k_blend_bwd(ViewsIO io, int nv, int to
       // per-lane sums over its pixels: m = (sum dP dx, sum dP dy, sum dP dx^2, sum dP dx dy,
       // sum dP dy^2, d opacity (times the opacity until the reduction), d rgb),
       // dP = dL/d(exponent), (dx, dy) = mean - pixel
-      float m[9];
 #pragma unroll
       for (int q = 0; q < 9; q++) m[q] = 0.f;
       bool any = false;
@@ -532,12 +515,25 @@ __global__ __launch_bounds__(kLanes) void k_blend_bwd(ViewsIO io, int nv, int to
         m[3] = fmaf(pdx, dy, m[3]);
         m[4] = fmaf(pdy, dy, m[4]);
       }
-      if (any) {  // uniform
+      return any;
+    };
+    // two entries at a time, for their sums over the lanes to be taken together (one at a time, us:
+    // 13 views of 1280x720 1012, 4 of 1920x1080 1005; now 990, 980)
+    for (int j = n_kept - 1; j >= 0; j -= 2) {
+      float m0[9], m1[9];
+      const bool any0 = entry(j, m0);
+      const bool any1 = j > 0 && entry(j - 1, m1);
+      if (j == 0) {
+#pragma unroll
+        for (int q = 0; q < 9; q++) m1[q] = 0.f;
+      }
+      if (any0 || any1) {  // uniform
         // the sums are linear in the entry's conic, so the conic is applied once per
         // (view, Gaussian) by the projection adjoint, not here
-        m[5] *= s_st[j].io;
-        const float tot = wave_reduce9(m);
-        if (writes) atomicAdd(&g2d[(int64_t)s_st[j].p * 9 + slot], tot);
+        const float tot = wave_reduce18(m0, m1, odd);
+        const int e = lane < 32 ? j : max(j - 1, 0);
+        const float o = slot == 5 ? s_st[e].io : 1.f;
+        if (writes && (lane < 32 ? any0 : any1)) atomicAdd(&g2d[(int64_t)s_st[e].p * 9 + slot], tot * o);
       }
     }
   }
@@ -791,7 +787,7 @@ __global__ __launch_bounds__(kQB) void k_blend_bwd_q(ViewsIO io, int nv, int tot
   }
   const int max_last = __builtin_amdgcn_readfirstlane(min(max_all, (int)(r.y - r.x)));
   if (max_last <= 0) return;  // uniform over the workgroup
-  const int slot = kRedSlot18[(lane >> 1) & 15];
+  const int slot = kRedSlot[(lane >> 1) & 15];
   const bool writes = (lane & 1) == 0 && slot >= 0, odd = (lane & 2) != 0;
   for (int bi = (max_last + kQB - 1) / kQB - 1; bi >= 0; bi--) {
     const int idx0 = bi * kQB;
