@@ -1058,17 +1058,24 @@ dass_status densify_append(dass_ctx ctx, dass_gaussians* g, const float* const* 
   Workspace& ws = ctx->ws;
   const SceneK sc = scene_of(g);
   stage_begin(ctx, DASS_STAGE_DENSIFY, st);
-  launch_fill_u32(ws.counters + 1, 0u, 1, st);
-  // members packed in index order into u32 keys (the depth-sort buffers, free here), the score key
-  // staged in the second buffer; a stable 32-bit sort ranks by score, ties by index
-  uint32_t* k32[2] = {ws.dkey[0], ws.dkey[1]};
-  launch_densify_select(sc, a, gradnorm_sum, grad_count, g->n_base, ws.keep, ws.keep_scan, ws.scan_tmp, k32[1], k32[0],
-                        ws.dval[0], ws.counters + 1, st);
-  const int cur = radix_sort_u32(k32, ws.dval, ws.counters + 1, g->n_base, 0, 32, ws.hist, sort_blocks_for(g->n_base),
-                                 st);
+  // the depth-sort buffers are free here: the rows of codes and the keys lie in them
+  const DensifyWs w{ws.dkey[0], ws.cap_vn, ws.keep, ws.dkey[1], ws.keep_scan, ws.hist};
+  const int want = std::max(0, std::min<int>(k_max, g->capacity - g->n));
+  const uint32_t* parents = ws.dval[0];
+  if (densify_selects(want)) {
+    launch_densify_select(sc, a, gradnorm_sum, grad_count, g->n_base, want, w, ws.dval[0], ws.counters + 1, st);
+  } else {
+    // members packed in index order, the codes no longer needed; a stable 32-bit sort ranks by score,
+    // ties by index
+    uint32_t* k32[2] = {ws.dkey[0], ws.dkey[1]};
+    launch_densify_pack(sc, a, gradnorm_sum, grad_count, g->n_base, w, ws.scan_tmp, k32[0], ws.dval[0], ws.counters + 1,
+                        st);
+    parents = ws.dval[radix_sort_u32(k32, ws.dval, ws.counters + 1, g->n_base, 0, 32, ws.hist,
+                                     sort_blocks_for(g->n_base), st)];
+  }
   const int K = (g->sh_degree + 1) * (g->sh_degree + 1);
   launch_densify_spawn(g->mean, g->quat, g->log_scale, g->opacity_logit, g->sh, 3 * K, g->capacity, g->n,
-                       g->capacity, ws.dval[cur], ws.counters + 1, k_max, seed, n_appended, st);
+                       g->capacity, parents, ws.counters + 1, k_max, seed, n_appended, st);
   stage_end(ctx, DASS_STAGE_DENSIFY, st);
   ctx->have_fwd = false;  // the depth-order buffers were reused
   return check_launch(ctx, "densify_append");

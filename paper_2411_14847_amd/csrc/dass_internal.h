@@ -351,9 +351,24 @@ struct DensifyArgs {
   int nv;
   float gamma_err, tau_pos, tau_err;
 };
+// Scratch of a densification (api.hip lends buffers that are free between renders).
+struct DensifyWs {
+  uint32_t* codes;      // [cap_codes] rows of n_base
+  int64_t cap_codes;    // >= n_base
+  uint32_t* keep;       // [n_base] members
+  uint32_t* score_key;  // [n_base] rank keys
+  uint64_t* pos;        // [n_base + 1]
+  uint32_t* sel;        // [8192] histograms, state and counts of the selection
+};
+// Whether a call that uses `want` ranked members selects them, or ranks all members by a sort.
+bool densify_selects(int want);
+// sel_idx[0 .. min(|S|, want)): the best members in rank order; *d_count = |S| (0 if want is 0).
 void launch_densify_select(const SceneK& s, const DensifyArgs& a, const float* gsum, const int32_t* gcnt, int n_base,
-                           uint32_t* keep, uint64_t* pos, uint64_t* scan_tmp, uint32_t* score_key, uint32_t* sel_keys,
-                           uint32_t* sel_vals, uint32_t* d_count, hipStream_t st);
+                           int want, const DensifyWs& w, uint32_t* sel_idx, uint32_t* d_count, hipStream_t st);
+// All members in index order with their rank keys, for a stable sort; *d_count = |S|.
+void launch_densify_pack(const SceneK& s, const DensifyArgs& a, const float* gsum, const int32_t* gcnt, int n_base,
+                         const DensifyWs& w, uint64_t* scan_tmp, uint32_t* sel_keys, uint32_t* sel_vals,
+                         uint32_t* d_count, hipStream_t st);
 void launch_densify_spawn(float* mean, float* quat, float* log_scale, float* logit, float* sh, int n_planes_sh,
                           int stride, int n, int capacity, const uint32_t* sel_idx, const uint32_t* d_count,
                           int k_max, uint64_t seed, int32_t* n_appended, hipStream_t st);

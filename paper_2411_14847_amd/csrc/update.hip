@@ -2,6 +2,8 @@
 // adjoint, a multi-tensor Adam step, the L1 fidelity gradient with the error map (Sec. 3.4),
 // and error-guided densification (Sec. 3.4, Alg. 1, Eq. 4).  All are memory-bound
 // elementwise passes; each is one launch over all of its groups / views.
+#include <algorithm>
+
 #include "dass_internal.h"
 
 namespace dass {
@@ -173,54 +175,279 @@ __device__ bool alg1_pixel(const double* T, int Wi, int Hi, double X, double Y, 
   return true;
 }
 
-// Selection (Alg. 1): a workgroup takes 64 base Gaussians, its wave w the views w, w + 4, ...
-// (the view index stays uniform over a wave); the score is the largest error at the Gaussian's
-// pixel over the views that see it.  Wave 0 combines the four waves and writes, per Gaussian, the
-// membership flag and the rank key (complemented score bits: ascending key = descending score);
-// a scan then packs the members in index order, so a stable sort on the 32-bit key alone ranks
-// them with ties by index.
-constexpr int kSelWaves = 4;
-__global__ __launch_bounds__(64 * kSelWaves) void k_densify_select(SceneK s, DensifyArgs a,
-                                                                   const float* __restrict__ gsum,
-                                                                   const int32_t* __restrict__ gcnt, int n_base,
-                                                                   uint32_t* __restrict__ keep,
-                                                                   uint32_t* __restrict__ score_key) {
+// Selection (Alg. 1), two kernels.  The score is the largest error at the Gaussian's pixel over the
+// views that see it; the member test needs it, whether any of these errors passes gamma, and the mean
+// gradient norm.
+//
+// k_densify_scores reads the error maps at random pixels, a line per read, and is bound by these lines:
+// an XCD takes the (view, Gaussians) blocks of one view after the other, so that the lines of one map
+// (5.5 MB at 1352x1014) are read again from its 4 MB L2 and not all views' maps at once.  Each of up to
+// `planes` groups of views leaves its largest error in a row of codes.  200k Gaussians, 20 views of
+// 1352x1014: 65 us with a workgroup over all views, 34 now.
+constexpr int kScoreThreads = 256, kScorePer = 4;  // Gaussians of a workgroup: 1,024
+__global__ __launch_bounds__(kScoreThreads) void k_densify_scores(SceneK s, DensifyArgs a, int n_base, int group,
+                                                                 int chunks, int total, int per,
+                                                                 uint32_t* __restrict__ codes) {
   __shared__ double s_T[DASS_MAX_VIEWS][12];
-  __shared__ float s_score[kSelWaves][64];
-  __shared__ int s_ie[kSelWaves][64];
-  for (int v = threadIdx.x; v < a.nv; v += blockDim.x) alg1_columns(a.cams[v], s_T[v]);
+  const int b = (int)(blockIdx.x % kNumXcd) * per + (int)(blockIdx.x / kNumXcd);
+  if (b >= total) return;
+  const int row = b / chunks, g0 = (b - row * chunks) * (kScoreThreads * kScorePer) + (int)threadIdx.x;
+  const int v0 = row * group, v1 = min(v0 + group, a.nv);
+  if (v0 + (int)threadIdx.x < v1) alg1_columns(a.cams[v0 + threadIdx.x], s_T[threadIdx.x]);
   __syncthreads();
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int g = blockIdx.x * 64 + lane;
-  bool in_err = false;
-  float score = 0.f;
-  if (g < n_base) {
-    const double X = s.mean[g], Y = s.mean[(int64_t)s.stride + g], Z = s.mean[2 * (int64_t)s.stride + g];
-    for (int v = wave; v < a.nv; v += kSelWaves) {
+  double X[kScorePer], Y[kScorePer], Z[kScorePer];
+  uint32_t code[kScorePer];
+#pragma unroll
+  for (int i = 0; i < kScorePer; i++) {
+    const int g = min(g0 + i * kScoreThreads, n_base - 1);
+    X[i] = s.mean[g];
+    Y[i] = s.mean[(int64_t)s.stride + g];
+    Z[i] = s.mean[2 * (int64_t)s.stride + g];
+    code[i] = 0u;
+  }
+  for (int v = v0; v < v1; v++) {
+    const int W = a.cams[v].W, H = a.cams[v].H;
+    bool in[kScorePer];
+    float e[kScorePer];
+#pragma unroll
+    for (int i = 0; i < kScorePer; i++) {
       int x, y;
-      if (alg1_pixel(s_T[v], a.cams[v].W, a.cams[v].H, X, Y, Z, x, y)) {
-        const float e = a.err[v][(int64_t)y * a.cams[v].W + x];
-        in_err |= e > a.gamma_err;
-        score = fmaxf(score, e);
-      }
+      in[i] = alg1_pixel(s_T[v - v0], W, H, X[i], Y[i], Z[i], x, y);
+      e[i] = in[i] ? a.err[v][(int64_t)y * W + x] : 0.f;
+    }
+    // the error, at least 0, and below it whether the error passes gamma: the largest code of the
+    // views has both for all of them
+#pragma unroll
+    for (int i = 0; i < kScorePer; i++)
+      if (in[i]) code[i] = max(code[i], __float_as_uint(fmaxf(0.f, e[i])) << 1 | (e[i] > a.gamma_err ? 1u : 0u));
+  }
+#pragma unroll
+  for (int i = 0; i < kScorePer; i++)
+    if (g0 + i * kScoreThreads < n_base) codes[(int64_t)row * n_base + g0 + i * kScoreThreads] = code[i];
+}
+
+// The k_max best members are all that a call uses of the ranking, so that they are selected, not sorted:
+// three histogram passes over 11, 11 and 10 bits of the rank key (the complemented score bits: ascending
+// key = descending score, ties by index) find the key of the last one, two more collect the members
+// before it and as many of that key as still fit, in index order, and each one's rank among them is
+// counted.  Every pass takes the Gaussians in at most kSelBlocks equal runs.  200k Gaussians, 20 views,
+// 5,000 children: pack, scan and a stable sort of all members in 13 launches 109 us, now 6 and 45 us; up to
+// kSelMost children (the count of ranks grows with their square; the call with 16,384 137 us, sorted 153), else they are sorted.
+constexpr int kSelThreads = 1024, kSelBlocks = 256, kSelBits[3] = {11, 11, 10}, kSelShift[3] = {21, 10, 0};
+constexpr int kSelBins = 2048, kSelMost = 16384;
+// uint32 workspace: histograms [3][kSelBins], state, counts [kSelBlocks][2]
+constexpr int kSelState = 3 * kSelBins, kSelCounts = kSelState + 16;
+struct SelRun {
+  int n, run, want;  // Gaussians, of a workgroup, best members that are used (at most)
+};
+
+// The digit of the want-th smallest key among those of the histogram (want >= 1, at most their number),
+// and the keys with a smaller one: to *state.  Whole workgroup.
+__device__ __forceinline__ uint32_t sel_digit(const uint32_t* __restrict__ hist, uint32_t want, uint32_t* s_w,
+                                              uint32_t* s_res, uint32_t& before) {
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const uint32_t h0 = hist[2 * tid], h1 = hist[2 * tid + 1];
+  uint32_t inc = h0 + h1;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t y = __shfl_up(inc, d, 64);
+    if (lane >= d) inc += y;
+  }
+  if (lane == 63) s_w[w] = inc;
+  __syncthreads();
+  uint32_t base = 0;
+  for (int i = 0; i < w; i++) base += s_w[i];
+  const uint32_t e0 = base + inc - h0 - h1, e1 = e0 + h0;
+  if (e0 < want && want <= e1) s_res[0] = 2 * tid, s_res[1] = e0;
+  if (e1 < want && want <= e1 + h1) s_res[0] = 2 * tid + 1, s_res[1] = e1;
+  __syncthreads();
+  before = s_res[1];
+  return s_res[0];
+}
+
+// Adds the workgroup's histogram to the call's.
+__device__ __forceinline__ void sel_add(const uint32_t* __restrict__ s_h, uint32_t* __restrict__ hist) {
+  __syncthreads();
+  for (int i = threadIdx.x; i < kSelBins; i += kSelThreads)
+    if (s_h[i]) atomicAdd(&hist[i], s_h[i]);
+}
+
+// Members and their rank keys from the rows of codes; the first digit's histogram (sel != 0).
+__global__ __launch_bounds__(kSelThreads) void k_densify_members(SelRun r, const uint32_t* __restrict__ codes, int rows,
+                                                                 float tau_pos, float tau_err,
+                                                                 const float* __restrict__ gsum,
+                                                                 const int32_t* __restrict__ gcnt,
+                                                                 uint32_t* __restrict__ keep,
+                                                                 uint32_t* __restrict__ score_key,
+                                                                 uint32_t* __restrict__ sel) {
+  __shared__ uint32_t s_h[kSelBins];
+  for (int i = threadIdx.x; i < kSelBins; i += kSelThreads) s_h[i] = 0u;
+  __syncthreads();
+  const int g1 = min((int)(blockIdx.x + 1) * r.run, r.n);
+  for (int g = blockIdx.x * r.run + threadIdx.x; g < g1; g += kSelThreads) {
+    uint32_t code = 0u;
+#pragma unroll 4
+    for (int k = 0; k < rows; k++) code = max(code, codes[(int64_t)k * r.n + g]);
+    const int32_t c = gcnt[g];
+    const float gbar = c > 0 ? gsum[g] / (float)c : 0.f;
+    const bool in_s = (gbar > tau_pos) || ((code & 1u) != 0 && gbar > tau_err);
+    const uint32_t key = ~(code >> 1);
+    keep[g] = in_s ? 1u : 0u;
+    score_key[g] = key;
+    if (sel && in_s) atomicAdd(&s_h[key >> kSelShift[0]], 1u);
+  }
+  if (sel) sel_add(s_h, sel);
+}
+
+// The digit of pass P - 1 (to the state, with what is still wanted beyond it), and the histogram of
+// pass P over the keys that agree in the digits before.  state: [0] key prefix, [1] still wanted.
+template <int P>
+__global__ __launch_bounds__(kSelThreads) void k_densify_digit(SelRun r, const uint32_t* __restrict__ keep,
+                                                               const uint32_t* __restrict__ score_key,
+                                                               uint32_t* __restrict__ sel,
+                                                               uint32_t* __restrict__ d_count) {
+  __shared__ uint32_t s_h[kSelBins], s_w[kSelThreads / 64], s_res[2], s_n;
+  uint32_t* __restrict__ state = sel + kSelState + 4 * P;  // of this pass (the one before: 4 words earlier)
+  for (int i = threadIdx.x; i < kSelBins; i += kSelThreads) s_h[i] = 0u;
+  uint32_t want, prefix = 0u;
+  if (P == 1) {  // the first digit's histogram also gives the number of members
+    if (threadIdx.x == 0) s_n = 0u;
+    __syncthreads();
+    uint32_t m = sel[2 * threadIdx.x] + sel[2 * threadIdx.x + 1];
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) m += __shfl_xor(m, d, 64);
+    if ((threadIdx.x & 63) == 0) atomicAdd(&s_n, m);
+    __syncthreads();
+    if (blockIdx.x == 0 && threadIdx.x == 0) *d_count = s_n;
+    want = min(s_n, (uint32_t)r.want);
+  } else {
+    prefix = state[-4];
+    want = state[-3];
+  }
+  if (want == 0u) {  // no members: nothing is collected
+    if (blockIdx.x == 0 && threadIdx.x == 0) state[0] = 0u, state[1] = 0u;
+    return;
+  }
+  uint32_t before;
+  const uint32_t digit = sel_digit(sel + (P - 1) * kSelBins, want, s_w, s_res, before);
+  prefix |= digit << kSelShift[P - 1];
+  want -= before;
+  if (blockIdx.x == 0 && threadIdx.x == 0) state[0] = prefix, state[1] = want;
+  const int g1 = min((int)(blockIdx.x + 1) * r.run, r.n);
+  for (int g = blockIdx.x * r.run + threadIdx.x; g < g1; g += kSelThreads) {
+    const uint32_t key = score_key[g];
+    if (keep[g] && (key >> kSelShift[P - 1]) == (prefix >> kSelShift[P - 1]))
+      atomicAdd(&s_h[(key >> kSelShift[P]) & ((1u << kSelBits[P]) - 1u)], 1u);
+  }
+  sel_add(s_h, sel + P * kSelBins);
+}
+
+// The last digit, and how many members of each run lie before the key and at it.
+__global__ __launch_bounds__(kSelThreads) void k_densify_count(SelRun r, const uint32_t* __restrict__ keep,
+                                                               const uint32_t* __restrict__ score_key,
+                                                               uint32_t* __restrict__ sel) {
+  __shared__ uint32_t s_w[kSelThreads / 64], s_res[2], s_c[2];
+  uint32_t* __restrict__ state = sel + kSelState + 12;
+  uint32_t prefix = state[-4], want = state[-3];
+  if (want == 0u) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) state[0] = 0u, state[1] = 0u;
+    return;
+  }
+  if (threadIdx.x < 2) s_c[threadIdx.x] = 0u;
+  uint32_t before;
+  prefix |= sel_digit(sel + 2 * kSelBins, want, s_w, s_res, before);
+  want -= before;
+  if (blockIdx.x == 0 && threadIdx.x == 0) state[0] = prefix, state[1] = want;
+  uint32_t less = 0, same = 0;
+  const int g1 = min((int)(blockIdx.x + 1) * r.run, r.n);
+  for (int g = blockIdx.x * r.run + threadIdx.x; g < g1; g += kSelThreads) {
+    const uint32_t key = score_key[g];
+    if (keep[g]) less += key < prefix ? 1u : 0u, same += key == prefix ? 1u : 0u;
+  }
+  if (less) atomicAdd(&s_c[0], less);
+  if (same) atomicAdd(&s_c[1], same);
+  __syncthreads();
+  if (threadIdx.x < 2) sel[kSelCounts + 2 * blockIdx.x + threadIdx.x] = s_c[threadIdx.x];
+}
+
+// (key, index) of the members before the key of the last one, and of the first `want` at it, in index
+// order per kind: those before first.
+__global__ __launch_bounds__(kSelThreads) void k_densify_collect(SelRun r, const uint32_t* __restrict__ keep,
+                                                                 const uint32_t* __restrict__ score_key,
+                                                                 const uint32_t* __restrict__ sel,
+                                                                 uint64_t* __restrict__ out) {
+  __shared__ uint32_t s_w[2][kSelThreads / 64], s_at[2], s_less;
+  const uint32_t last = sel[kSelState + 12], want = sel[kSelState + 13];
+  if (want == 0u) return;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  if (tid < 2) s_at[tid] = 0u;
+  if (tid == 2) s_less = 0u;
+  __syncthreads();
+  if (tid < (int)gridDim.x) {
+    const uint32_t l = sel[kSelCounts + 2 * tid], e = sel[kSelCounts + 2 * tid + 1];
+    if (l) atomicAdd(&s_less, l);
+    if (tid < (int)blockIdx.x) {
+      if (l) atomicAdd(&s_at[0], l);
+      if (e) atomicAdd(&s_at[1], e);
     }
   }
-  s_score[wave][lane] = score;
-  s_ie[wave][lane] = in_err ? 1 : 0;
   __syncthreads();
-  if (wave != 0) return;
-  int ie = 0;
-#pragma unroll
-  for (int w = 0; w < kSelWaves; w++) {
-    score = fmaxf(score, s_score[w][lane]);
-    ie |= s_ie[w][lane];
+  uint32_t at_l = s_at[0], at_e = s_at[1];
+  const uint32_t all_less = s_less;
+  const uint64_t lt = (1ull << lane) - 1ull;
+  const int g0 = blockIdx.x * r.run, g1 = min(g0 + r.run, r.n);
+  for (int base = g0; base < g1; base += kSelThreads) {  // uniform
+    const int g = base + tid;
+    const uint32_t key = g < g1 ? score_key[g] : 0u;
+    const bool in = g < g1 && keep[g] != 0u;
+    const uint64_t bl = __ballot(in && key < last), be = __ballot(in && key == last);
+    if (lane == 0) {
+      s_w[0][w] = (uint32_t)__popcll(bl);
+      s_w[1][w] = (uint32_t)__popcll(be);
+    }
+    __syncthreads();
+    uint32_t ol = at_l, oe = at_e, tl = 0, te = 0;
+    for (int i = 0; i < kSelThreads / 64; i++) {
+      if (i < w) ol += s_w[0][i], oe += s_w[1][i];
+      tl += s_w[0][i];
+      te += s_w[1][i];
+    }
+    const uint64_t kv = (uint64_t)key << 32 | (uint32_t)g;
+    if (in && key < last) out[ol + (uint32_t)__popcll(bl & lt)] = kv;
+    if (in && key == last) {
+      const uint32_t e = oe + (uint32_t)__popcll(be & lt);
+      if (e < want) out[all_less + e] = kv;
+    }
+    at_l += tl;
+    at_e += te;
+    __syncthreads();
   }
-  if (g >= n_base) return;
-  const int32_t c = gcnt[g];
-  const float gbar = c > 0 ? gsum[g] / (float)c : 0.f;
-  const bool in_s = (gbar > a.tau_pos) || (ie != 0 && gbar > a.tau_err);
-  keep[g] = in_s ? 1u : 0u;
-  score_key[g] = ~__float_as_uint(score);
+}
+
+// Ranks of the collected members by counting: sixteen lanes share a member and take every sixteenth of
+// the others, tile after tile of LDS.
+constexpr int kRankThreads = 256, kRankLanes = 16, kRankTile = 4096;
+__global__ __launch_bounds__(kRankThreads) void k_densify_rank(int want, const uint32_t* __restrict__ d_count,
+                                                               const uint64_t* __restrict__ in,
+                                                               uint32_t* __restrict__ sel_idx) {
+  __shared__ uint64_t s_k[kRankTile];
+  const int m = (int)min(*d_count, (uint32_t)want);
+  const int i0 = blockIdx.x * (kRankThreads / kRankLanes);
+  if (i0 >= m) return;
+  const int i = i0 + (int)threadIdx.x / kRankLanes, sub = threadIdx.x % kRankLanes;
+  const uint64_t mine = in[min(i, m - 1)];
+  int rank = 0;
+  for (int base = 0; base < m; base += kRankTile) {
+    const int cnt = min(kRankTile, m - base);
+    __syncthreads();
+    for (int j = threadIdx.x; j < cnt; j += kRankThreads) s_k[j] = in[base + j];
+    __syncthreads();
+#pragma unroll 8
+    for (int j = sub; j < cnt; j += kRankLanes) rank += s_k[j] < mine ? 1 : 0;
+  }
+#pragma unroll
+  for (int d = 1; d < kRankLanes; d <<= 1) rank += __shfl_xor(rank, d, 64);
+  if (sub == 0 && i < m) sel_idx[rank] = (uint32_t)mine;
 }
 
 // members packed in index order: key and Gaussian index at the member's rank in the scan
@@ -344,13 +571,53 @@ void launch_l1(const L1Args& a, int64_t total_blocks, float* loss, hipStream_t s
   if (total_blocks > 0) k_l1<<<(unsigned)total_blocks, 256, 0, st>>>(a, loss);
 }
 
+static void densify_members(const SceneK& s, const DensifyArgs& a, const DensifyWs& w, const SelRun& r,
+                            const float* gsum, const int32_t* gcnt, uint32_t* sel, hipStream_t st) {
+  // a row of codes per group of views, as many as the buffer holds: one view each unless a call has
+  // more views than the context was made for
+  const int rows_max = (int)std::min<int64_t>(a.nv, w.cap_codes / r.n);
+  const int group = (a.nv + rows_max - 1) / rows_max, rows = (a.nv + group - 1) / group;
+  const int chunk = kScoreThreads * kScorePer, chunks = (r.n + chunk - 1) / chunk;
+  const int64_t total = (int64_t)rows * chunks, per = (total + kNumXcd - 1) / kNumXcd;
+  k_densify_scores<<<(unsigned)(per * kNumXcd), kScoreThreads, 0, st>>>(s, a, r.n, group, chunks, (int)total, (int)per,
+                                                                       w.codes);
+  k_densify_members<<<(r.n + r.run - 1) / r.run, kSelThreads, 0, st>>>(r, w.codes, rows, a.tau_pos, a.tau_err, gsum, gcnt,
+                                                                      w.keep, w.score_key, sel);
+}
+
+static SelRun sel_run(int n, int want) {
+  const int per = (n + kSelBlocks - 1) / kSelBlocks;
+  return SelRun{n, (per + kSelThreads - 1) / kSelThreads * kSelThreads, want};
+}
+
+bool densify_selects(int want) { return want <= kSelMost; }
+
 void launch_densify_select(const SceneK& s, const DensifyArgs& a, const float* gsum, const int32_t* gcnt, int n_base,
-                           uint32_t* keep, uint64_t* pos, uint64_t* scan_tmp, uint32_t* score_key, uint32_t* sel_keys,
-                           uint32_t* sel_vals, uint32_t* d_count, hipStream_t st) {
-  if (n_base <= 0) return;  // *d_count stays at the zero the caller wrote
-  k_densify_select<<<(n_base + 63) / 64, 64 * kSelWaves, 0, st>>>(s, a, gsum, gcnt, n_base, keep, score_key);
-  scan_u32_to_u64(keep, pos, n_base, scan_tmp, st);
-  k_densify_pack<<<(n_base + 255) / 256, 256, 0, st>>>(n_base, keep, pos, score_key, sel_keys, sel_vals, d_count);
+                           int want, const DensifyWs& w, uint32_t* sel_idx, uint32_t* d_count, hipStream_t st) {
+  if (n_base <= 0 || want <= 0) {
+    launch_fill_u32(d_count, 0u, 1, st);
+    return;
+  }
+  const SelRun r = sel_run(n_base, std::min(want, n_base));
+  const unsigned blocks = (unsigned)((n_base + r.run - 1) / r.run);
+  launch_fill_u32(w.sel, 0u, kSelState, st);
+  densify_members(s, a, w, r, gsum, gcnt, w.sel, st);
+  k_densify_digit<1><<<blocks, kSelThreads, 0, st>>>(r, w.keep, w.score_key, w.sel, d_count);
+  k_densify_digit<2><<<blocks, kSelThreads, 0, st>>>(r, w.keep, w.score_key, w.sel, d_count);
+  k_densify_count<<<blocks, kSelThreads, 0, st>>>(r, w.keep, w.score_key, w.sel);
+  k_densify_collect<<<blocks, kSelThreads, 0, st>>>(r, w.keep, w.score_key, w.sel, w.pos);
+  const int per = kRankThreads / kRankLanes;
+  k_densify_rank<<<(r.want + per - 1) / per, kRankThreads, 0, st>>>(r.want, d_count, w.pos, sel_idx);
+}
+
+void launch_densify_pack(const SceneK& s, const DensifyArgs& a, const float* gsum, const int32_t* gcnt, int n_base,
+                         const DensifyWs& w, uint64_t* scan_tmp, uint32_t* sel_keys, uint32_t* sel_vals,
+                         uint32_t* d_count, hipStream_t st) {
+  launch_fill_u32(d_count, 0u, 1, st);
+  if (n_base <= 0) return;
+  densify_members(s, a, w, sel_run(n_base, 0), gsum, gcnt, nullptr, st);
+  scan_u32_to_u64(w.keep, w.pos, n_base, scan_tmp, st);
+  k_densify_pack<<<(n_base + 255) / 256, 256, 0, st>>>(n_base, w.keep, w.pos, w.score_key, sel_keys, sel_vals, d_count);
 }
 
 void launch_densify_spawn(float* mean, float* quat, float* log_scale, float* logit, float* sh, int n_planes_sh,

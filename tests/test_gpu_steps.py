@@ -598,3 +598,31 @@ def test_bake_applies_the_final_offsets(shift):
         np.testing.assert_allclose(g.quat[:, :n].cpu().numpy(), oq, rtol=1e-5, atol=1e-6)
         # G^var rows were not shifted: they hold exactly their final parameters
         np.testing.assert_array_equal(g.mean[:, g.n_base:n].cpu().numpy(), fin.mean[:, g.n_base:])
+
+
+@pytest.mark.parametrize("n,k_max,levels,max_views", [
+    (1, 1, 0, 3), (1023, 16, 0, 3), (1025, 17, 4, 3), (3000, 1000, 1, 3),   # rank groups; ties, all alike
+    (70_001, 5000, 40, 3),       # several runs of Gaussians, the last member among many ties
+    (40_000, 16_384, 0, 3), (40_000, 16_385, 0, 3),  # the most that is selected; one more is sorted
+    (2000, 300, 0, 1),           # fewer rows of codes than views
+])
+def test_densify_parents_at_the_selections_edges(n, k_max, levels, max_views):
+    """The parents of the children, in rank order (score descending, ties by index), against a stable
+    sort of the oracle's members: the children's copied quaternions, bit for bit.  levels > 0:
+    errors of that many values only, so that the last used rank falls among equal scores."""
+    scene, cams, errs, gsum, cnt, k_max, cap, tp, te, gamma = _densify_case(n, n, 3, k_max, k_max + 5, 0.4, 0.1, 0.5)
+    if levels:
+        errs = [np.ceil(e * levels).astype(np.float32) / np.float32(levels) for e in errs]
+    sel, score, _ = oracle.densify_select(scene.mean, cams, errs, gsum, cnt, gamma, tp, te)
+    g = to_gpu(scene, capacity=cap)
+    ctx = make_ctx(cap, cams[:max_views])
+    n_dev = torch.zeros(1, dtype=torch.int32, device="cuda")
+    ctx.densify_append(g, [dev(e) for e in errs], cams, dev(gsum), dev(cnt), gamma, tp, te, k_max, 7, n_dev)
+    ctx.sync()
+    log(f"  |S|={sel.size} of {n}, children {k_max}")
+    if sel.size == 0:
+        assert int(n_dev.item()) == 0
+        return
+    assert int(n_dev.item()) == k_max
+    parents = np.asarray(sel)[np.arange(k_max) % sel.size]
+    np.testing.assert_array_equal(g.quat[:, n:n + k_max].cpu().numpy(), scene.quat[:, parents])
