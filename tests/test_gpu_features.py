@@ -131,3 +131,29 @@ def test_dynamic_mask_degenerate_cases():
     ctx.dynamic_mask(cams, F, flows, 1.0, dev(cls_w), dev(cls_b), fdev, 0, idx, nd)
     ctx.sync()
     assert int(nd.item()) == 0
+
+
+@pytest.mark.parametrize("w,h,channels", [(100, 84, 16), (101, 83, 1), (17, 5, 3), (8, 130, 16), (3, 3, 4), (258, 40, 15)])
+def test_feature_render_on_matrix_cores_at_the_edges(w, h, channels):
+    """The 16x16 sub-tiles accumulate by matrix products of 16 pixels x 16 channels: widths whose rows do
+    and do not start on 16 bytes, images narrower than a sub-tile or a quadrant, few channels, and lists
+    beyond one batch, against the oracle (float64; the tolerance of the colour images)."""
+    scene, cams, _ = synth.multiview_scene(33, n=3000, n_views=2, width=w, height=h, with_grads=False)
+    feat, _, _, _ = synth.identity_setup(34, scene.n, channels=channels)
+    g = to_gpu(scene)
+    fdev = torch.zeros(channels, g.capacity, device="cuda")
+    fdev[:, :scene.n] = dev(feat)
+    log(f"feature render {w}x{h} channels {channels}")
+    ctx = make_ctx(scene.n, cams)
+    ctx.tile = (32, 32)
+    ctx.render_fwd(g, cams, BG)
+    F = ctx.render_features(g, cams, fdev)
+    ctx.sync()
+    for v, c in enumerate(cams):
+        vr = oracle.render_view(scene, c, bg=BG, tile=(32, 32))
+        want = oracle.render_features(vr, c, feat, tile=(32, 32))
+        keep = ~excluded_pixels(vr, c, tile=(32, 32))
+        got = F[v].cpu().numpy()
+        assert np.abs(got).max() > 0.0
+        err = np.abs(got - want)[:, keep].max()
+        assert err <= IMG_TOL, (v, err)
