@@ -279,16 +279,69 @@ __global__ __launch_bounds__(1024) void k_bin_tiles(int tiles, const uint32_t* _
   }
 }
 
+// The keys of 64 rectangles (area, start: the lane's keys and those before them, total: of all).
+__device__ __forceinline__ void place_by_key(const Clip& c, int area, int start, int total, uint32_t val, const Window& W,
+                                             int lane, uint64_t bit, uint64_t lt, uint32_t cap, int* s_own,
+                                             uint64_t* s_mask, uint32_t* s_pos, uint32_t* __restrict__ vals) {
+  const int where = (c.y0 * W.bx + c.x0) | (c.w << 16);
+  int carry = 0;  // 1 + the lane that owns the last key of the keys before
+  for (int k0 = 0; k0 < total; k0 += 64) {
+    // 1 + lane at the first key of every Gaussian that starts among these 64, then a max-scan
+    const int at = start - k0;
+    const bool here = area > 0 && at >= 0 && at < 64;
+    s_own[lane] = 0;
+    wave_sync();
+    if (here) s_own[at] = lane + 1;
+    wave_sync();
+    int own = s_own[lane];
+    own = max(wave_scan_max(own), carry);
+    carry = __builtin_amdgcn_readlane(own, 63);
+    const int k = k0 + lane, src = own - 1;
+    const int wh = __shfl(where, src, 64);
+    const int i = k - __shfl(start, src, 64);
+    const uint32_t vv = (uint32_t)__shfl((int)val, src, 64);
+    const bool live = k < total;
+    const int w = wh >> 16;
+    // i / w by a float reciprocal, corrected to the exact quotient (i < 2^20)
+    int q = (int)((float)i * __builtin_amdgcn_rcpf((float)w));
+    int x = i - q * w;
+    if (x < 0) {
+      q--;
+      x += w;
+    } else if (x >= w) {
+      q++;
+      x -= w;
+    }
+    const int t = live ? (wh & 0xFFFF) + q * W.bx + x : 0;
+    if (live) atomicOr(reinterpret_cast<unsigned long long*>(&s_mask[t]), (unsigned long long)bit);
+    wave_sync();
+    const uint64_t m = s_mask[t];
+    const uint32_t pos = s_pos[t];
+    const uint32_t o = pos + (uint32_t)__popcll(m & lt);
+    if (live && o < cap) vals[o] = vv;
+    wave_sync();
+    if (live && (m >> lane) == 1ull) {  // the tile's last key among the 64
+      s_pos[t] = min(pos + (uint32_t)__popcll(m), cap);
+      s_mask[t] = 0ull;
+    }
+    wave_sync();
+  }
+}
+
 // A (view, window, chunk) per wave, 64 Gaussians at a time, either
 //   by key: the group's keys spread evenly over the lanes, 64 at a time in Gaussian order (lane l
 //     finds the Gaussian of its key by a max-scan over the lanes where a Gaussian's keys start); a
 //     lane mask per tile in LDS ranks the keys that meet in a tile;
-//   by tile (more than kDenseKeys keys per tile of the group's common box): the wave walks the
-//     box, the tile's lanes store their run together, and a row's positions stay in registers.
-//     By key, 64 neighbouring keys of a wide Gaussian are stored to 64 lines: 2e8 keys of Gaussians
-//     over about 50 tiles each took 2.34 ms by key alone, 1.06 / 0.85 / 0.78 ms with the line
-//     drawn at 8 / 5 / 3.
+//   by tile (more than kDenseKeys keys per tile of the group's common box), with the next seven groups:
+//     the wave walks the box, its lanes holding eight rectangles each, collects a tile's run in LDS and
+//     stores it in one piece; a row's positions stay in registers.  By key, 64 neighbouring keys of a
+//     wide Gaussian are stored to 64 lines, and a store of the few lanes of one group costs what a
+//     full one does: 2e8 keys of Gaussians over about 50 tiles each took 2.34 ms by key alone, 0.77 ms
+//     by tile with one group at a time, 0.51 so.
+//     At 2 keys the call gains 8 us, but groups just past the line that are followed by sparse ones cost
+//     20 views of 200k small Gaussians 154 us instead of 98.
 constexpr int kDenseKeys = 3;
+constexpr int kGroups = 8;  // of 64 Gaussians
 __global__ __launch_bounds__(64) void k_bin_scatter(int n, int nv, int wins, int chunk, int chunks,
                                                     BinViews bv, const uint32_t* __restrict__ gid,
                                                     const uint2* __restrict__ rect_s, const uint32_t* __restrict__ hist,
@@ -296,6 +349,7 @@ __global__ __launch_bounds__(64) void k_bin_scatter(int n, int nv, int wins, int
                                                     uint32_t* __restrict__ vals) {
   __shared__ uint64_t s_mask[kScatterTiles];
   __shared__ int s_own[64];
+  __shared__ uint32_t s_run[64 * kGroups];   // a tile's run
   __shared__ uint32_t s_pos[kScatterTiles];  // next position of each tile's list (the key budget at most)
   Piece pc;
   if (!piece_of(chunks, nv, wins, pc)) return;
@@ -339,75 +393,74 @@ __global__ __launch_bounds__(64) void k_bin_scatter(int n, int nv, int wins, int
     const int total = __builtin_amdgcn_readlane(incl, 63);
     if (total == 0) continue;
     if (total > 4 * 64 && fits) {
-      const int bx0 = wave_min(area ? c.x0 : kScatterTiles), bx1 = wave_max(area ? c.x0 + c.w : 0);
-      const int by0 = wave_min(area ? c.y0 : kScatterTiles), by1 = wave_max(area ? c.y0 + c.h : 0);
-      if (total > kDenseKeys * (bx1 - bx0) * (by1 - by0)) {
-        for (int y = by0; y < by1; y++) {
-          uint32_t width = (uint32_t)(y - c.y0) < (uint32_t)c.h ? (uint32_t)c.w : 0u;  // of the lane's rectangle here
-          __asm__ volatile("" : "+v"(width));  // one compare per tile below, not two
-          for (int xb = bx0; xb < bx1; xb += 64) {
-            const int nx = min(64, bx1 - xb);
+      int x0 = area ? c.x0 : kScatterTiles, x1 = area ? c.x0 + c.w : 0;
+      int y0 = area ? c.y0 : kScatterTiles, y1 = area ? c.y0 + c.h : 0;
+      if (total > kDenseKeys * (wave_max(x1) - wave_min(x0)) * (wave_max(y1) - wave_min(y0))) {
+        // these 64 and the next 64 (kGroups - 1), whatever they are
+        Clip cs[kGroups];
+        uint32_t vs[kGroups];
+        cs[0] = c;
+        vs[0] = val;
+#pragma unroll
+        for (int i = 1; i < kGroups; i++) {
+          const int e = b + 64 * i + lane;
+          cs[i] = clip_rect(e < p1 ? rect_s[row + e] : make_uint2(0u, 0u), W);
+          vs[i] = e < p1 ? (uint32_t)row + gid[row + e] : 0u;
+          if (cs[i].w > 0) {
+            x0 = min(x0, cs[i].x0);
+            x1 = max(x1, cs[i].x0 + cs[i].w);
+            y0 = min(y0, cs[i].y0);
+            y1 = max(y1, cs[i].y0 + cs[i].h);
+          }
+        }
+        x0 = wave_min(x0);
+        x1 = wave_max(x1);
+        y0 = wave_min(y0);
+        y1 = wave_max(y1);
+        for (int y = y0; y < y1; y++) {
+          uint32_t width[kGroups];  // of the lane's rectangles in this row
+#pragma unroll
+          for (int i = 0; i < kGroups; i++) {
+            width[i] = (uint32_t)(y - cs[i].y0) < (uint32_t)cs[i].h ? (uint32_t)cs[i].w : 0u;
+            __asm__ volatile("" : "+v"(width[i]));  // one compare per tile below, not two
+          }
+          for (int xb = x0; xb < x1; xb += 64) {
+            const int nx = min(64, x1 - xb);
             uint32_t* prow = &s_pos[y * W.bx + xb];
             int posv = lane < nx ? (int)prow[lane] : 0;  // lane i: the position of tile xb + i
             for (int x = 0; x < nx; x++) {
-              const bool in = (uint32_t)(xb + x - c.x0) < width;
-              const uint64_t m = __ballot(in);
+              int cnt = 0;
+#pragma unroll
+              for (int i = 0; i < kGroups; i++) {
+                const bool in = (uint32_t)(xb + x - cs[i].x0) < width[i];
+                const uint64_t m = __ballot(in);
+                if (m != 0) {
+                  if (in)
+                    s_run[__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                                    __builtin_amdgcn_mbcnt_lo((uint32_t)m, (uint32_t)cnt))] = vs[i];
+                  cnt += (int)__popcll(m);
+                }
+              }
+              if (cnt == 0) continue;
+              wave_sync();
               const int pos = __builtin_amdgcn_readlane(posv, x);
-              if (in)
-                vals[__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
-                                               __builtin_amdgcn_mbcnt_lo((uint32_t)m, (uint32_t)pos))] = val;
-              if (lane == x) posv = pos + (int)__popcll(m);
+              for (int k = lane; k < cnt; k += 64) vals[(uint32_t)pos + (uint32_t)k] = s_run[k];
+              wave_sync();
+              if (lane == x) posv = pos + cnt;
             }
             if (lane < nx) prow[lane] = (uint32_t)posv;
           }
         }
         wave_sync();
+        b += 64 * (kGroups - 1);
+        if (b + 64 + lane < p1) {
+          r_next = rect_s[row + b + 64 + lane];
+          g_next = gid[row + b + 64 + lane];
+        }
         continue;
       }
     }
-    const int where = (c.y0 * W.bx + c.x0) | (c.w << 16);
-    int carry = 0;  // 1 + the lane that owns the last key of the keys before
-    for (int k0 = 0; k0 < total; k0 += 64) {
-      // 1 + lane at the first key of every Gaussian that starts among these 64, then a max-scan
-      const int at = start - k0;
-      const bool here = area > 0 && at >= 0 && at < 64;
-      s_own[lane] = 0;
-      wave_sync();
-      if (here) s_own[at] = lane + 1;
-      wave_sync();
-      int own = s_own[lane];
-      own = max(wave_scan_max(own), carry);
-      carry = __builtin_amdgcn_readlane(own, 63);
-      const int k = k0 + lane, src = own - 1;
-      const int wh = __shfl(where, src, 64);
-      const int i = k - __shfl(start, src, 64);
-      const uint32_t vv = (uint32_t)__shfl((int)val, src, 64);
-      const bool live = k < total;
-      const int w = wh >> 16;
-      // i / w by a float reciprocal, corrected to the exact quotient (i < 2^20)
-      int q = (int)((float)i * __builtin_amdgcn_rcpf((float)w));
-      int x = i - q * w;
-      if (x < 0) {
-        q--;
-        x += w;
-      } else if (x >= w) {
-        q++;
-        x -= w;
-      }
-      const int t = live ? (wh & 0xFFFF) + q * W.bx + x : 0;
-      if (live) atomicOr(reinterpret_cast<unsigned long long*>(&s_mask[t]), (unsigned long long)bit);
-      wave_sync();
-      const uint64_t m = s_mask[t];
-      const uint32_t pos = s_pos[t];
-      const uint32_t o = pos + (uint32_t)__popcll(m & lt);
-      if (live && o < cap) vals[o] = vv;
-      wave_sync();
-      if (live && (m >> lane) == 1ull) {  // the tile's last key among the 64
-        s_pos[t] = min(pos + (uint32_t)__popcll(m), cap);
-        s_mask[t] = 0ull;
-      }
-      wave_sync();
-    }
+    place_by_key(c, area, start, total, val, W, lane, bit, lt, cap, s_own, s_mask, s_pos, vals);
   }
 }
 

@@ -227,6 +227,34 @@ def test_tile_lists_at_group_chunk_and_window_edges(n, log_scale, tile):
         np.testing.assert_array_equal(gr, r)
 
 
+@pytest.mark.parametrize("n,mix", [(28_001, False), (32_805, False), (32_805, True)])
+def test_tile_lists_of_wide_gaussians_in_long_chunks(n, mix):
+    """32 views, so that a chunk holds seven or eight groups of 64: wide footprints, placed by tile eight
+    groups at a time with the last ones short or missing, and (mix) wide ones among narrow ones in
+    depth order, so that such a piece begins among wide and ends among narrow ones.  Lists of the
+    first and the last view bit-exact against the oracle."""
+    scene, _ = synth.frustum_scene(7, n, 0, -4.0, 0.3)
+    z = scene.mean[2]
+    wide = (np.sin(z * 40.0) > 0.0) if mix else np.ones(n, bool)
+    scene.log_scale[:, wide] += 3.5
+    cams = [synth.make_camera(np.eye(3), (0.0, 0.0, 0.0), 700 - 3 * v, 500 - v) for v in range(32)]
+    log(f"[lists] n {n} mix {mix}")
+    g = to_gpu(scene)
+    ctx = make_ctx(scene.n, cams, keys_per_gaussian=90)
+    ctx.tile = (64, 64)
+    ctx.render_fwd(g, cams, BG)
+    ctx.sync()
+    for v in (0, 31):
+        p = oracle.project(scene, cams[v], (64, 64))
+        k, val, r = oracle.keys(p, cams[v], (64, 64))
+        TX, TY = oracle.tiles_of(cams[v], (64, 64))
+        log(f"  view {v}: {k.size} keys of {n} Gaussians on {TX * TY} tiles")
+        gk, gv, gr = ctx.debug_keys(v, k.size + 16, TX * TY)
+        np.testing.assert_array_equal(gk, k)
+        np.testing.assert_array_equal(gv, val)
+        np.testing.assert_array_equal(gr, r)
+
+
 @pytest.mark.parametrize("make", ["opaque", "ragged"])
 def test_blend_by_quadrant_matches_blend_by_subtile(make):
     """A call of few 16x16 sub-tiles is blended by one wave per 8x8 quadrant, one of many by one wave
