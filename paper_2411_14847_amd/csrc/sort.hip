@@ -408,8 +408,8 @@ __global__ __launch_bounds__(kDepthLdsThreads) void k_depth_lds(int n, const uin
 // Larger views: least-significant-digit radix sort of every view by itself (blockIdx.y), three
 // 9-bit digits of the keys' low 27 bits.  A pass is an upsweep (each block's digit counts) and a
 // scatter, whose blocks add up the counts of the blocks before them by themselves.
-constexpr int kDepthIt = 16;                           // pairs per thread and batch
-constexpr int kDepthBatch = kSortThreads * kDepthIt;     // 4,096
+constexpr int kDepthIt = 16;  // keys per thread of the upsweep's loads
+constexpr int kDepthBatch = kSortThreads * kDepthIt;  // 4,096 pairs
 constexpr int kDepthBlocks = 64;                       // blocks per view at most
 
 // View v and block b of it that a workgroup takes, and the block's part [lo, hi) of the view.  Each
@@ -451,60 +451,89 @@ __global__ __launch_bounds__(kSortThreads) void k_depth_upsweep(int n, int nv, i
     hist[((int64_t)v * blocks + b) * kDepthR + d] = s_h[0][d] + s_h[1][d] + s_h[2][d] + s_h[3][d];
 }
 
-// FIRST: the values are the positions themselves.  LAST: the keys are written only if the view has
+// NT threads.  FIRST: the values are the positions themselves.  LAST: the keys are written only if the view has
 // far depths (a fourth digit follows).
-template <bool FIRST, bool LAST>
-__global__ __launch_bounds__(kSortThreads) void k_depth_scatter(int n, int nv, int blocks, int shift,
+template <bool FIRST, bool LAST, int NT>
+__global__ __launch_bounds__(NT) void k_depth_scatter(int n, int nv, int blocks, int shift,
                                                                 const uint32_t* __restrict__ kin,
                                                                 const uint32_t* __restrict__ vin,
                                                                 uint32_t* __restrict__ kout, uint32_t* __restrict__ vout,
                                                                 const uint32_t* __restrict__ hist,
                                                                 const uint32_t* __restrict__ far) {
-  constexpr int D = kDepthR / kSortThreads;  // digits owned per thread
-  constexpr int kRun = kDepthIt * 64;        // consecutive pairs ranked by one wave per batch
-  __shared__ uint32_t s_base[kDepthR], s_boff[kDepthR], s_tmp[4];
-  __shared__ uint16_t s_wc[4][kDepthR];
-  __shared__ uint64_t s_mask[4][kDepthR];
-  for (int i = threadIdx.x; i < 4 * kDepthR; i += kSortThreads) (&s_mask[0][0])[i] = 0;
+  constexpr int NW = NT / 64, IT = kDepthBatch / NT;  // waves, pairs per thread and batch
+  constexpr int OWN = NT < kDepthR ? NT : kDepthR;    // threads that own digits
+  constexpr int D = kDepthR / OWN;                    // digits owned per thread
+  constexpr int kRun = IT * 64;                       // consecutive pairs ranked by one wave per batch
+  __shared__ uint32_t s_base[kDepthR], s_boff[kDepthR], s_tmp[OWN / 64];
+  __shared__ uint16_t s_wc[NW][kDepthR];
+  __shared__ uint64_t s_mask[NW][kDepthR];
+  for (int i = threadIdx.x; i < NW * kDepthR; i += NT) (&s_mask[0][0])[i] = 0;
   __shared__ uint32_t s_x[kDepthBatch];  // the batch in digit order: its keys, then its values
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   int v, blk, lo, hi;
   if (!depth_piece(n, nv, blocks, v, blk, lo, hi) || lo >= hi) return;  // uniform over the workgroup
   const int64_t row = (int64_t)v * n;
   const bool write_keys = !LAST || far[v] != 0;
-  {  // first position of each digit: the digit's counts in the blocks before, after all smaller digits
-    const uint2* __restrict__ h = reinterpret_cast<const uint2*>(hist + (int64_t)v * blocks * kDepthR) + tid;
-    static_assert(D == 2, "two digits per thread");
-    uint2 before = make_uint2(0u, 0u), total = make_uint2(0u, 0u);
-    constexpr int kAhead = 8;
-    for (int b = 0; b < blocks; b += kAhead) {
-      uint2 x[kAhead];
+  // exclusive scan over the digits, thread t < OWN with the digits t D, t D + 1, ...; whole workgroup
+  auto digit_scan = [&](const uint32_t (&x)[D]) {
+    uint32_t own = 0;
+#pragma unroll
+    for (int i = 0; i < D; i++) own += x[i];
+    const uint32_t inc = wave_incl_scan(own);
+    if (lane == 63 && tid < OWN) s_tmp[wave] = inc;
+    __syncthreads();
+    uint32_t run = inc - own;
+#pragma unroll
+    for (int w = 0; w < OWN / 64; w++) run += w < wave ? s_tmp[w] : 0u;
+    __syncthreads();
+    return run;
+  };
+  {  // first position of each digit: the digit's counts in the blocks before, after all smaller digits;
+     // where threads outnumber the digits, they read the blocks' counts in turn
+    constexpr int G = NT / OWN, kAhead = D == 2 ? 8 : 16;
+    const int o = tid % OWN, gr = tid / OWN;
+    const uint32_t* __restrict__ h = hist + (int64_t)v * blocks * kDepthR + o * D;
+    uint32_t before[D], total[D];
+#pragma unroll
+    for (int i = 0; i < D; i++) before[i] = total[i] = 0u;
+    for (int b = gr; b < blocks; b += G * kAhead) {
+      typedef uint32_t Digits __attribute__((ext_vector_type(D)));  // a thread's digits, one load
+      Digits x[kAhead];
 #pragma unroll
       for (int u = 0; u < kAhead; u++)
-        x[u] = b + u < blocks ? h[(int64_t)(b + u) * kSortThreads] : make_uint2(0u, 0u);
+        x[u] = b + u * G < blocks ? *reinterpret_cast<const Digits*>(h + (int64_t)(b + u * G) * kDepthR) : Digits(0u);
 #pragma unroll
-      for (int u = 0; u < kAhead; u++) {
-        total.x += x[u].x;
-        total.y += x[u].y;
-        if (b + u < blk) {
-          before.x += x[u].x;
-          before.y += x[u].y;
+      for (int u = 0; u < kAhead; u++)
+#pragma unroll
+        for (int i = 0; i < D; i++) {
+          total[i] += x[u][i];
+          before[i] += b + u * G < blk ? x[u][i] : 0u;
         }
+    }
+    if (G > 1) {
+      static_assert(G <= 2, "one other group's sums");
+      if (gr == 1) s_base[o] = total[0], s_boff[o] = before[0];
+      __syncthreads();
+      if (gr == 0) total[0] += s_base[o], before[0] += s_boff[o];
+      __syncthreads();
+    }
+    uint32_t run = digit_scan(total);
+    if (gr == 0) {
+#pragma unroll
+      for (int i = 0; i < D; i++) {
+        s_base[o * D + i] = run + before[i];
+        run += total[i];
       }
     }
-    const uint32_t tv[D] = {total.x, total.y};
-    const uint32_t run = block_excl_scan_digits<D>(tv, s_tmp, nullptr);
-    s_base[tid * 2] = run + before.x;
-    s_base[tid * 2 + 1] = run + total.x + before.y;
   }
   const uint64_t lt = lanemask_lt();
   for (int batch = lo; batch < hi; batch += kDepthBatch) {
     const int nb = min(kDepthBatch, hi - batch);
     const int wbase = batch + wave * kRun;
     for (int d = lane; d < kDepthR; d += 64) s_wc[wave][d] = 0;
-    uint32_t key[kDepthIt], val[kDepthIt], rank[kDepthIt];
+    uint32_t key[IT], val[IT], rank[IT];
 #pragma unroll
-    for (int s = 0; s < kDepthIt; s++) {
+    for (int s = 0; s < IT; s++) {
       const int i = wbase + s * 64 + lane;
       if (i < hi) {
         key[s] = kin[row + i];
@@ -513,7 +542,7 @@ __global__ __launch_bounds__(kSortThreads) void k_depth_scatter(int n, int nv, i
     }
     wave_lds_sync();
 #pragma unroll
-    for (int s = 0; s < kDepthIt; s++) {
+    for (int s = 0; s < IT; s++) {
       const bool valid = wbase + s * 64 + lane < hi;
       const uint32_t d = valid ? (key[s] >> shift) & (kDepthR - 1) : 0u;
       rank[s] = wave_rank(s_mask[wave], s_wc[wave], d, valid, lane, lt);
@@ -521,37 +550,43 @@ __global__ __launch_bounds__(kSortThreads) void k_depth_scatter(int n, int nv, i
     __syncthreads();
     uint32_t c[D];
 #pragma unroll
-    for (int i = 0; i < D; i++) {
-      uint32_t run = 0;
-#pragma unroll
-      for (int w = 0; w < 4; w++) {
-        const uint32_t x = s_wc[w][tid * D + i];
-        s_wc[w][tid * D + i] = (uint16_t)run;
-        run += x;
-      }
-      c[i] = run;
-    }
-    {
-      uint32_t run = block_excl_scan_digits<D>(c, s_tmp, nullptr);
+    for (int i = 0; i < D; i++) c[i] = 0u;
+    if (tid < OWN) {
 #pragma unroll
       for (int i = 0; i < D; i++) {
-        s_boff[tid * D + i] = run;
-        run += c[i];
+        uint32_t run = 0;
+#pragma unroll
+        for (int w = 0; w < NW; w++) {
+          const uint32_t x = s_wc[w][tid * D + i];
+          s_wc[w][tid * D + i] = (uint16_t)run;
+          run += x;
+        }
+        c[i] = run;
+      }
+    }
+    {
+      uint32_t run = digit_scan(c);
+      if (tid < OWN) {
+#pragma unroll
+        for (int i = 0; i < D; i++) {
+          s_boff[tid * D + i] = run;
+          run += c[i];
+        }
       }
     }
     __syncthreads();
 #pragma unroll
-    for (int s = 0; s < kDepthIt; s++)
+    for (int s = 0; s < IT; s++)
       if (wbase + s * 64 + lane < hi) {
         const uint32_t d = (key[s] >> shift) & (kDepthR - 1);
         rank[s] += s_boff[d] + s_wc[wave][d];  // position in the ordered batch
         s_x[rank[s]] = key[s];
       }
     __syncthreads();
-    uint32_t to[kDepthIt];  // where the batch's elements tid, tid + 256, ... go
+    uint32_t to[IT];  // where the batch's elements tid, tid + NT, ... go
 #pragma unroll
-    for (int s = 0; s < kDepthIt; s++) {
-      const int j = s * kSortThreads + tid;
+    for (int s = 0; s < IT; s++) {
+      const int j = s * NT + tid;
       if (j < nb) {
         const uint32_t k = s_x[j];
         const uint32_t d = (k >> shift) & (kDepthR - 1);
@@ -561,18 +596,20 @@ __global__ __launch_bounds__(kSortThreads) void k_depth_scatter(int n, int nv, i
     }
     __syncthreads();
 #pragma unroll
-    for (int s = 0; s < kDepthIt; s++)
+    for (int s = 0; s < IT; s++)
       if (wbase + s * 64 + lane < hi) s_x[rank[s]] = val[s];
     __syncthreads();
 #pragma unroll
-    for (int s = 0; s < kDepthIt; s++) {
-      const int j = s * kSortThreads + tid;
+    for (int s = 0; s < IT; s++) {
+      const int j = s * NT + tid;
       if (j < nb && to[s] < (uint32_t)n) vout[row + to[s]] = s_x[j];
     }
     if (batch + kDepthBatch >= hi) break;
     __syncthreads();
+    if (tid < OWN) {
 #pragma unroll
-    for (int i = 0; i < D; i++) s_base[tid * D + i] += c[i];
+      for (int i = 0; i < D; i++) s_base[tid * D + i] += c[i];
+    }
     __syncthreads();
   }
 }
@@ -757,6 +794,17 @@ int radix_sort_u32(uint32_t* keys[2], uint32_t* vals[2], const uint32_t* d_count
 
 size_t depth_hist_elems(int max_views) { return (size_t)max_views * kDepthBlocks * kDepthR; }
 
+template <int NT>
+static void depth_passes(int n, int nv, int blocks, unsigned grid, uint32_t* const keys[2], uint32_t* const vals[2],
+                         uint32_t* hist, uint32_t* far, hipStream_t st) {
+  k_depth_upsweep<<<grid, kSortThreads, 0, st>>>(n, nv, blocks, 0, keys[0], hist);
+  k_depth_scatter<true, false, NT><<<grid, NT, 0, st>>>(n, nv, blocks, 0, keys[0], nullptr, keys[1], vals[1], hist, far);
+  k_depth_upsweep<<<grid, kSortThreads, 0, st>>>(n, nv, blocks, 9, keys[1], hist);
+  k_depth_scatter<false, false, NT><<<grid, NT, 0, st>>>(n, nv, blocks, 9, keys[1], vals[1], keys[0], vals[0], hist, far);
+  k_depth_upsweep<<<grid, kSortThreads, 0, st>>>(n, nv, blocks, 18, keys[0], hist);
+  k_depth_scatter<false, true, NT><<<grid, NT, 0, st>>>(n, nv, blocks, 18, keys[0], vals[0], keys[1], vals[1], hist, far);
+}
+
 void launch_depth_sort(int n, int nv, uint32_t* const keys[2], uint32_t* const vals[2], uint32_t* hist, uint32_t* far,
                        hipStream_t st) {
   if (n <= 0) return;
@@ -775,15 +823,13 @@ void launch_depth_sort(int n, int nv, uint32_t* const keys[2], uint32_t* const v
   else {
     const int blocks = std::min(kDepthBlocks, (n + kDepthBatch - 1) / kDepthBatch);
     const unsigned grid = (unsigned)((blocks * nv + kNumXcd - 1) / kNumXcd * kNumXcd);
-    k_depth_upsweep<<<grid, kSortThreads, 0, st>>>(n, nv, blocks, 0, keys[0], hist);
-    k_depth_scatter<true, false><<<grid, kSortThreads, 0, st>>>(n, nv, blocks, 0, keys[0], nullptr, keys[1], vals[1], hist,
-                                                                far);
-    k_depth_upsweep<<<grid, kSortThreads, 0, st>>>(n, nv, blocks, 9, keys[1], hist);
-    k_depth_scatter<false, false><<<grid, kSortThreads, 0, st>>>(n, nv, blocks, 9, keys[1], vals[1], keys[0], vals[0], hist,
-                                                                 far);
-    k_depth_upsweep<<<grid, kSortThreads, 0, st>>>(n, nv, blocks, 18, keys[0], hist);
-    k_depth_scatter<false, true><<<grid, kSortThreads, 0, st>>>(n, nv, blocks, 18, keys[0], vals[0], keys[1], vals[1], hist,
-                                                                far);
+    // blocks of 1,024 threads, four pairs each, while every block has a CU to itself: the ranks are a chain
+    // per wave, sixteen pairs long with 256 threads.  us of the sort, 256 -> 1,024 threads: one view of
+    // 200k 65 -> 51, four (196 blocks) 66 -> 54, of 1M (256) 155 -> 129; eight of 200k (392) 71, 80
+    if (blocks * nv <= 256)
+      depth_passes<1024>(n, nv, blocks, grid, keys, vals, hist, far, st);
+    else
+      depth_passes<256>(n, nv, blocks, grid, keys, vals, hist, far, st);
     k_depth_far<<<nv, 1024, 0, st>>>(n, keys[1], vals[1], vals[0], far);
   }
 }
