@@ -158,11 +158,11 @@ dass_status allocate(dass_ctx ctx, const dass_limits& l) {
   ALLOC(w.vals, w.cap_keys > 0 ? w.cap_keys : 1);
   ALLOC(w.ranges, w.cap_tiles > 0 ? w.cap_tiles : 1);
   ALLOC(w.tile_tot, w.cap_tiles + 4);
-  w.cap_bin = bin_hist_elems(w.cap_tiles);
+  w.cap_bin = bin_hist_elems(w.cap_tiles, l.max_gaussians);
   ALLOC(w.bin_hist, w.cap_bin);
   ALLOC(w.depth_hist, depth_hist_elems(l.max_views));
   ALLOC(w.far, DASS_MAX_VIEWS);
-  ALLOC(w.hist, 2048 * 1024 + 2048);  // [radix][max sort blocks] counts + radix digit totals
+  ALLOC(w.hist, 2048 * 512 + 2048);  // [radix][max sort blocks] counts + radix digit totals
   ALLOC(w.scan_tmp, scan_tmp_elems(vn));
   ALLOC(w.counters, 16);
   ALLOC(w.pairs, 2);
@@ -1070,8 +1070,8 @@ dass_status densify_append(dass_ctx ctx, dass_gaussians* g, const float* const* 
     uint32_t* k32[2] = {ws.dkey[0], ws.dkey[1]};
     launch_densify_pack(sc, a, gradnorm_sum, grad_count, g->n_base, w, ws.scan_tmp, k32[0], ws.dval[0], ws.counters + 1,
                         st);
-    parents = ws.dval[radix_sort_u32(k32, ws.dval, ws.counters + 1, g->n_base, 0, 32, ws.hist,
-                                     sort_blocks_for(g->n_base), st)];
+    parents = ws.dval[radix_sort_u32(k32, ws.dval, ws.counters + 1, g->n_base, ws.hist, sort_blocks_for(g->n_base),
+                                     st)];
   }
   const int K = (g->sh_degree + 1) * (g->sh_degree + 1);
   launch_densify_spawn(g->mean, g->quat, g->log_scale, g->opacity_logit, g->sh, 3 * K, g->capacity, g->n,
@@ -1235,7 +1235,7 @@ dass_status dass_autotune_tile(dass_ctx ctx, const dass_gaussians* g, const dass
   if (e1) (void)hipEventDestroy(e1);
   // the first candidate (in the caller's order of preference) within 1% of the fastest, so that
   // timing noise between near-equal sizes does not flip the choice from run to run (at 2% a
-  // tile size whose key sort takes a second pass was chosen while 1.6% behind the fastest)
+  // size 1.6% behind the fastest was once chosen)
   if (s == DASS_OK && *best >= 0) {
     for (int c = 0; c < n_candidates; c++)
       if (ms[c] >= 0.f && ms[c] <= 1.01f * best_ms) {

@@ -26,13 +26,10 @@ namespace {
 
 // Tiles a wave counts or scatters at once; a view's tiles beyond this are taken window by window.
 // The count's windows only have to fit its array.  The scatter is bound by latency, so by the waves
-// per CU: 256 tiles (3.3 KB of LDS per wave) against 1,024 take 0.100 against 0.149 ms for the
+// per CU: 256 tiles (5.3 KB of LDS per wave) against 1,024 take 0.100 against 0.149 ms for the
 // 1.5e7 keys of 20 views of 200k Gaussians, 0.89 against 1.37 ms for 2e8 keys of wide Gaussians.
 constexpr int kWinTiles = 1024;
-#ifndef WT
-#define WT 256
-#endif
-constexpr int kScatterTiles = WT;
+constexpr int kScatterTiles = 256;
 // ((bx + 1) | 1)(by + 1) for bx by <= kWinTiles: at most bx by + bx + 2 by + 2
 constexpr int kDiffCells = 3 * kWinTiles + 8;
 
@@ -471,7 +468,10 @@ int windows_of(int TX, int TY, int most) {
 
 }  // namespace
 
-int64_t bin_hist_elems(int64_t max_tiles) { return 128 * max_tiles + (int64_t(1) << 22); }
+// 128 chunks per tile and up to 16 MB more, as far as chunks of 64 Gaussians need it.
+int64_t bin_hist_elems(int64_t max_tiles, int64_t max_gaussians) {
+  return 128 * max_tiles + std::min(int64_t(1) << 22, max_tiles * (max_gaussians / 64 + 1));
+}
 
 void launch_binning(int n, int nv, const CamsK& cams, int64_t total_tiles, Workspace& ws, hipStream_t st) {
   if (total_tiles == 0) return;

@@ -243,12 +243,11 @@ void launch_debug_projection(const SceneK& s, const CamsK& cams, int view, doubl
 // Exclusive scan of n uint32 values into uint64 out[0..n], out[n] = total.
 void scan_u32_to_u64(const uint32_t* in, uint64_t* out, int64_t n, uint64_t* tmp, hipStream_t st);
 size_t scan_tmp_elems(int64_t n);
-// LSD radix sort of (key, value) pairs on bits [begin_bit, end_bit); the element count is read
-// from device memory (*d_count) and must not exceed max_count.  Keys and values ping-pong
-// between buffer 0 and 1; returns the index of the buffer holding the result.
-int radix_sort_u32(uint32_t* keys[2], uint32_t* vals[2], const uint32_t* d_count, int64_t max_count,
-                   int begin_bit, int end_bit, uint32_t* hist, int blocks, hipStream_t st,
-                   int digit_cap = 11);
+// LSD radix sort of (key, value) pairs; the element count is read from device memory (*d_count) and
+// must not exceed max_count.  Keys and values ping-pong between buffer 0 and 1; returns the index
+// of the buffer holding the result.
+int radix_sort_u32(uint32_t* keys[2], uint32_t* vals[2], const uint32_t* d_count, int64_t max_count, uint32_t* hist,
+                   int blocks, hipStream_t st);
 int sort_blocks_for(int64_t max_count);
 // Depth keys: float32 bits of a visible Gaussian's depth less those of the near plane, or
 // kDepthInvisible.
@@ -261,7 +260,7 @@ void launch_depth_sort(int n, int nv, uint32_t* const keys[2], uint32_t* const v
                        hipStream_t st);
 
 // binning.hip
-int64_t bin_hist_elems(int64_t max_tiles);
+int64_t bin_hist_elems(int64_t max_tiles, int64_t max_gaussians);
 // tile lists (ws.vals, ws.ranges) from the depth order (ws.gid_s) and the rectangles (ws.rect_u)
 void launch_binning(int n, int nv, const CamsK& cams, int64_t total_tiles, Workspace& ws, hipStream_t st);
 

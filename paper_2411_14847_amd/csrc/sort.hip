@@ -1,14 +1,14 @@
-// Prefix scan and LSD radix sort for wave64 (gfx950).
+// Prefix scan and the two sorts for wave64 (gfx950): the views' depth order (below), and a radix sort
+// of one list of 32-bit keys, the densification's ranking of all members.
 //
-// Radix sort: reduce-then-scan with a fixed grid, so that the element count can stay on the
-// device (no host round trip inside a render; the launch sequence is graph-capturable).
-// Each pass over a digit of 8 to 11 bits is
+// The radix sort is reduce-then-scan with a fixed grid, so that the element count can stay on the
+// device (no host round trip; the launch sequence is graph-capturable).  Each of three passes over
+// an 11-bit digit is
 //   (1) upsweep: every block histograms its contiguous chunk into LDS (per-wave
 //       sub-histograms to spread LDS atomics), written digit-major to global memory;
 //   (2) scan: one workgroup per digit turns the [radix][blocks] counts into global offsets;
-//   (3) scatter: every block re-reads its chunk in batches of 2048 pairs (4096 for 9- and
-//       10-bit digits), ranks them stably
-//       with wave ballots (8-11 ballots give each lane the mask of lanes holding the same
+//   (3) scatter: every block re-reads its chunk in batches of 4,096 pairs, ranks them stably
+//       with wave ballots (11 ballots give each lane the mask of lanes holding the same
 //       digit; each wave ranks its own quarter of the batch), orders the batch by digit in
 //       LDS and writes each digit's run contiguously.
 // A pass never depends on forward progress between workgroups.
@@ -22,10 +22,7 @@ namespace {
 constexpr int kSortThreads = 256;
 constexpr int kSortItems = 8;                      // items per thread per batch
 constexpr int kBatch = kSortThreads * kSortItems;  // 2048
-constexpr int kMaxRadixBits = 11;  // 32-bit keys; 64-bit keys use at most 10 (LDS per block)
-constexpr int kMaxRadix = 1 << kMaxRadixBits;
-// at most 512 blocks: the 15.4M 10-bit tile keys of the 20-view, 200k-Gaussian benchmark sort in
-// 0.159 ms with 512 (about 30k keys per block), 0.168 with 1024 and 0.194 with 256
+constexpr int kRadixBits = 11, kRadix = 1 << kRadixBits;
 constexpr int kMaxSortBlocks = 512;
 
 __device__ __forceinline__ uint64_t lanemask_lt() {
@@ -72,10 +69,7 @@ __device__ __forceinline__ uint32_t block_excl_scan256(uint32_t x, uint32_t* s_w
   return base + inc - x;
 }
 
-template <int RB, typename K>
-__device__ __forceinline__ uint32_t digit_of(K k, int shift) {
-  return (uint32_t)(k >> shift) & ((1u << RB) - 1);
-}
+__device__ __forceinline__ uint32_t digit_of(uint32_t k, int shift) { return (k >> shift) & (kRadix - 1u); }
 
 __device__ __forceinline__ void chunk_of(uint32_t count, int blocks, uint32_t& lo, uint32_t& hi) {
   const uint32_t chunk = (uint32_t)(((uint64_t)count + blocks - 1) / blocks);
@@ -85,10 +79,10 @@ __device__ __forceinline__ void chunk_of(uint32_t count, int blocks, uint32_t& l
   hi = (uint32_t)(h < count ? h : count);
 }
 
-template <typename K, int RB>
-__global__ __launch_bounds__(kSortThreads) void k_upsweep(const K* __restrict__ keys, const uint32_t* __restrict__ d_count,
-                                                          int shift, int blocks, uint32_t* __restrict__ hist) {
-  constexpr int R = 1 << RB;
+__global__ __launch_bounds__(kSortThreads) void k_upsweep(const uint32_t* __restrict__ keys,
+                                                          const uint32_t* __restrict__ d_count, int shift, int blocks,
+                                                          uint32_t* __restrict__ hist) {
+  constexpr int R = kRadix;
   __shared__ uint32_t s_h[4][R];
   const int tid = threadIdx.x, wave = tid >> 6;
   for (int i = tid; i < 4 * R; i += kSortThreads) (&s_h[0][0])[i] = 0;
@@ -98,13 +92,13 @@ __global__ __launch_bounds__(kSortThreads) void k_upsweep(const K* __restrict__ 
   uint32_t i = lo + tid;
   // eight independent loads in flight per thread, then their LDS increments
   for (; i + (kSortItems - 1) * kSortThreads < hi; i += kSortItems * kSortThreads) {
-    K k[kSortItems];
+    uint32_t k[kSortItems];
 #pragma unroll
     for (int u = 0; u < kSortItems; u++) k[u] = keys[i + u * kSortThreads];
 #pragma unroll
-    for (int u = 0; u < kSortItems; u++) atomicAdd(&s_h[wave][digit_of<RB>(k[u], shift)], 1u);
+    for (int u = 0; u < kSortItems; u++) atomicAdd(&s_h[wave][digit_of(k[u], shift)], 1u);
   }
-  for (; i < hi; i += kSortThreads) atomicAdd(&s_h[wave][digit_of<RB>(keys[i], shift)], 1u);
+  for (; i < hi; i += kSortThreads) atomicAdd(&s_h[wave][digit_of(keys[i], shift)], 1u);
   __syncthreads();
   for (int d = tid; d < R; d += kSortThreads)
     hist[(int64_t)d * blocks + blockIdx.x] = s_h[0][d] + s_h[1][d] + s_h[2][d] + s_h[3][d];
@@ -153,17 +147,13 @@ __device__ __forceinline__ void wave_lds_sync() {
 // with no workgroup barrier, so the ranks follow the input order.  Waves are then combined by
 // an exclusive prefix of their counts per digit, the batch is ordered by digit in LDS, and each
 // digit's run is written to its global position.
-// IT items per thread per batch: 16 for 10-bit digits, where a 2,048-pair batch would leave
-// runs of about two pairs per digit and the stores would barely coalesce (one 10-bit pass over
-// the 1.5e7 tile keys of a 20-view call at 64x32 tiles: 0.199 -> 0.167 ms), else 8 (wider
-// batches measured slower for 8-bit digits, and for the 11-bit passes over a few 1e5 keys).
-template <typename K, int RB, int IT>
-__global__ __launch_bounds__(kSortThreads) void k_scatter(const K* __restrict__ kin, const uint32_t* __restrict__ vin,
-                                                          K* __restrict__ kout, uint32_t* __restrict__ vout,
+__global__ __launch_bounds__(kSortThreads) void k_scatter(const uint32_t* __restrict__ kin,
+                                                          const uint32_t* __restrict__ vin, uint32_t* __restrict__ kout,
+                                                          uint32_t* __restrict__ vout,
                                                           const uint32_t* __restrict__ d_count, int shift, int blocks,
                                                           const uint32_t* __restrict__ hist,
                                                           const uint32_t* __restrict__ totals) {
-  constexpr int R = 1 << RB;
+  constexpr int R = kRadix, IT = 16;         // pairs per thread and batch
   constexpr int D = R / kSortThreads;        // digits owned per thread
   constexpr int kWaveRun = IT * 64;          // consecutive pairs ranked by one wave per batch
   constexpr int kBatchP = kSortThreads * IT;  // pairs per batch
@@ -171,7 +161,7 @@ __global__ __launch_bounds__(kSortThreads) void k_scatter(const K* __restrict__ 
   __shared__ uint32_t s_boff[R];             // exclusive digit offsets within the batch
   __shared__ uint32_t s_wc[4][R];            // per-wave digit counts, then their prefix over waves
   __shared__ uint32_t s_tmp[4];
-  __shared__ K s_k[kBatchP];
+  __shared__ uint32_t s_k[kBatchP];
   __shared__ uint32_t s_v[kBatchP];
 
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
@@ -196,8 +186,7 @@ __global__ __launch_bounds__(kSortThreads) void k_scatter(const K* __restrict__ 
     const uint32_t nb = min((uint32_t)kBatchP, hi - batch);
     const uint32_t wbase = batch + (uint32_t)(wave * kWaveRun);
     for (int d = lane; d < R; d += 64) s_wc[wave][d] = 0;
-    K key[IT];
-    uint32_t val[IT], rank[IT], dig[IT];
+    uint32_t key[IT], val[IT], rank[IT], dig[IT];
 #pragma unroll
     for (int s = 0; s < IT; s++) {
       const uint32_t idx = wbase + (uint32_t)(s * 64 + lane);
@@ -210,11 +199,11 @@ __global__ __launch_bounds__(kSortThreads) void k_scatter(const K* __restrict__ 
 #pragma unroll
     for (int s = 0; s < IT; s++) {
       const bool valid = wbase + (uint32_t)(s * 64 + lane) < hi;
-      const uint32_t d = valid ? digit_of<RB>(key[s], shift) : 0u;
+      const uint32_t d = valid ? digit_of(key[s], shift) : 0u;
       dig[s] = d;
       uint64_t peers = __ballot(valid);
 #pragma unroll
-      for (int b = 0; b < RB; b++) {
+      for (int b = 0; b < kRadixBits; b++) {
         const uint64_t m = __ballot((d >> b) & 1);
         peers &= ((d >> b) & 1) ? m : ~m;
       }
@@ -261,8 +250,8 @@ __global__ __launch_bounds__(kSortThreads) void k_scatter(const K* __restrict__ 
     for (int s = 0; s < IT; s++) {
       const uint32_t j = s * kSortThreads + tid;
       if (j < nb) {
-        const K k = s_k[j];
-        const uint32_t d = digit_of<RB>(k, shift);
+        const uint32_t k = s_k[j];
+        const uint32_t d = digit_of(k, shift);
         const uint32_t o = s_base[d] + (j - s_boff[d]);
         if (o < count) {  // always true for a consistent histogram; keeps stores in bounds
           kout[o] = k;
@@ -405,7 +394,7 @@ __global__ __launch_bounds__(kDepthLdsThreads) void k_depth_lds(int n, const uin
     if (first + s * 64 < n) out[row + first + s * 64] = val[s];
 }
 
-// Larger views: least-significant-digit radix sort of every view by itself (blockIdx.y), three
+// Larger views: least-significant-digit radix sort of every view by itself, three
 // 9-bit digits of the keys' low 27 bits.  A pass is an upsweep (each block's digit counts) and a
 // scatter, whose blocks add up the counts of the blocks before them by themselves.
 constexpr int kDepthIt = 16;  // keys per thread of the upsweep's loads
@@ -742,40 +731,6 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_final(const uint32_t* __r
 
 __global__ void k_set_u64(uint64_t* p, uint64_t v) { *p = v; }
 
-template <typename K, int RB>
-void radix_pass(K* keys[2], uint32_t* vals[2], int cur, const uint32_t* d_count, int shift, int blocks,
-                uint32_t* hist, uint32_t* totals, hipStream_t st) {
-  k_upsweep<K, RB><<<blocks, kSortThreads, 0, st>>>(keys[cur], d_count, shift, blocks, hist);
-  k_scan_rows<<<1 << RB, kSortThreads, 0, st>>>(hist, blocks, totals);
-  k_scatter<K, RB, RB >= 9 ? 16 : 8><<<blocks, kSortThreads, 0, st>>>(keys[cur], vals[cur], keys[cur ^ 1],
-                                                                      vals[cur ^ 1], d_count, shift, blocks, hist,
-                                                                      totals);
-}
-
-template <typename K>
-int radix_sort_impl(K* keys[2], uint32_t* vals[2], const uint32_t* d_count, int64_t max_count, int begin_bit,
-                    int end_bit, uint32_t* hist, int blocks, hipStream_t st, int digit_cap) {
-  int cur = 0;
-  if (max_count == 0 || end_bit <= begin_bit) return cur;
-  // fewest passes of at most max_bits, with the narrowest digit (>= 8 bits) that keeps that pass
-  // count: wider digits cost LDS and ballots per item
-  const int max_bits = std::max(8, std::min(digit_cap, sizeof(K) == 4 ? kMaxRadixBits : kMaxRadixBits - 1));
-  const int bits = end_bit - begin_bit;
-  const int passes = (bits + max_bits - 1) / max_bits;
-  const int rb = max(8, (bits + passes - 1) / passes);
-  uint32_t* totals = hist + (int64_t)kMaxRadix * kMaxSortBlocks;
-  for (int shift = begin_bit; shift < end_bit; shift += rb) {
-    switch (rb) {
-      case 8: radix_pass<K, 8>(keys, vals, cur, d_count, shift, blocks, hist, totals, st); break;
-      case 9: radix_pass<K, 9>(keys, vals, cur, d_count, shift, blocks, hist, totals, st); break;
-      case 10: radix_pass<K, 10>(keys, vals, cur, d_count, shift, blocks, hist, totals, st); break;
-      default: radix_pass<K, sizeof(K) == 4 ? 11 : 10>(keys, vals, cur, d_count, shift, blocks, hist, totals, st);
-    }
-    cur ^= 1;
-  }
-  return cur;
-}
-
 }  // namespace
 
 int sort_blocks_for(int64_t max_count) {
@@ -787,9 +742,18 @@ int sort_blocks_for(int64_t max_count) {
   return (int)b;
 }
 
-int radix_sort_u32(uint32_t* keys[2], uint32_t* vals[2], const uint32_t* d_count, int64_t max_count, int begin_bit,
-                   int end_bit, uint32_t* hist, int blocks, hipStream_t st, int digit_cap) {
-  return radix_sort_impl<uint32_t>(keys, vals, d_count, max_count, begin_bit, end_bit, hist, blocks, st, digit_cap);
+int radix_sort_u32(uint32_t* keys[2], uint32_t* vals[2], const uint32_t* d_count, int64_t max_count, uint32_t* hist,
+                   int blocks, hipStream_t st) {
+  int cur = 0;
+  if (max_count == 0) return cur;
+  uint32_t* totals = hist + (int64_t)kRadix * kMaxSortBlocks;
+  for (int shift = 0; shift < 32; shift += kRadixBits, cur ^= 1) {
+    k_upsweep<<<blocks, kSortThreads, 0, st>>>(keys[cur], d_count, shift, blocks, hist);
+    k_scan_rows<<<kRadix, kSortThreads, 0, st>>>(hist, blocks, totals);
+    k_scatter<<<blocks, kSortThreads, 0, st>>>(keys[cur], vals[cur], keys[cur ^ 1], vals[cur ^ 1], d_count, shift, blocks,
+                                               hist, totals);
+  }
+  return cur;
 }
 
 size_t depth_hist_elems(int max_views) { return (size_t)max_views * kDepthBlocks * kDepthR; }
@@ -809,7 +773,7 @@ void launch_depth_sort(int n, int nv, uint32_t* const keys[2], uint32_t* const v
                        hipStream_t st) {
   if (n <= 0) return;
   // a view in LDS as long as one workgroup's registers hold it: 16,384 Gaussians in 43 us, against
-  // 46 (1 view) to 51 us (20) for the radix passes at 17,000; 12,000 in 32, 4,000 in 16 us
+  // 47 (1 view) to 49 us (20) for the radix passes at 20,000; 12,000 in 32, 4,000 in 16 us
   if (n <= 2 * kDepthLdsThreads)
     k_depth_lds<2><<<nv, kDepthLdsThreads, 0, st>>>(n, keys[0], vals[1], far);
   else if (n <= 4 * kDepthLdsThreads)
