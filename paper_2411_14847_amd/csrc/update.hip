@@ -231,8 +231,9 @@ __global__ __launch_bounds__(kScoreThreads) void k_densify_scores(SceneK s, Dens
 // key = descending score, ties by index) find the key of the last one, two more collect the members
 // before it and as many of that key as still fit, in index order, and each one's rank among them is
 // counted.  Every pass takes the Gaussians in at most kSelBlocks equal runs.  200k Gaussians, 20 views,
-// 5,000 children: pack, scan and a stable sort of all members in 13 launches 109 us, now 6 and 45 us; up to
-// kSelMost children (the count of ranks grows with their square; the call with 16,384 137 us, sorted 153), else they are sorted.
+// 5,000 children: pack, scan and a stable sort of all members in 13 launches 109 us, now 6 and 41 us; up to
+// kSelMost children (the count of ranks grows with their square; the call with 16,384 126 us, sorted
+// 151), else they are sorted.
 constexpr int kSelThreads = 1024, kSelBlocks = 256, kSelBits[3] = {11, 11, 10}, kSelShift[3] = {21, 10, 0};
 constexpr int kSelBins = 2048, kSelMost = 16384;
 // uint32 workspace: histograms [3][kSelBins], state, counts [kSelBlocks][2]
@@ -424,9 +425,10 @@ __global__ __launch_bounds__(kSelThreads) void k_densify_collect(SelRun r, const
   }
 }
 
-// Ranks of the collected members by counting: sixteen lanes share a member and take every sixteenth of
-// the others, tile after tile of LDS.
-constexpr int kRankThreads = 256, kRankLanes = 16, kRankTile = 4096;
+// Ranks of the collected members by counting: a wave takes a member, its lanes every 64th of the others,
+// tile after tile of LDS, which sixteen waves share (5,000 members 9.3 us; 13.3 with sixteen lanes to a
+// member and four waves).
+constexpr int kRankThreads = 1024, kRankLanes = 64, kRankTile = 4096;
 __global__ __launch_bounds__(kRankThreads) void k_densify_rank(int want, const uint32_t* __restrict__ d_count,
                                                                const uint64_t* __restrict__ in,
                                                                uint32_t* __restrict__ sel_idx) {
