@@ -152,6 +152,13 @@ def test_gradients_match_oracle(case):
     assert_grad_close("gradnorm", gn[:scene.n].cpu().numpy(), ogn, exclude=gflag)
 
 
+@pytest.mark.parametrize("n,deg", [(1, 3), (63, 2), (64, 1), (65, 0), (129, 3)])
+def test_gradients_at_the_adjoints_workgroup_edges(monkeypatch, n, deg):
+    """The adjoints take 64 Gaussians per workgroup (a wave per channel, four views' inputs at a time)."""
+    monkeypatch.setitem(CASES, "edge", lambda: small_multiview(seed=40 + n, n=n, views=5, W=48, H=40, deg=deg))
+    test_gradients_match_oracle("edge")
+
+
 def test_forward_is_deterministic_and_batch_independent():
     scene, cams, _ = small_multiview(seed=8, n=2500, views=3)
     log("[determinism]")
