@@ -283,3 +283,28 @@ def test_streaming_with_hash_fields(use_graph):
 def test_field_table_gradient_at_slice_and_part_edges(monkeypatch, L, F, lt, nmax, m):
     monkeypatch.setitem(CONFIGS, "edge", (L, F, lt, 64, nmax))
     run_case("edge", 2 * m + 10, m, 5)
+
+
+@pytest.mark.parametrize("offset", [0, 2])
+def test_field_of_two_features_reads_row_pairs(offset):
+    """F = 2: two neighbouring rows are one 16-byte load, from a table that starts on 8 bytes only; the last
+    row of a level, dense and hashed, included (positions at the box's upper corner).  Against the oracle."""
+    from paper_2411_14847_amd import Context
+    p = synth.hash_field_params(21, levels=6, features=2, log2_table=12, hidden=32, n_max=256)
+    f = HF.from_params(p)
+    from paper_2411_14847_amd import HashField
+    fd = HashField.from_numpy(p, "cuda")
+    buf = torch.zeros(fd.table.numel() + 4, device="cuda")
+    buf[offset:offset + fd.table.numel()] = fd.table.reshape(-1)
+    fd.table = buf[offset:offset + fd.table.numel()].view(fd.table.shape)
+    mean, idx, _, _ = synth.field_queries(22, 900, 500)
+    mean[:, idx[:40]] = np.asarray(f.aabb_max if hasattr(f, "aabb_max") else p.aabb_max, np.float32)[:, None]
+    mean[:, idx[40:80]] = np.asarray(p.aabb_min, np.float32)[:, None]
+    ctx = Context(max_gaussians=900, max_views=1, max_keys=1 << 10, max_tiles=16)
+    dpos, drot = torch.zeros(3, 500, device="cuda"), torch.zeros(4, 500, device="cuda")
+    log(f"field row pairs, table {offset} floats off")
+    ctx.hash_field_fwd(fd, dev(mean), 900, dev(idx), 500, dpos, drot)
+    ctx.sync()
+    odp, odr = HF.field_fwd(f, mean[:, idx].astype(np.float64))
+    assert_grad_close("dpos", dpos.cpu().numpy(), odp)
+    assert_grad_close("drot", drot.cpu().numpy(), odr)
