@@ -949,7 +949,12 @@ const char* ssim_args(const dass_camera* cams, int32_t n_views, const float* con
   {
     double g[11], sum = 0.0;
     for (int k = 0; k < 11; k++) sum += (g[k] = std::exp(-((k - 5.0) * (k - 5.0)) / (2.0 * 1.5 * 1.5)));
-    for (int k = 0; k < 11; k++) a.w[k] = (float)(g[k] / sum);
+    double before = 0.0;
+    for (int k = 0; k < 11; k++) {
+      a.w[k] = (float)(g[k] / sum);
+      a.w_before[k] = (float)before;
+      before += a.w[k];
+    }
   }
   for (int v = 0; v < n_views; v++) {
     if (!render[v] || !target[v] || !dl_drgb[v] || !scratch[v]) return "NULL buffer";

@@ -338,6 +338,7 @@ struct SsimArgs {
   float gS[DASS_MAX_VIEWS];        // dL/dSSIM(pixel, channel) = -lambda / (3 H W V)
   float l1_scale[DASS_MAX_VIEWS];  // (1 - lambda) / (3 H W V)
   float w[11];                     // normalised Gaussian window, sigma 1.5
+  float w_before[11];              // sums of w[0 .. i)
   int nv;
   int64_t rows, total_rows;        // per wave; of all views
 };

@@ -5,20 +5,32 @@
 // Large calls take one pass.  A wave takes a strip of one channel of one view, kCols (128) columns of which the
 // inner 108 are output, two neighbouring columns per lane, and marches down the rows of its
 // segment.  Per row it
-//   - writes the row's pixels to LDS, takes the horizontal window sums of x, y, x^2 + y^2 and xy
-//     (all the SSIM map needs: the two variances occur only as their sum) and adds them to the
-//     eleven output rows they reach, kept as partial sums in registers (a shift per row that costs
-//     nothing: each multiply-add writes its neighbour's register);
-//   - the row five above is then complete: its SSIM value and the map's derivatives with respect
-//     to mu_x, E[x^2] and E[xy] go through a second LDS row (its window scaled by dL/dSSIM) and a second set of
-//     partial sums in the same way (the window is symmetric, so the adjoint of a window sum is the
-//     same sum), which completes dL/dx = W*P1 + 2 x W*P2 + y W*P3 ten rows above, to which the L1
-//     term is added.
-// The waves share nothing, so there are no barriers, and the derivative maps never leave the chip.
+//   - writes the row's pixels to LDS, takes the horizontal window sums of t, t^2, d and d^2 (t = x + y,
+//     d = y - x: all the SSIM map needs) and adds them to the eleven output rows they reach, kept as
+//     partial sums in registers (a shift per row that costs nothing: each multiply-add writes its
+//     neighbour's register);
+//   - the row five above is then complete: its SSIM value and three derivative maps go through a second LDS
+//     row (its window scaled by dL/dSSIM) and a second set of partial sums in the same way (the window is
+//     symmetric, so the adjoint of a window sum is the same sum), which completes dL/dx ten rows above,
+//     to which the L1 term is added.
+// The waves share nothing, so there are no barriers, and the maps never leave the chip.
 //
-// Bound: vector ALU, about 420 instructions per row and lane (two pixels) at two waves per SIMD (the
+// Differences that cancel are avoided, so that no range of values loses digits (dark images and a black
+// background that both images share least of all, whose gradient is exactly 0):
+//   - with V = var(d), D = (var(t) + V) / 2 + C2 the structure's denominator and e = V / D, the structure
+//     is 1 - e and the luminance 1 - l, l = mu_d^2 / C: both errors are small where the images are alike;
+//   - with K = (1 - l) / D, the gradient is 2 W*[(1 - e) (mu_d + mu_x l) / C + K ((d - mu_d) + e (x - mu_x))],
+//     d and x at the pixel, the rest at the window's centre.  The first form's sum of W*P1, 2 x W*P2 and y W*P3
+//     is the same with terms of the size of x K where these are of the size of d K;
+//   - t enters var(t) less a shift that every lane takes from the pixels themselves: every kAhead rows
+//     the horizontal mean of its newest row, the partial sums moved to it.
+//
+// Bound: vector ALU, about 470 instructions per row and lane (two pixels) at two waves per SIMD (the
 // 140 partial sums); the halo costs a quarter of the work.  20 views at 1352x1014: 1.30 ms in the two
-// passes (whose maps moved 2.2 GB) -> 0.75 ms, the error against 64 bits 8.4e-6 -> 1.3e-6.
+// passes (whose maps moved 2.2 GB) -> 0.775 ms, the relative error against 64 bits 8.6e-6 -> 3.5e-7.  (0.76 ms
+// and 1.3e-6 with x, y less a fixed 0.5 in the first form; but then the gradient of a dark image, [0, 0.02],
+// was off by 1.5e-4 of the pixel's share where the two passes are by 2.8e-6, now 1.5e-7, and that of a
+// shared black background by 1.2e-4 where it is 0.)
 #include <algorithm>
 
 #include "dass_internal.h"
@@ -32,10 +44,8 @@ constexpr int kLanes = 64;
 constexpr int kCols = 2 * kLanes;           // columns a wave reads
 constexpr int kOut = kCols - 4 * kR;        // columns it writes (108)
 constexpr int kRowW = kCols + 2 * kR;       // an LDS row: the columns and what the outer lanes read beyond them
-// Pixels enter the moments less this (a pixel outside the image as -kShift): the window sums to
-// 1, so the variances and the covariance are the same, and their differences of moments, and the sum
-// over the derivative maps, cancel less than with values in [0, 1].
-constexpr float kShift = 0.5f;
+// The shift of t stays within this (t lies in [0, 2]), and where it is no number.
+constexpr float kMaxShift = 4.f;
 constexpr int kBehind = 2 * kR + 1;         // rows between the one read and the one that completes
 constexpr int kRing = kBehind + 1;
 constexpr float kC1 = 0.01f * 0.01f;
@@ -72,11 +82,10 @@ __device__ __forceinline__ float push(float (&acc)[kTaps - 1], const float* w, f
   return done;
 }
 
-__global__ __launch_bounds__(kLanes) void k_ssim(SsimArgs a, int per, float* __restrict__ loss_slots) {
-  // the pixels (render, target) of the last twelve rows and a row's SSIM derivatives; a lane's window
-  // starts on an even column, so it is read in aligned pairs
-  __shared__ __align__(16) float2 s_xy[kRing][kRowW];
-  __shared__ __align__(16) float2 s_sh[kRowW], s_sq[kRowW];  // the newest row shifted: x, y; x^2 + y^2, x y
+__global__ __launch_bounds__(kLanes, 2) void k_ssim(SsimArgs a, int per, float* __restrict__ loss_slots) {
+  // the pixels (t, d) of the last twelve rows and a row's derivative maps; a lane's window starts on an
+  // even column, so it is read in aligned pairs
+  __shared__ __align__(16) float2 s_td[kRing][kRowW];
   __shared__ __align__(16) float s_p[3][kRowW];
   const int lane = threadIdx.x;
   const int64_t wave = (int64_t)(blockIdx.x % kNumXcd) * per + blockIdx.x / kNumXcd;
@@ -84,10 +93,9 @@ __global__ __launch_bounds__(kLanes) void k_ssim(SsimArgs a, int per, float* __r
   // the margins that only the outermost lanes read: their sums are not used, but must be numbers
   if (lane < kR) {
 #pragma unroll
-    for (int i = 0; i < kRing; i++) s_xy[i][lane] = s_xy[i][kRowW - 1 - lane] = make_float2(0.f, 0.f);
+    for (int i = 0; i < kRing; i++) s_td[i][lane] = s_td[i][kRowW - 1 - lane] = make_float2(0.f, 0.f);
 #pragma unroll
     for (int m = 0; m < 3; m++) s_p[m][lane] = s_p[m][kRowW - 1 - lane] = 0.f;
-    s_sh[lane] = s_sh[kRowW - 1 - lane] = s_sq[lane] = s_sq[kRowW - 1 - lane] = make_float2(0.f, 0.f);
   }
   float part = 0.f;  // this wave's share of the loss
   int vi = 0;
@@ -108,9 +116,9 @@ __global__ __launch_bounds__(kLanes) void k_ssim(SsimArgs a, int per, float* __r
 #pragma unroll
   for (int i = 0; i < kTaps; i++) w[i] = a.w[i];
   const float gS = a.gS[vi], sl1 = a.l1_scale[vi];
-  float wg[kTaps];  // the window scaled by dL/dSSIM, for the derivative maps
+  float wg[kTaps];  // the window scaled by 2 dL/dSSIM, for the derivative maps
 #pragma unroll
-  for (int i = 0; i < kTaps; i++) wg[i] = gS * w[i];
+  for (int i = 0; i < kTaps; i++) wg[i] = 2.f * gS * w[i];
   const int x0 = x_lo - 2 * kR + 2 * lane;  // this lane's columns x0, x0 + 1
   int xc[2];            // the columns kept inside the image, for the loads
   bool in[2], owns[2];  // column inside the image; written by this wave
@@ -120,7 +128,8 @@ __global__ __launch_bounds__(kLanes) void k_ssim(SsimArgs a, int per, float* __r
     xc[j] = min(max(x0 + j, 0), W - 1);
     owns[j] = x0 + j >= x_lo && x0 + j < x_hi;
   }
-  float am[4][2][kTaps - 1], ap[3][2][kTaps - 1];  // partial sums: moments, derivative maps
+  // partial sums: moments (t and t^2 less the shift, d, d^2), derivative maps
+  float am[4][2][kTaps - 1], ap[3][2][kTaps - 1];
 #pragma unroll
   for (int i = 0; i < kTaps - 1; i++) {
 #pragma unroll
@@ -146,8 +155,9 @@ __global__ __launch_bounds__(kLanes) void k_ssim(SsimArgs a, int per, float* __r
   // completes is r - 11.  Pixels are loaded kAhead steps ahead into registers of their own (the steps
   // are unrolled kAhead times): the waves are few (two per SIMD, for their partial sums), so the
   // loads' latency has to be hidden by the wave itself.
-  constexpr int kAhead = 3;
+  constexpr int kAhead = 4;
   float qx[kAhead][2], qy[kAhead][2], P[3][2];
+  float shift = 0.f, mean = 0.f;  // of the lane's two columns; the newest row's horizontal mean less the shift
 #pragma unroll
   for (int i = 0; i < kAhead; i++) fetch(y_lo - 2 * kR + i, qx[i], qy[i]);
 #pragma unroll
@@ -158,20 +168,32 @@ __global__ __launch_bounds__(kLanes) void k_ssim(SsimArgs a, int per, float* __r
   int slot = 0;  // of row r in the ring; row r - 11 is in the next one
   const int r_end = y_hi + kBehind;
   for (int r0 = y_lo - 2 * kR; r0 < r_end; r0 += kAhead) {
+    {  // the shift to the newest row's mean.  (Rows that still entered with a shift from beyond an edge
+       // weigh at most 0.16 together in the first windows that lie on this side of it altogether.)
+      const float to = shift + mean, by = fabsf(to) <= kMaxShift ? to - shift : 0.f;
+      shift += by;
+#pragma unroll
+      for (int i = 0; i < kTaps - 1; i++) {
+        const float wi = a.w_before[kTaps - 1 - i];  // the weights this partial sum has taken
+#pragma unroll
+        for (int j = 0; j < 2; j++) {
+          const float was = am[0][j][i];
+          am[0][j][i] = fmaf(-by, wi, was);
+          am[1][j][i] = fmaf(-by, was + am[0][j][i], am[1][j][i]);
+        }
+      }
+    }
 #pragma unroll
   for (int u0 = 0; u0 < kAhead; u0++) {
     const int r = r0 + u0;
     if (r >= r_end) break;  // uniform
-    float2* __restrict__ row = s_xy[slot];
+    float2* __restrict__ row = s_td[slot];
     slot = slot + 1 == kRing ? 0 : slot + 1;
     const bool in_r = r >= 0 && r < H;
 #pragma unroll
     for (int j = 0; j < 2; j++) {
       const float x = in[j] && in_r ? qx[u0][j] : 0.f, y = in[j] && in_r ? qy[u0][j] : 0.f;
-      row[kR + 2 * lane + j] = make_float2(x, y);
-      const float xs = x - kShift, ys = y - kShift;
-      s_sh[kR + 2 * lane + j] = make_float2(xs, ys);
-      s_sq[kR + 2 * lane + j] = make_float2(fmaf(xs, xs, ys * ys), xs * ys);
+      row[kR + 2 * lane + j] = make_float2(x + y, y - x);
     }
 #pragma unroll
     for (int m = 0; m < 3; m++) {
@@ -179,8 +201,8 @@ __global__ __launch_bounds__(kLanes) void k_ssim(SsimArgs a, int per, float* __r
       s_p[m][kR + 1 + 2 * lane] = P[m][1];
     }
     const int ro = r - kBehind;
-    const float2 o0 = s_xy[slot][kR + 2 * lane], o1 = s_xy[slot][kR + 1 + 2 * lane];
-    const float ox[2] = {o0.x, o1.x}, oy[2] = {o0.y, o1.y};
+    const float2 o0 = s_td[slot][kR + 2 * lane], o1 = s_td[slot][kR + 1 + 2 * lane];
+    const float ot[2] = {o0.x, o1.x}, od[2] = {o0.y, o1.y};
     fetch(r + kAhead, qx[u0], qy[u0]);
     float er[2];  // |error| of channels 0 and 1 summed, row ro
     if (errs) {
@@ -203,54 +225,53 @@ __global__ __launch_bounds__(kLanes) void k_ssim(SsimArgs a, int per, float* __r
     for (int m = 0; m < 3; m++) g[m][0] = g[m][1] = 0.f;
 #pragma unroll
     for (int i2 = 0; i2 < (kTaps + 1) / 2; i2++) {
-      const float4 q2 = *reinterpret_cast<const float4*>(&s_sh[2 * lane + 2 * i2]);
-      const float4 s2 = *reinterpret_cast<const float4*>(&s_sq[2 * lane + 2 * i2]);
+      const float4 q2 = *reinterpret_cast<const float4*>(&row[2 * lane + 2 * i2]);
       float2 d2[3];
 #pragma unroll
       for (int m = 0; m < 3; m++) d2[m] = *reinterpret_cast<const float2*>(&s_p[m][2 * lane + 2 * i2]);
 #pragma unroll
       for (int u = 0; u < 2; u++) {
-        const float vx = u ? q2.z : q2.x, vy = u ? q2.w : q2.y;
-        const float v2 = u ? s2.z : s2.x, v3 = u ? s2.w : s2.y;
+        const float vt = (u ? q2.z : q2.x) - shift, vd = u ? q2.w : q2.y;
+        const float vtt = vt * vt, vdd = vd * vd;
 #pragma unroll
         for (int j = 0; j < 2; j++) {
           const int k = 2 * i2 + u - j;
           if (k < 0 || k >= kTaps) continue;
-          h[0][j] = fmaf(w[k], vx, h[0][j]);
-          h[1][j] = fmaf(w[k], vy, h[1][j]);
-          h[2][j] = fmaf(w[k], v2, h[2][j]);
-          h[3][j] = fmaf(w[k], v3, h[3][j]);
+          h[0][j] = fmaf(w[k], vt, h[0][j]);
+          h[1][j] = fmaf(w[k], vtt, h[1][j]);
+          h[2][j] = fmaf(w[k], vd, h[2][j]);
+          h[3][j] = fmaf(w[k], vdd, h[3][j]);
 #pragma unroll
           for (int m = 0; m < 3; m++) g[m][j] = fmaf(wg[k], u ? d2[m].y : d2[m].x, g[m][j]);
         }
       }
     }
     wave_sync();
+    mean = h[0][0];
     float out[2];
 #pragma unroll
     for (int j = 0; j < 2; j++) {
       const float q0 = push(ap[0][j], w, g[0][j]), q1 = push(ap[1][j], w, g[1][j]), q2 = push(ap[2][j], w, g[2][j]);
-      const float d = ox[j] - oy[j];
-      const float l1 = d > 0.f ? sl1 : (d < 0.f ? -sl1 : 0.f);
-      out[j] = l1 + (q0 + 2.f * (ox[j] - kShift) * q1 + (oy[j] - kShift) * q2);
+      const float l1 = od[j] < 0.f ? sl1 : (od[j] > 0.f ? -sl1 : 0.f);
+      out[j] = l1 + fmaf(od[j], q1, fmaf(0.5f * (ot[j] - od[j]), q2, q0));
     }
     const int rs = r - kR;  // the row whose moments are complete
     const bool in_y = rs >= 0 && rs < H, counts = rs >= y_lo && rs < y_hi;
 #pragma unroll
     for (int j = 0; j < 2; j++) {
-      const float ux = push(am[0][j], w, h[0][j]), uy = push(am[1][j], w, h[1][j]);
-      const float e2 = push(am[2][j], w, h[2][j]), exy = push(am[3][j], w, h[3][j]);
-      const float mx = ux + kShift, my = uy + kShift;
-      const float A = fmaf(2.f * mx, my, kC1);                  // luminance numerator
-      const float B = fmaf(2.f, fmaf(-ux, uy, exy), kC2);       // 2 sigma_xy + C2
-      const float Cc = fmaf(mx, mx, fmaf(my, my, kC1));         // luminance denominator
-      const float D = fmaf(-ux, ux, fmaf(-uy, uy, e2)) + kC2;   // sigma_x^2 + sigma_y^2 + C2
-      const float iC = recip(Cc), iD = recip(D);
-      const float iCD = in[j] && in_y ? iC * iD : 0.f;  // outside the image the map and its derivatives are 0
-      const float S = A * B * iCD;
-      P[0][j] = 2.f * (fmaf(my, B, -uy * A) * iCD - S * fmaf(mx, iC, -ux * iD));
-      P[1][j] = -S * iD;
-      P[2][j] = 2.f * A * iCD;
+      const float ut = push(am[0][j], w, h[0][j]), e2 = push(am[1][j], w, h[1][j]);
+      const float md = push(am[2][j], w, h[2][j]), d2 = push(am[3][j], w, h[3][j]);
+      const float mt = ut + shift, mx = 0.5f * (mt - md), my = 0.5f * (mt + md);
+      const float Vd = fmaf(-md, md, d2), Vt = fmaf(-ut, ut, e2);
+      const float iC = recip(fmaf(mx, mx, fmaf(my, my, kC1)));  // 1 / luminance denominator
+      const float iD = recip(fmaf(0.5f, Vt + Vd, kC2));         // 1 / (sigma_x^2 + sigma_y^2 + C2)
+      const float e = Vd * iD, l = md * md * iC;                // 1 - structure, 1 - luminance
+      const float K = (1.f - l) * iD, Ke = K * e;
+      const float S = (1.f - l) * (1.f - e);
+      const bool on = in[j] && in_y;  // outside the image the map and its derivatives are 0
+      P[0][j] = on ? (1.f - e) * iC * fmaf(mx, l, md) - fmaf(Ke, mx, K * md) : 0.f;
+      P[1][j] = on ? K : 0.f;
+      P[2][j] = on ? Ke : 0.f;
       ssum += owns[j] && counts ? S : 0.f;
     }
     if (ro >= y_lo) {  // uniform (ro < y_hi)
@@ -259,7 +280,7 @@ __global__ __launch_bounds__(kLanes) void k_ssim(SsimArgs a, int per, float* __r
       for (int j = 0; j < 2; j++) {
         if (!owns[j]) continue;
         o[j] = out[j];
-        const float e = fabsf(ox[j] - oy[j]);
+        const float e = fabsf(od[j]);
         l1sum += e;
         if (errs) V.err[(int64_t)ro * W + x0 + j] = (er[j] + e) * (1.0f / 3.0f);  // in channel order
       }
@@ -528,9 +549,10 @@ void launch_ssim(SsimArgs& a, float* loss_slots, hipStream_t st) {
   if (total == 0) return;
   constexpr int kSlots = 2048;
   // A row takes a wave about 1.8 us, and the two passes 47 us per million pixels, so few or narrow
-  // strips go through the passes: measured in us, passes / one pass, 1 view of 1352x1014 81 / 103, 2
-  // views 129 / 110, 3 198 / 163, 6 404 / 262, 20 1300 / 860; 9 of 640x480 134 / 131; 20 of 333x477
-  // 163 / 172 (four strips of 84 columns each).
+  // strips go through the passes: measured in us, passes / one pass, 1 view of 1352x1014 80 / 104, 2
+  // views 129 / 112, 3 198 / 168, 6 406 / 270, 20 1300 / 775; 1 of 1920x1080 100 / 120, 2 197 / 168; 9 of
+  // 640x480 132 / 134, 20 324 / 221; 10 of 500x500 123 / 134, 20 267 / 207; 20 of 333x477 161 / 176
+  // (four strips of 84 columns each), 20 of 109x1014 130 / 175.
   if (1.8 * ((double)total / kSlots + 29.0) >= 47e-6 * pixels) {
     int64_t blocks = 0;
     for (int v = 0; v < a.nv; v++) {

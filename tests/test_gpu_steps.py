@@ -626,3 +626,104 @@ def test_densify_parents_at_the_selections_edges(n, k_max, levels, max_views):
     assert int(n_dev.item()) == k_max
     parents = np.asarray(sel)[np.arange(k_max) % sel.size]
     np.testing.assert_array_equal(g.quat[:, n:n + k_max].cpu().numpy(), scene.quat[:, parents])
+
+
+def _loss_images(kind, rng, h, w):
+    """(render, target), (3, h, w) float32 each."""
+    u = lambda lo, hi: rng.uniform(lo, hi, (3, h, w))
+    near = lambda t, sd: np.clip(t + rng.normal(0, sd, t.shape), 0, 1)
+    if kind == "black":
+        t = np.zeros((3, h, w))
+        r = t
+    elif kind == "flat":  # one bright value in both
+        t = np.full((3, h, w), 0.7)
+        r = t
+    elif kind == "dark":
+        t = u(0.0, 0.1)
+        r = near(t, 0.006)
+    elif kind == "very dark":
+        t = u(0.0, 0.02)
+        r = near(t, 0.001)
+    elif kind == "mid":
+        t = u(0.1, 0.9)
+        r = near(t, 0.05)
+    elif kind == "white":
+        t = u(0.9, 1.0)
+        r = near(t, 0.006)
+    else:  # smooth fields, on all the image or on a disc in front of black
+        low = torch.as_tensor(rng.uniform(0.1, 0.9, (1, 3, h // 64, w // 64)))
+        t = torch.nn.functional.interpolate(low, size=(h, w), mode="bilinear", align_corners=True)[0].numpy()
+        t = near(t, 0.02)
+        r = near(t, 0.02)
+        if kind == "object":
+            yy, xx = np.mgrid[:h, :w]
+            on = (yy - h / 2) ** 2 + (xx - w / 2) ** 2 < (h / 4) ** 2
+            t, r = t * on, r * on
+    return r.astype(np.float32), t.astype(np.float32)
+
+
+LOSS_KINDS = ("black", "flat", "dark", "very dark", "mid", "white", "smooth", "object")
+
+
+def test_dssim_gradient_of_dark_and_bright_images_in_one_pass():
+    """A large call takes the one-pass form, a view by itself the two-pass form.  On every kind of image the
+    one pass is no further from float64 (root mean square and largest, lambda 1, in units of the pixel's
+    share) than the two passes, and images that agree in a flat area have a gradient of exactly 0 there."""
+    h, w = 480, 640
+    rng = np.random.default_rng(51)
+    pairs = [_loss_images(k, rng, h, w) for k in LOSS_KINDS]
+    folds = 3
+    cams = [synth.make_camera(np.eye(3), (0, 0, 0), w, h) for _ in range(len(pairs) * folds)]
+    ctx = make_ctx(10, cams[:1])
+    R, T = [dev(p[0]) for p in pairs], [dev(p[1]) for p in pairs]
+    dl = [torch.full((3, h, w), 7.0, device="cuda") for _ in cams]
+    loss = torch.zeros(1, device="cuda")
+    ctx.fidelity_loss_grad(cams, R * folds, T * folds, 1.0, dl, None, loss)
+    one = [torch.zeros(3, h, w, device="cuda") for _ in pairs]
+    for r, t, d in zip(R, T, one):
+        ctx.fidelity_loss_grad(cams[:1], [r], [t], 1.0, [d])
+    ctx.sync()
+    total = 0.0
+    for i, kind in enumerate(LOSS_KINDS):
+        lv, want, _ = oracle.fidelity_loss_grad(pairs[i][0][None], pairs[i][1][None], 1.0)
+        total += lv / len(pairs)
+        share = 1.0 / (3.0 * h * w)
+        e2 = (one[i].cpu().numpy() - want[0]) / share
+        for k in range(folds):
+            got = dl[i + k * len(pairs)].cpu().numpy().astype(np.float64) * len(cams)
+            e1 = (got - want[0]) / share
+            log(f"{kind}: rms / largest error, one pass {np.sqrt((e1 ** 2).mean()):.2e} {np.abs(e1).max():.2e}, "
+                f"two passes {np.sqrt((e2 ** 2).mean()):.2e} {np.abs(e2).max():.2e}")
+            if kind in ("black", "flat"):
+                inner = (slice(None), slice(10, -10), slice(10, -10))
+                assert not got[inner].any(), kind
+                assert kind != "black" or not got.any()
+            else:
+                assert (e1 ** 2).mean() <= (e2 ** 2).mean() and np.abs(e1).max() <= np.abs(e2).max(), kind
+    assert float(loss.item()) == pytest.approx(total, rel=1e-5, abs=1e-6)
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf"), 1e6])
+@pytest.mark.parametrize("at", [(0, 0), (240, 107), (479, 639)])
+def test_dssim_in_one_pass_keeps_a_bad_pixel_local(bad, at):
+    """A pixel that is no number, or huge, reaches the gradient of its channel within two window radii
+    (10 pixels) and nothing else: there the gradient is that of the images without it (rounding apart)."""
+    h, w = 480, 640
+    rng = np.random.default_rng(52)
+    r, t = _loss_images("smooth", rng, h, w)
+    cams = [synth.make_camera(np.eye(3), (0, 0, 0), w, h) for _ in range(20)]
+    ctx = make_ctx(10, cams[:1])
+    R, T = dev(r), dev(t)
+    Rb = R.clone()
+    Rb[1, at[0], at[1]] = bad
+    res = []
+    for renders in ([R] * 20, [Rb] * 20):
+        dl = [torch.full((3, h, w), 7.0, device="cuda") for _ in cams]
+        ctx.fidelity_loss_grad(cams, renders, [T] * 20, 1.0, dl)
+        ctx.sync()
+        res.append(torch.stack(dl).cpu().numpy().astype(np.float64))
+    want, got = res
+    near = np.zeros((3, h, w), bool)
+    near[1, max(0, at[0] - 10):at[0] + 11, max(0, at[1] - 10):at[1] + 11] = True
+    assert np.isfinite(got[:, ~near]).all()
+    assert (np.abs(got - want) <= 1e-3 * np.abs(want) + 1e-4 * np.abs(want).max())[:, ~near].all()
