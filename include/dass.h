@@ -259,6 +259,7 @@ dass_status dass_render_fwd_l1(dass_ctx ctx, const dass_gaussians* g, const dass
  * [0, 1]).  Writes dl_drgb[v] = dL/drender (not accumulated) and err[v] [H][W] = mean over
  * channels of |render - target| (Sec. 3.4; err may be NULL); *loss (device float, may be
  * NULL) += L.  lambda in [0, 1]; lambda = 0 is dass_l1_loss_grad (scratch may then be NULL).
+ * dl_drgb[v] and err[v] may take the place of render[v] or target[v] of the same view.
  * scratch: host array of n_views device pointers to 9 H W floats each, caller-owned and
  * overwritten.  Host arrays of n_views device pointers otherwise as dass_l1_loss_grad.
  * Errors: DASS_E_INVALID (lambda outside [0, 1], NULL arrays or entries, bad sizes). */

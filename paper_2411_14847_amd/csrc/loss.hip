@@ -532,6 +532,19 @@ __global__ __launch_bounds__(kThreads) void k_ssim_bwd(SsimArgs a, int64_t total
   add_to_slot(l1sum, sl1, s_w, loss_slots);
 }
 
+// Whether a view's outputs lie in its inputs, or its error map in its gradient.  The two passes read the windows'
+// pixels before the first output and only the own pixel's afterwards, so that the gradient may take
+// the place of the images; the waves of the one pass read pixels that others write.
+bool in_place(const SsimView& V) {
+  const int64_t hw = (int64_t)V.W * V.H;
+  const auto meet = [](const float* a, int64_t na, const float* b, int64_t nb) {
+    const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+    return x < y + (uintptr_t)nb * 4 && y < x + (uintptr_t)na * 4;
+  };
+  if (meet(V.dl, 3 * hw, V.render, 3 * hw) || meet(V.dl, 3 * hw, V.target, 3 * hw)) return true;
+  return V.err && (meet(V.err, hw, V.render, 3 * hw) || meet(V.err, hw, V.target, 3 * hw) || meet(V.err, hw, V.dl, 3 * hw));
+}
+
 }  // namespace
 
 void launch_ssim(SsimArgs& a, float* loss_slots, hipStream_t st) {
@@ -540,11 +553,13 @@ void launch_ssim(SsimArgs& a, float* loss_slots, hipStream_t st) {
   // more (its halo), and once more where it passes into the next strip.
   int64_t total = 0;
   double pixels = 0.0;
+  bool two = false;  // in place: the two passes
   for (int v = 0; v < a.nv; v++) {
     a.v[v].strips = (a.v[v].W + kOut - 1) / kOut;
     a.v[v].row_begin = total;
     total += 3ll * a.v[v].strips * a.v[v].H;
     pixels += (double)a.v[v].W * a.v[v].H;
+    two = two || in_place(a.v[v]);
   }
   if (total == 0) return;
   constexpr int kSlots = 2048;
@@ -553,7 +568,7 @@ void launch_ssim(SsimArgs& a, float* loss_slots, hipStream_t st) {
   // views 129 / 112, 3 198 / 168, 6 406 / 270, 20 1300 / 775; 1 of 1920x1080 100 / 120, 2 197 / 168; 9 of
   // 640x480 132 / 134, 20 324 / 221; 10 of 500x500 123 / 134, 20 267 / 207; 20 of 333x477 161 / 176
   // (four strips of 84 columns each), 20 of 109x1014 130 / 175.
-  if (1.8 * ((double)total / kSlots + 29.0) >= 47e-6 * pixels) {
+  if (two || 1.8 * ((double)total / kSlots + 29.0) >= 47e-6 * pixels) {
     int64_t blocks = 0;
     for (int v = 0; v < a.nv; v++) {
       a.v[v].TX = (a.v[v].W + kT - 1) / kT;

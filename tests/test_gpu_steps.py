@@ -727,3 +727,36 @@ def test_dssim_in_one_pass_keeps_a_bad_pixel_local(bad, at):
     near[1, max(0, at[0] - 10):at[0] + 11, max(0, at[1] - 10):at[1] + 11] = True
     assert np.isfinite(got[:, ~near]).all()
     assert (np.abs(got - want) <= 1e-3 * np.abs(want) + 1e-4 * np.abs(want).max())[:, ~near].all()
+
+
+@pytest.mark.parametrize("place", ["render", "target", "err in render"])
+def test_dssim_gradient_in_place_of_the_images(place):
+    """The gradient (or the error map) may be written over the view's own images, also in a call that is large enough
+    for the one pass, whose waves read their neighbours' pixels: the same results as with buffers of its own
+    (tolerance of the tests above; the two forms round differently)."""
+    h, w, n = 480, 640, 16
+    rng = np.random.default_rng(53)
+    cams = [synth.make_camera(np.eye(3), (0, 0, 0), w, h) for _ in range(n)]
+    ctx = make_ctx(10, cams[:1])
+    pairs = [_loss_images("smooth", rng, h, w) for _ in range(2)]
+    R, T = [dev(pairs[v % 2][0]) for v in range(n)], [dev(pairs[v % 2][1]) for v in range(n)]
+    new = lambda *s: torch.full(s, 7.0, device="cuda")
+    want, werr = [new(3, h, w) for _ in cams], [new(h, w) for _ in cams]
+    lw, lg = torch.zeros(1, device="cuda"), torch.zeros(1, device="cuda")
+    ctx.fidelity_loss_grad(cams, R, T, 0.2, want, werr, lw)
+    ctx.sync()
+    Ri, Ti = [r.clone() for r in R], [t.clone() for t in T]
+    got, gerr = [new(3, h, w) for _ in cams], [new(h, w) for _ in cams]
+    if place == "render":
+        got[1:] = Ri[1:]  # the first view's apart
+    elif place == "target":
+        got = Ti
+    else:
+        gerr = [r[1] for r in Ri]
+    log(f"in place of {place}")
+    ctx.fidelity_loss_grad(cams, Ri, Ti, 0.2, got, gerr, lg)
+    ctx.sync()
+    for a, b, ea, eb in zip(got, want, gerr, werr):
+        assert ((a - b).abs() <= 1e-3 * b.abs() + 1e-4 * b.abs().max()).all()
+        assert torch.equal(ea, eb)
+    assert float(lg.item()) == pytest.approx(float(lw.item()), rel=1e-5)
