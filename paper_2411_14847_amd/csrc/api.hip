@@ -161,7 +161,7 @@ dass_status allocate(dass_ctx ctx, const dass_limits& l) {
   w.cap_bin = bin_hist_elems(w.cap_tiles, l.max_gaussians);
   ALLOC(w.bin_hist, w.cap_bin);
   ALLOC(w.depth_hist, depth_hist_elems(l.max_views));
-  ALLOC(w.far, DASS_MAX_VIEWS);
+  ALLOC(w.far, 2 * DASS_MAX_VIEWS);
   ALLOC(w.hist, 2048 * 512 + 2048);  // [radix][max sort blocks] counts + radix digit totals
   ALLOC(w.scan_tmp, scan_tmp_elems(vn));
   ALLOC(w.counters, 16);
@@ -179,7 +179,7 @@ dass_status allocate(dass_ctx ctx, const dass_limits& l) {
   ALLOC(w.err, 1);
 #undef ALLOC
   w.gid_s = w.dval[1];
-  HIP_TRY(ctx, hipMemset(w.far, 0, DASS_MAX_VIEWS * sizeof(uint32_t)));
+  HIP_TRY(ctx, hipMemset(w.far, 0, 2 * DASS_MAX_VIEWS * sizeof(uint32_t)));
   HIP_TRY(ctx, hipMemset(w.counters, 0, 16 * sizeof(uint32_t)));
   HIP_TRY(ctx, hipMemset(w.err, 0, sizeof(uint32_t)));
   HIP_TRY(ctx, hipMemset(w.pairs, 0, 2 * sizeof(unsigned long long)));
@@ -459,7 +459,8 @@ dass_status render_fwd_impl(dass_ctx ctx, const dass_gaussians* g, const dass_ca
   stage_end(ctx, DASS_STAGE_PROJECT, st);
   // 2. per-view depth order
   stage_begin(ctx, DASS_STAGE_DEPTH_SORT, st);
-  launch_depth_sort(g->n, n_views, ws.dkey, ws.dval, ws.depth_hist, ws.far, st);
+  // (the rectangles in depth order are not there yet)
+  launch_depth_sort(g->n, n_views, ws.dkey, ws.dval, reinterpret_cast<uint32_t*>(ws.rect_s), ws.depth_hist, ws.far, st);
   stage_end(ctx, DASS_STAGE_DEPTH_SORT, st);
   // 3. tile lists in depth order
   stage_begin(ctx, DASS_STAGE_BINNING, st);

@@ -201,8 +201,9 @@ struct Workspace {
   uint2* rect_s = nullptr;
   uint32_t* gid_s = nullptr;       // gid of sorted position p (dval[1])
   uint32_t* depth_hist = nullptr;  // depth sort: digit counts per view and block
-  uint32_t* far = nullptr;         // [DASS_MAX_VIEWS] the view has depths whose key needs more than 27
-                                   // bits (set by the projection, cleared by the depth sort)
+  uint32_t* far = nullptr;         // [2 DASS_MAX_VIEWS] the view has depths whose key needs more than 27
+                                   // bits: set by the projection and cleared by the depth sort; the
+                                   // depth sort's copy
   float* g2d = nullptr;            // [cap_vn][9], row v * n + g: blend-backward sums (moments of
                                    // dL/d(exponent) over the offsets, d opacity, d rgb)
   uint8_t* vis = nullptr;          // [cap_vn], row v * n + g: bit 3 visible, bit c colour channel c
@@ -256,8 +257,9 @@ constexpr uint32_t kDepthInvisible = 0x7FFFFFFFu;
 constexpr uint32_t kDepthFar = 0x7FFFFFFu;        // from here on a key needs more than 27 bits
 size_t depth_hist_elems(int max_views);
 // Orders the n Gaussians of every view by depth, ties by index: keys[0] -> indices in vals[1].
-void launch_depth_sort(int n, int nv, uint32_t* const keys[2], uint32_t* const vals[2], uint32_t* hist, uint32_t* far,
-                       hipStream_t st);
+// spare: n nv values.
+void launch_depth_sort(int n, int nv, uint32_t* const keys[2], uint32_t* const vals[2], uint32_t* spare, uint32_t* hist,
+                       uint32_t* far, hipStream_t st);
 
 // binning.hip
 int64_t bin_hist_elems(int64_t max_tiles, int64_t max_gaussians);

@@ -418,13 +418,18 @@ __device__ __forceinline__ bool depth_piece(int n, int nv, int blocks, int& v, i
 
 __global__ __launch_bounds__(kSortThreads) void k_depth_upsweep(int n, int nv, int blocks, int shift,
                                                                 const uint32_t* __restrict__ keys,
-                                                                uint32_t* __restrict__ hist) {
+                                                                uint32_t* __restrict__ hist,
+                                                                uint32_t* __restrict__ far) {
   __shared__ uint32_t s_h[4][kDepthR];
   const int tid = threadIdx.x, wave = tid >> 6;
   for (int i = tid; i < 4 * kDepthR; i += kSortThreads) (&s_h[0][0])[i] = 0;
   __syncthreads();
   int v, b, lo, hi;
   if (!depth_piece(n, nv, blocks, v, b, lo, hi)) return;
+  if (shift == 0 && b == 0 && tid == 0) {  // the projection's flag, for the passes of this call
+    far[DASS_MAX_VIEWS + v] = far[v];
+    far[v] = 0;
+  }
   const uint32_t* __restrict__ k = keys + (int64_t)v * n;
   int i = lo + tid;
   for (; i + (kDepthIt - 1) * kSortThreads < hi; i += kDepthIt * kSortThreads) {
@@ -441,14 +446,15 @@ __global__ __launch_bounds__(kSortThreads) void k_depth_upsweep(int n, int nv, i
 }
 
 // NT threads.  FIRST: the values are the positions themselves.  LAST: the keys are written only if the view has
-// far depths (a fourth digit follows).
+// far depths (a fourth digit follows), and its values then go to vspare.
 template <bool FIRST, bool LAST, int NT>
 __global__ __launch_bounds__(NT) void k_depth_scatter(int n, int nv, int blocks, int shift,
                                                                 const uint32_t* __restrict__ kin,
                                                                 const uint32_t* __restrict__ vin,
                                                                 uint32_t* __restrict__ kout, uint32_t* __restrict__ vout,
                                                                 const uint32_t* __restrict__ hist,
-                                                                const uint32_t* __restrict__ far) {
+                                                                const uint32_t* __restrict__ far,
+                                                                uint32_t* __restrict__ vspare) {
   constexpr int NW = NT / 64, IT = kDepthBatch / NT;  // waves, pairs per thread and batch
   constexpr int OWN = NT < kDepthR ? NT : kDepthR;    // threads that own digits
   constexpr int D = kDepthR / OWN;                    // digits owned per thread
@@ -462,7 +468,8 @@ __global__ __launch_bounds__(NT) void k_depth_scatter(int n, int nv, int blocks,
   int v, blk, lo, hi;
   if (!depth_piece(n, nv, blocks, v, blk, lo, hi) || lo >= hi) return;  // uniform over the workgroup
   const int64_t row = (int64_t)v * n;
-  const bool write_keys = !LAST || far[v] != 0;
+  const bool write_keys = !LAST || far[DASS_MAX_VIEWS + v] != 0;
+  if (LAST && write_keys) vout = vspare;
   // exclusive scan over the digits, thread t < OWN with the digits t D, t D + 1, ...; whole workgroup
   auto digit_scan = [&](const uint32_t (&x)[D]) {
     uint32_t own = 0;
@@ -604,43 +611,79 @@ __global__ __launch_bounds__(NT) void k_depth_scatter(int n, int nv, int blocks,
 }
 
 // The fourth digit (bits 27 to 30) of the views that have depths beyond the low 27 bits (float
-// depths from 13,107 on, of which a scene has none as a rule): a stable counting sort of the whole view by one
-// workgroup, and the view's flag back to zero.
-__global__ __launch_bounds__(1024) void k_depth_far(int n, const uint32_t* __restrict__ keys, uint32_t* __restrict__ vals,
-                                                    uint32_t* __restrict__ tmp, uint32_t* __restrict__ far) {
-  __shared__ uint32_t s_base[16], s_wc[16][16];
-  const int v = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const bool any = far[v] != 0;
-  __syncthreads();
-  if (!any) return;  // uniform over the workgroup
-  if (tid == 0) far[v] = 0;
+// depths from 13,107 on: distant Gaussians of an unbounded scene); the workgroups of other views return at
+// once.  One launch: each of a view's workgroups counts the digits of the whole view by itself (a column of
+// counters per thread), those before its own part first, and then places its part, 1,024 at a time.
+// us of a whole render without / with far depths (one or nine in ten alike): a view of 200k 148 / 175, of 1M
+// 347 / 467, 20 of 200k 825 / 870; 580, 2650 and 1280 with one workgroup per view.
+constexpr int kFarThreads = 1024, kFarDigits = 16;
+__global__ __launch_bounds__(kFarThreads) void k_depth_far(int n, int blocks, const uint32_t* __restrict__ keys,
+                                                           const uint32_t* __restrict__ vin,
+                                                           uint32_t* __restrict__ vout,
+                                                           const uint32_t* __restrict__ far) {
+  __shared__ uint32_t s_cnt[kFarDigits][kFarThreads];
+  __shared__ uint32_t s_before[kFarDigits], s_base[kFarDigits], s_wc[kFarThreads / 64][kFarDigits];
+  const int v = blockIdx.x / blocks, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (far[DASS_MAX_VIEWS + v] == 0) return;  // uniform over the workgroup
   const int64_t row = (int64_t)v * n;
-  if (tid < 16) s_base[tid] = 0;
+  const int chunk = (n + blocks - 1) / blocks;
+  const int lo = min((int)(blockIdx.x % blocks) * chunk, n), hi = min(lo + chunk, n);
+  const auto digit = [&](uint32_t k) { return (k >> 27) & (kFarDigits - 1u); };
+  const auto count = [&](int b, int e) {  // into the thread's own column
+    constexpr int kAhead = 8;
+    int i = b + tid;
+    for (; i + (kAhead - 1) * kFarThreads < e; i += kAhead * kFarThreads) {
+      uint32_t k[kAhead];
+#pragma unroll
+      for (int u = 0; u < kAhead; u++) k[u] = keys[row + i + u * kFarThreads];
+#pragma unroll
+      for (int u = 0; u < kAhead; u++) atomicAdd(&s_cnt[digit(k[u])][tid], 1u);
+    }
+    for (; i < e; i += kFarThreads) atomicAdd(&s_cnt[digit(keys[row + i])][tid], 1u);
+  };
+  static_assert(kFarThreads / 64 == kFarDigits, "a wave adds up a digit's columns");
+  const auto total = [&] {  // of the wave's digit
+    uint32_t x = 0;
+#pragma unroll
+    for (int i = 0; i < kFarThreads; i += 64) x += s_cnt[wave][i + lane];
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) x += __shfl_xor(x, d, 64);
+    return x;
+  };
+#pragma unroll
+  for (int d = 0; d < kFarDigits; d++) s_cnt[d][tid] = 0u;
+  count(0, lo);
   __syncthreads();
-  for (int i = tid; i < n; i += 1024) atomicAdd(&s_base[(keys[row + i] >> 27) & 15u], 1u);
+  const uint32_t before = total();
+  if (lane == 0) s_before[wave] = before;
+  __syncthreads();
+  count(lo, n);
+  __syncthreads();
+  const uint32_t all = total();
+  if (lane == 0) s_base[wave] = all;
   __syncthreads();
   if (tid == 0) {
     uint32_t run = 0;
-    for (int d = 0; d < 16; d++) {
+    for (int d = 0; d < kFarDigits; d++) {
       const uint32_t x = s_base[d];
-      s_base[d] = run;
+      s_base[d] = run + s_before[d];
       run += x;
     }
   }
   __syncthreads();
   const uint64_t lt = lanemask_lt();
-  for (int b = 0; b < n; b += 1024) {
+  for (int b = lo; b < hi; b += kFarThreads) {
     const int i = b + tid;
-    const bool valid = i < n;
-    const uint32_t d = valid ? (keys[row + i] >> 27) & 15u : 0u;
-    const uint32_t val = valid ? vals[row + i] : 0u;
+    const bool valid = i < hi;
+    const uint32_t d = valid ? digit(keys[row + i]) : 0u;
+    const uint32_t val = valid ? vin[row + i] : 0u;
     uint64_t peers = __ballot(valid);
 #pragma unroll
     for (int k = 0; k < 4; k++) {
       const uint64_t m = __ballot((d >> k) & 1);
       peers &= ((d >> k) & 1) ? m : ~m;
     }
-    if (lane < 16) s_wc[wave][lane] = 0;
+    if (lane < kFarDigits) s_wc[wave][lane] = 0;
     wave_lds_sync();
     const uint32_t rw = __popcll(peers & lt);
     if (valid && rw == 0) s_wc[wave][d] = __popcll(peers);
@@ -648,15 +691,13 @@ __global__ __launch_bounds__(1024) void k_depth_far(int n, const uint32_t* __res
     if (valid) {
       uint32_t o = s_base[d] + rw;
       for (int w = 0; w < wave; w++) o += s_wc[w][d];
-      tmp[row + o] = val;
+      vout[row + o] = val;
     }
     __syncthreads();
-    if (tid < 16)
-      for (int w = 0; w < 16; w++) s_base[tid] += s_wc[w][tid];
+    if (tid < kFarDigits)
+      for (int w = 0; w < kFarThreads / 64; w++) s_base[tid] += s_wc[w][tid];
     __syncthreads();
   }
-  __threadfence_block();
-  for (int i = tid; i < n; i += 1024) vals[row + i] = tmp[row + i];
 }
 
 // ---- scan of uint32 -> uint64 (exclusive), 3 phases ----------------------------------------
@@ -760,17 +801,20 @@ size_t depth_hist_elems(int max_views) { return (size_t)max_views * kDepthBlocks
 
 template <int NT>
 static void depth_passes(int n, int nv, int blocks, unsigned grid, uint32_t* const keys[2], uint32_t* const vals[2],
-                         uint32_t* hist, uint32_t* far, hipStream_t st) {
-  k_depth_upsweep<<<grid, kSortThreads, 0, st>>>(n, nv, blocks, 0, keys[0], hist);
-  k_depth_scatter<true, false, NT><<<grid, NT, 0, st>>>(n, nv, blocks, 0, keys[0], nullptr, keys[1], vals[1], hist, far);
-  k_depth_upsweep<<<grid, kSortThreads, 0, st>>>(n, nv, blocks, 9, keys[1], hist);
-  k_depth_scatter<false, false, NT><<<grid, NT, 0, st>>>(n, nv, blocks, 9, keys[1], vals[1], keys[0], vals[0], hist, far);
-  k_depth_upsweep<<<grid, kSortThreads, 0, st>>>(n, nv, blocks, 18, keys[0], hist);
-  k_depth_scatter<false, true, NT><<<grid, NT, 0, st>>>(n, nv, blocks, 18, keys[0], vals[0], keys[1], vals[1], hist, far);
+                         uint32_t* spare, uint32_t* hist, uint32_t* far, hipStream_t st) {
+  k_depth_upsweep<<<grid, kSortThreads, 0, st>>>(n, nv, blocks, 0, keys[0], hist, far);
+  k_depth_scatter<true, false, NT><<<grid, NT, 0, st>>>(n, nv, blocks, 0, keys[0], nullptr, keys[1], vals[1], hist, far,
+                                                        spare);
+  k_depth_upsweep<<<grid, kSortThreads, 0, st>>>(n, nv, blocks, 9, keys[1], hist, far);
+  k_depth_scatter<false, false, NT><<<grid, NT, 0, st>>>(n, nv, blocks, 9, keys[1], vals[1], keys[0], vals[0], hist, far,
+                                                         spare);
+  k_depth_upsweep<<<grid, kSortThreads, 0, st>>>(n, nv, blocks, 18, keys[0], hist, far);
+  k_depth_scatter<false, true, NT><<<grid, NT, 0, st>>>(n, nv, blocks, 18, keys[0], vals[0], keys[1], vals[1], hist, far,
+                                                        spare);
 }
 
-void launch_depth_sort(int n, int nv, uint32_t* const keys[2], uint32_t* const vals[2], uint32_t* hist, uint32_t* far,
-                       hipStream_t st) {
+void launch_depth_sort(int n, int nv, uint32_t* const keys[2], uint32_t* const vals[2], uint32_t* spare, uint32_t* hist,
+                       uint32_t* far, hipStream_t st) {
   if (n <= 0) return;
   // a view in LDS as long as one workgroup's registers hold it: 16,384 Gaussians in 43 us, against
   // 47 (1 view) to 49 us (20) for the radix passes at 20,000; 12,000 in 32, 4,000 in 16 us
@@ -791,10 +835,12 @@ void launch_depth_sort(int n, int nv, uint32_t* const keys[2], uint32_t* const v
     // per wave, sixteen pairs long with 256 threads.  us of the sort, 256 -> 1,024 threads: one view of
     // 200k 65 -> 51, four (196 blocks) 66 -> 54, of 1M (256) 155 -> 129; eight of 200k (392) 71, 80
     if (blocks * nv <= 256)
-      depth_passes<1024>(n, nv, blocks, grid, keys, vals, hist, far, st);
+      depth_passes<1024>(n, nv, blocks, grid, keys, vals, spare, hist, far, st);
     else
-      depth_passes<256>(n, nv, blocks, grid, keys, vals, hist, far, st);
-    k_depth_far<<<nv, 1024, 0, st>>>(n, keys[1], vals[1], vals[0], far);
+      depth_passes<256>(n, nv, blocks, grid, keys, vals, spare, hist, far, st);
+    // a workgroup per CU at most, so that without far depths the launch is over at once
+    const int far_blocks = std::max(8, std::min(32, 256 / nv));
+    k_depth_far<<<nv * far_blocks, kFarThreads, 0, st>>>(n, far_blocks, keys[1], spare, vals[1], far);
   }
 }
 

@@ -319,3 +319,71 @@ def test_depth_order_at_the_sorts_edges(n, depths):
         np.testing.assert_array_equal(gk, k)
         np.testing.assert_array_equal(gv, val)
         np.testing.assert_array_equal(gr, r)
+
+
+def _scene_with_far_depths(n, share, top=1e10):
+    """n small Gaussians at depths 2 to 10, `share` of them (at least one) at depths 13,000 to `top` instead."""
+    rng = np.random.default_rng(n)
+    scene, _ = synth.frustum_scene(29, n, 0, -4.0, 0.5)
+    z = rng.uniform(2.0, 10.0, n)
+    far = rng.choice(n, max(1, int(n * share)), replace=False)
+    z[far] = np.exp(rng.uniform(np.log(1.3e4), np.log(top), far.size))
+    z[far[0]] = 20_000.0
+    scene.mean[2] = z.astype(np.float32)
+    scene.mean[:2] = (rng.uniform(-0.4, 0.4, (2, n)) * z).astype(np.float32)
+    scene.log_scale[:] = (np.log(0.002 * z) + rng.normal(0, 0.3, (3, n))).astype(np.float32)
+    return scene, far
+
+
+@pytest.mark.parametrize("n,views,share", [(16_385, 1, 0.0), (16_385, 3, 0.5), (60_001, 3, 0.05), (60_001, 9, 0.9)])
+def test_depth_order_with_far_depths_among_near_ones(n, views, share):
+    """A view with depths beyond 13,107 takes a fourth digit, spread over 8 to 32 workgroups: a single far
+    Gaussian, few and most of them, over several of that digit's values, the other views without any
+    (looking the other way).  Lists bit-exact against the oracle, in a second call as in the first."""
+    scene, _ = _scene_with_far_depths(n, share)
+    away = np.diag([1.0, -1.0, -1.0])
+    cams = [synth.make_camera(away if v % 2 else np.eye(3), (0.01 * v, 0.0, 0.0), 320, 200) for v in range(views)]
+    log(f"[far depths] n {n} views {views} share {share}")
+    g = to_gpu(scene)
+    ctx = make_ctx(scene.n, cams)
+    for _ in range(2):
+        ctx.render_fwd(g, cams, BG)
+    ctx.sync()
+    for v, cam in enumerate(cams):
+        p = oracle.project(scene, cam, (16, 16))
+        assert not np.any(p.flags & oracle.FLAG_RADIUS)
+        k, val, r = oracle.keys(p, cam, (16, 16))
+        TX, TY = oracle.tiles_of(cam, (16, 16))
+        gk, gv, gr = ctx.debug_keys(v, k.size + 16, TX * TY)
+        np.testing.assert_array_equal(gk, k)
+        np.testing.assert_array_equal(gv, val)
+        np.testing.assert_array_equal(gr, r)
+
+
+def test_far_gaussians_do_not_dominate_a_views_time():
+    """One Gaussian of 300k at depth 20,000, or a tenth of them: the render takes at most half as long again as
+    with all near (their digit of the sort is one more pass of four; by one workgroup it took as long
+    as several renders)."""
+    scene, far = _scene_with_far_depths(300_000, 0.1)
+    cams = [synth.make_camera(np.eye(3), (0.0, 0.0, 0.0), 640, 480)]
+    ctx = make_ctx(scene.n, cams)
+    out, best = None, {}
+    at = np.random.default_rng(3).uniform(-0.4, 0.4, (2, far.size))
+    for rep in range(6):
+        for name, of in (("near", far[:0]), ("one", far[:1]), ("tenth", far)):
+            z = np.full(far.size, 9.0)
+            z[:of.size] = 20_000.0
+            scene.mean[:, far] = np.concatenate([at * z, z[None]])
+            scene.log_scale[:, far] = np.log(0.002 * z)
+            g = to_gpu(scene)
+            out = ctx.render_fwd(g, cams, BG, out=out)
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            ctx.sync()
+            a.record()
+            for _ in range(10):
+                ctx.render_fwd(g, cams, BG, out=out)
+            b.record()
+            b.synchronize()
+            best[name] = min(best.get(name, 1e9), a.elapsed_time(b) / 10)
+    log(f"  ms: {best}")
+    assert best["one"] <= 1.5 * best["near"] and best["tenth"] <= 1.5 * best["near"]
