@@ -1180,24 +1180,27 @@ void launch_fill_u32(uint32_t* p, uint32_t v, int64_t n, hipStream_t st) {
   k_fill_u32<<<(unsigned)blocks, 256, 0, st>>>(p, v, n);
 }
 
-// Whether a call's 16x16 sub-tiles are walked by one wave per quadrant: up to where the chip's
-// 1,024 SIMDs hold about ten (forward) or four (backward) of the four-quadrant waves each, so the
-// longest list sets the time.  Measured, us forward / backward, four quadrants per wave -> one:
-// 1,280 sub-tiles (7k Gaussians, 20 views at 128x128) 244 -> 59 / 485 -> 118; 2,760 (200k at 960x720)
-// 127 -> 79 / 194 -> 185; 3,840 (300k at 1280x720) 195 -> 113 / 330 -> 272; 5,632 (200k at 1352x1014)
-// 110 -> 90 / 207 -> 245; 8,160 117 -> 111 / 243 -> 318; 11,264 150 -> 154 / 321 -> 454 (there the
-// LDS reads, one entry per quadrant instead of per four, and the reductions bound it).
-constexpr int64_t kByQuadrantFwd = 10240, kByQuadrantBwd = 4096;
-static inline bool by_quadrant(const ViewsIO& io, int64_t sub_tiles, int64_t most) {
-  return io.sub == 16 && sub_tiles <= most;
-}
-
 // The number of views if there are several and all have as many tiles, else 0.
 static inline int views_alike(const ViewsIO& io, int nv, int64_t total_tiles) {
   if (nv < 2 || total_tiles % nv) return 0;
   for (int v = 1; v < nv; v++)
     if (io.v[v].tile_base != v * (total_tiles / nv)) return 0;
   return nv;
+}
+
+// Whether a call's 16x16 sub-tiles are walked by one wave per quadrant: up to where the chip's 1,024 SIMDs
+// hold about ten (forward) or four (backward) of the four-quadrant waves each, so the longest list sets the
+// time.  The backward's line lies lower for one view (or views of several sizes), whose crowded middle is on
+// few XCDs, and wide footprints, whose lists are alike.  Times of the call in us, one quadrant per wave /
+// four: forward (one view; frustum scene of narrow footprints, or wide ones of about 200 pixels, 100k
+// Gaussians), 5,632 sub-tiles 174 / 188, 249 / 295 wide; 8,160 200 / 208, 280 / 325; 10,240 213 / 218, 319 /
+// 365 (20k narrow ones 119 / 114); forward and backward, 1,024 narrow 322 / 419, wide 437 / 522; 3,072 352 /
+// 359, 490 / 554; 3,584 386 / 397, 632 / 595 (500k: 545 / 642, 784 / 796); 4,032 392 / 391, 553 / 557 (20k
+// wide 456 / 416); 4,096 412 / 414, 773 / 641; 4,800 420 / 394, 544 / 535; 16 views of 256 sub-tiles
+// each 904 / 1040, 842 / 923.
+constexpr int64_t kByQuadrantFwd = 10240, kByQuadrantBwd = 4096, kByQuadrantBwdOne = 3600;
+static inline bool by_quadrant(const ViewsIO& io, int64_t sub_tiles, int64_t most) {
+  return io.sub == 16 && sub_tiles <= most;
 }
 
 static inline int per_xcd(int64_t total_tiles) { return (int)((total_tiles + kNumXcd - 1) / kNumXcd); }
@@ -1314,9 +1317,10 @@ void launch_blend_bwd(const ViewsIO& io, int nv, int64_t total_tiles, const floa
   if (total == 0) return;
   const int per = per_xcd(total);
   const dim3 grid(per * kNumXcd), block(kLanes);
-  if (by_quadrant(io, total, kByQuadrantBwd)) {
-    k_blend_bwd_q<<<grid, kQB, 0, st>>>(io, nv, (int)total, per, views_alike(io, nv, total_tiles), bg[0], bg[1], bg[2],
-                                        ws.ranges, ws.vals, ws.rec_u, ws.g2d);
+  const int alike = views_alike(io, nv, total_tiles);
+  if (by_quadrant(io, total, alike ? kByQuadrantBwd : kByQuadrantBwdOne)) {
+    k_blend_bwd_q<<<grid, kQB, 0, st>>>(io, nv, (int)total, per, alike, bg[0], bg[1], bg[2], ws.ranges, ws.vals, ws.rec_u,
+                                        ws.g2d);
     return;
   }
 #define DASS_BWD(SUBT, BT)                                                                                     \

@@ -387,3 +387,33 @@ def test_far_gaussians_do_not_dominate_a_views_time():
             best[name] = min(best.get(name, 1e9), a.elapsed_time(b) / 10)
     log(f"  ms: {best}")
     assert best["one"] <= 1.5 * best["near"] and best["tenth"] <= 1.5 * best["near"]
+
+
+def test_backward_of_one_wide_view_does_not_slow_down_below_its_rules_line():
+    """Wide footprints, one view: the backward of 1024x1024 (4,096 sub-tiles) takes no longer than that of the
+    slightly larger 1088x1024, whatever kernel either is given (it took a fifth longer by quadrants)."""
+    rng = np.random.default_rng(11)
+    n = 100_000
+    scene, _ = synth.frustum_scene(11, n, 0, -2.0, 0.5)
+    z = rng.uniform(2.0, 10.0, n)
+    scene.mean[:] = np.concatenate([rng.uniform(-0.4, 0.4, (2, n)) * z, z[None]])
+    g = to_gpu(scene)
+    grads, ms = g.zeros_like(), {}
+    for rep in range(4):
+        for w in (1024, 1088):
+            cams = [synth.make_camera(np.eye(3), (0.0, 0.0, 0.0), w, 1024)]
+            ctx = make_ctx(n, cams, keys_per_gaussian=90)
+            ctx.tile = (64, 64)
+            out = ctx.render_fwd(g, cams, BG)
+            dl = [torch.ones(3, 1024, w, device="cuda")]
+            ctx.render_bwd(g, cams, BG, out, dl, grads)
+            ctx.sync()
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(10):
+                ctx.render_bwd(g, cams, BG, out, dl, grads)
+            b.record()
+            b.synchronize()
+            ms[w] = min(ms.get(w, 1e9), a.elapsed_time(b) / 10)
+    log(f"  ms by width: {ms}")
+    assert ms[1024] <= 1.1 * ms[1088]
