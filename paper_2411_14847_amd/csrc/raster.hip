@@ -55,6 +55,7 @@ constexpr int kPosBits = 27;  // list positions carried with the clamp bit and t
 constexpr int kPosMask = (1 << kPosBits) - 1;
 constexpr uint32_t kClampBit = 1u << kPosBits;
 constexpr int kQmShift = 28;
+constexpr uint32_t kInfBit = 1u;  // (backward by quadrant) the colour is not finite
 constexpr float kNever = 2.0f;  // alpha threshold of a stopped pixel: above every alpha (<= 0.99)
 
 __device__ __forceinline__ uint64_t lane_lt_mask(int lane) { return lane == 0 ? 0ull : (~0ull >> (64 - lane)); }
@@ -641,7 +642,7 @@ __global__ __launch_bounds__(kQB) void k_blend_fwd_q(ViewsIO io, int nv, int tot
       const FwdStage* st = s_st[g];
       int ja = q_first(m), jb = q_first(m);
       FwdStage A = st[ja], B = st[jb];
-      auto blend2 = [&](const FwdStage& A, const FwdStage& B) {
+      auto blend2 = [&](const FwdStage& A, FwdStage& B) {
         // the operations of k_blend_fwd, the two alphas side by side
         float aa, ab;
         {
@@ -665,6 +666,8 @@ __global__ __launch_bounds__(kQB) void k_blend_fwd_q(ViewsIO io, int nv, int tot
           wa = stop_a ? 0.f : wa;
           ta = ta && !stop_a;
           thr = stop_a ? kNever : thr;
+          // the quadrant's last pixel stopped at A: it does not see B, whose colour may be infinite
+          if (__ballot(thr < 1.f) == 0) B.rgb.x = B.rgb.y = B.rgb.z = 0.f;
           tb = ab >= thr;
           wb = tb ? ab * T : 0.f;
           T -= wb;
@@ -804,7 +807,9 @@ __global__ __launch_bounds__(kQB) void k_blend_bwd_q(ViewsIO io, int nv, int tot
       if (qm) {
         s_st[k][lane].xy = xy;
         s_st[k][lane].co = make_float4(-0.5f * kLog2e * cn.x, -kLog2e * cn.y, -0.5f * kLog2e * cn.z, __log2f(cn.w));
-        s_st[k][lane].rgb = make_float4(R.r2.x, R.r2.y, R.r2.z, __uint_as_float(cn.w >= kAlphaMax ? kClampBit : 0u));
+        const bool inf = !(fabsf(R.r2.x) + fabsf(R.r2.y) + fabsf(R.r2.z) < INFINITY);
+        s_st[k][lane].rgb = make_float4(R.r2.x, R.r2.y, R.r2.z,
+                                        __uint_as_float((cn.w >= kAlphaMax ? kClampBit : 0u) | (inf ? kInfBit : 0u)));
         s_st[k][lane].p = p;
         s_st[k][lane].io = 1.0f / cn.w;
       }
@@ -825,7 +830,7 @@ __global__ __launch_bounds__(kQB) void k_blend_bwd_q(ViewsIO io, int nv, int tot
       const BwdStage* st = s_st[g];
       int ja = q_last(m), jb = q_last(m);
       BwdStage A = st[ja], B = st[jb];
-      auto blend2 = [&](const BwdStage& A, const BwdStage& B, int pa, int pb) {
+      auto blend2 = [&](BwdStage& A, BwdStage& B, int pa, int pb) {
         // the operations of k_blend_bwd, the two alphas side by side
         const float dxa = (A.xy.x - (float)qx) - kx, dya = (A.xy.y - (float)qy) - ky;
         const float dxb = (B.xy.x - (float)qx) - kx, dyb = (B.xy.y - (float)qy) - ky;
@@ -836,7 +841,16 @@ __global__ __launch_bounds__(kQB) void k_blend_bwd_q(ViewsIO io, int nv, int tot
         const float aa = fminf(kAlphaMax, ra), ab = fminf(kAlphaMax, rb);
         const bool ta = (idx0 + g * 64 + pa < last) && (aa >= kAlphaMin);
         const bool tb = (idx0 + g * 64 + pb < last) && (ab >= kAlphaMin);
-        if ((__ballot(ta) | __ballot(tb)) != 0) {
+        const uint64_t ma = __ballot(ta), mb = __ballot(tb);
+        if ((ma | mb) != 0) {
+          const uint32_t wab = (uint32_t)__builtin_amdgcn_readfirstlane(
+              (int)(__float_as_uint(A.rgb.w) | __float_as_uint(B.rgb.w)));
+          // an entry that no pixel takes adds nothing, also where a product with its 0 is no number
+          if (__builtin_expect((wab & kInfBit) != 0, 0)) {  // uniform, rare
+            __asm__ volatile("");
+            if (ma == 0) A.rgb.x = A.rgb.y = A.rgb.z = 0.f;
+            if (mb == 0) B.rgb.x = B.rgb.y = B.rgb.z = 0.f;
+          }
           const float ea = ta ? aa : 0.f, eb = tb ? ab : 0.f;
           const float ia = __builtin_amdgcn_rcpf(1.f - ea), ib = __builtin_amdgcn_rcpf(1.f - eb);
           const float Ta = T * ia;
@@ -847,17 +861,16 @@ __global__ __launch_bounds__(kQB) void k_blend_bwd_q(ViewsIO io, int nv, int tot
           const float db = fmaf(B.rgb.x, dC0, fmaf(B.rgb.y, dC1, fmaf(B.rgb.z, dC2, nS)));
           nS = fmaf(-eb, db, nS);
           float Pa = wa * da, Pb = wb * db;
-          const uint32_t wab = __float_as_uint(A.rgb.w) | __float_as_uint(B.rgb.w);
-          if (__builtin_expect(__builtin_amdgcn_readfirstlane((int)wab) != 0, 0)) {  // uniform, rare
+          if (__builtin_expect((wab & kClampBit) != 0, 0)) {  // uniform, rare
             __asm__ volatile("");
-            if (__float_as_uint(A.rgb.w) != 0u) Pa = ra < kAlphaMax ? Pa : 0.f;
-            if (__float_as_uint(B.rgb.w) != 0u) Pb = rb < kAlphaMax ? Pb : 0.f;
+            if (__float_as_uint(A.rgb.w) & kClampBit) Pa = ra < kAlphaMax ? Pa : 0.f;
+            if (__float_as_uint(B.rgb.w) & kClampBit) Pb = rb < kAlphaMax ? Pb : 0.f;
           }
           const float xa = Pa * dxa, ya = Pa * dya, xb = Pb * dxb, yb = Pb * dyb;
           const float sa[9] = {xa, ya, xa * dxa, xa * dya, ya * dya, Pa * A.io, wa * dC0, wa * dC1, wa * dC2};
           const float sb[9] = {xb, yb, xb * dxb, xb * dyb, yb * dyb, Pb * B.io, wb * dC0, wb * dC1, wb * dC2};
           const float tot = wave_reduce18(sa, sb, odd);
-          const int pos = lane < 32 ? pa : pb;
+          const int pos = lane < 32 ? (ma != 0 ? pa : 64) : (mb != 0 ? pb : 64);
           if (writes && pos < 64) atomicAdd(&s_acc[(g * 64 + pos) * 9 + slot], tot);
         }
       };
@@ -865,7 +878,7 @@ __global__ __launch_bounds__(kQB) void k_blend_bwd_q(ViewsIO io, int nv, int tot
         bool more = m != 0;
         int pa = ja, pb = jb;
         ja = q_last(m), jb = q_last(m);
-        const BwdStage An = st[ja], Bn = st[jb];
+        BwdStage An = st[ja], Bn = st[jb];
         blend2(A, B, pa, pb);
         if (!more) break;
         more = m != 0;

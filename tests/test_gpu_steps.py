@@ -760,3 +760,28 @@ def test_dssim_gradient_in_place_of_the_images(place):
         assert ((a - b).abs() <= 1e-3 * b.abs() + 1e-4 * b.abs().max()).all()
         assert torch.equal(ea, eb)
     assert float(lg.item()) == pytest.approx(float(lw.item()), rel=1e-5)
+
+
+@pytest.mark.parametrize("batch", [64, 128])
+def test_fused_forward_l1_by_subtile_matches_render_then_l1(batch):
+    """As the test of the fused forward above, for a call of 11,718 sub-tiles of 16x16, which a wave each blends
+    (the form of a training step over every camera)."""
+    scene, cams, _ = synth.tiny_scene(6, 1500, 489, 327, sh_degree=2, log_scale_mu=-2.2)
+    cams = cams * 18
+    rng = np.random.default_rng(12)
+    targets = [dev(rng.uniform(size=(3, c.height, c.width)).astype(np.float32)) for c in cams[:2]] * 9
+    g = to_gpu(scene)
+    ctx = make_ctx(scene.n, cams, keys_per_gaussian=700)
+    ctx.batch = batch
+    out = ctx.render_fwd(g, cams, BG)
+    dl, dl2 = ([torch.full_like(t, 5.0) for t in targets] for _ in range(2))
+    err, err2 = ([torch.full_like(t[0], 5.0) for t in targets] for _ in range(2))
+    loss, loss2 = torch.zeros(1, device="cuda"), torch.zeros(1, device="cuda")
+    ctx.l1_loss_grad(cams, [o.rgb for o in out], targets, dl, err, loss)
+    out2 = ctx.render_fwd_l1(g, cams, BG, targets, dl2, err2, loss2)
+    ctx.sync()
+    for v in range(len(cams)):
+        assert torch.equal(out2[v].rgb, out[v].rgb) and torch.equal(out2[v].t_final, out[v].t_final)
+        assert torch.equal(out2[v].n_contrib, out[v].n_contrib)
+        assert torch.equal(dl2[v], dl[v]) and torch.equal(err2[v], err[v])
+    assert float(loss2.item()) == pytest.approx(float(loss.item()), rel=1e-5)

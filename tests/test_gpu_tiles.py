@@ -417,3 +417,67 @@ def test_backward_of_one_wide_view_does_not_slow_down_below_its_rules_line():
             ms[w] = min(ms.get(w, 1e9), a.elapsed_time(b) / 10)
     log(f"  ms by width: {ms}")
     assert ms[1024] <= 1.1 * ms[1088]
+
+
+@pytest.mark.parametrize("batch", [64, 128, 256])
+def test_blend_kernels_agree_in_mixed_calls_and_for_every_batch(batch):
+    """A view by itself (both directions by quadrant), nine times over (5,859 sub-tiles: the forward by quadrant, the
+    backward by sub-tile, as one 1352x1014 view takes it) and eighteen times (both by sub-tile), with
+    every batch: images, T_final and n_contrib bit-identical, gradients as in the test above."""
+    scene, cams, _ = synth.tiny_scene(6, 1500, 489, 327, sh_degree=2, log_scale_mu=-2.2)
+    rng = np.random.default_rng(9)
+    dl = torch.as_tensor(rng.normal(size=(3, cams[0].height, cams[0].width)).astype(np.float32), device="cuda")
+    g = to_gpu(scene)
+    one = None
+    for k in (1, 9, 18):
+        cc = cams * k
+        ctx = make_ctx(scene.n, cc, keys_per_gaussian=700)
+        ctx.batch = batch
+        out = ctx.render_fwd(g, cc, BG)
+        grads = g.zeros_like()
+        ctx.render_bwd(g, cc, BG, out, [dl] * k, grads)
+        ctx.sync()
+        one = one or (out[0], grads)
+        for o in out:
+            assert torch.equal(o.rgb, one[0].rgb) and torch.equal(o.t_final, one[0].t_final)
+            assert torch.equal(o.n_contrib, one[0].n_contrib)
+        for a, b in zip(one[1].planes(), grads.planes()):
+            scale = float(a.abs().max())
+            assert scale > 0.0 and float((b / k - a).abs().max()) <= 1e-5 * scale
+
+
+@pytest.mark.parametrize("of", ["colours", "pixel gradients"])
+def test_infinities_spread_no_further_by_quadrant_than_by_subtile(of):
+    """Gaussians of infinite colour among opaque ones, or pixel gradients that are no numbers: the same pixels and
+    Gaussians get values that are no numbers whether a wave takes a quadrant, two entries at a time, or a sub-tile, one entry at a time (each pixel's
+    and each entry's operations are the same, and an entry no pixel of a quadrant takes adds nothing)."""
+    scene, cams, _ = synth.opaque_scene(5, n=900, width=485, height=318, sh_degree=0)
+    scene.logit[::3] -= 4.0  # faint ones too, with wide margins where no pixel takes them
+    rng = np.random.default_rng(9)
+    dl = torch.as_tensor(rng.normal(size=(3, cams[0].height, cams[0].width)).astype(np.float32), device="cuda")
+    if of == "colours":
+        scene.sh[:, 5::29] = np.inf
+    else:
+        dl[1, 150:170:7, 200:280:9] = float("nan")
+    g = to_gpu(scene)
+    res = []
+    for k in (1, 18):
+        cc = cams * k
+        ctx = make_ctx(scene.n, cc, keys_per_gaussian=700)
+        out = ctx.render_fwd(g, cc, BG)
+        grads = g.zeros_like()
+        ctx.render_bwd(g, cc, BG, out, [dl] * k, grads)
+        ctx.sync()
+        res.append((out[0], grads))
+    (a, ga), (b, gb) = res
+    bad = ~torch.isfinite(a.rgb)
+    log(f"  pixels that are no numbers: {int(bad.any(0).sum())} of {bad[0].numel()}, by sub-tile "
+        f"{int((~torch.isfinite(b.rgb)).any(0).sum())}")
+    log(f"  gradients: {[int((~torch.isfinite(p)).sum()) for p in ga.planes()]}, by sub-tile "
+        f"{[int((~torch.isfinite(p)).sum()) for p in gb.planes()]} of {[p.numel() for p in ga.planes()]}")
+    assert int(bad.sum()) < bad.numel() and (int(bad.sum()) > 0) == (of == "colours")
+    same = torch.equal(torch.nan_to_num(a.rgb, 7.0), torch.nan_to_num(b.rgb, 7.0))
+    assert same
+    for p, q in zip(ga.planes(), gb.planes()):
+        same = torch.equal(torch.isfinite(p), torch.isfinite(q))
+        assert same
