@@ -16,7 +16,7 @@
 // scatter waits on LDS and on its stores.  The keys-and-radix-sort form it replaces wrote 8 bytes per
 // key, read them twice and wrote them again per 8- to 11-bit pass, then read them for the ranges:
 // 1.5e7 keys of 20 views (64x32 tiles) 0.30 -> 0.17 ms, 2.2e7 keys of 8 mixed views (16x16 tiles)
-// 0.43 -> 0.32 ms, 2e8 keys of wide Gaussians 2.56 -> 0.87 ms, 8e5 keys of one view 62 -> 35 us.
+// 0.43 -> 0.32 ms, 2e8 keys of wide Gaussians 2.56 -> 0.60 ms, 8e5 keys of one view 62 -> 35 us.
 #include <algorithm>
 
 #include "dass_internal.h"
@@ -26,8 +26,10 @@ namespace {
 
 // Tiles a wave counts or scatters at once; a view's tiles beyond this are taken window by window.
 // The count's windows only have to fit its array.  The scatter is bound by latency, so by the waves
-// per CU: 256 tiles (5.3 KB of LDS per wave) against 1,024 take 0.100 against 0.149 ms for the
-// 1.5e7 keys of 20 views of 200k Gaussians, 0.89 against 1.37 ms for 2e8 keys of wide Gaussians.
+// per CU, also where small tiles give many windows and the rectangles are read once for each: whole
+// renders with 256, 512 and 1,024 tiles, in us: 8 views of 200k Gaussians at 1920x1080 in 16x16 tiles (32
+// windows of 256 each) 944, 1051, 1076; one at 3840x2160 (127) 473, 510, 511; one of 1M there 1619, 1652,
+// 1668; 20 of 200k at 1352x1014 in 32x32 tiles (6) 1312, 1316, 1318.
 constexpr int kWinTiles = 1024;
 constexpr int kScatterTiles = 256;
 // ((bx + 1) | 1)(by + 1) for bx by <= kWinTiles: at most bx by + bx + 2 by + 2
@@ -468,9 +470,11 @@ int windows_of(int TX, int TY, int most) {
 
 }  // namespace
 
-// 128 chunks per tile and up to 16 MB more, as far as chunks of 64 Gaussians need it.
+// 128 chunks per tile, within 1 GB as far as one chunk is (contexts for more than 2M tiles have fewer per
+// tile), and up to 16 MB more, as far as chunks of 64 Gaussians need it.
 int64_t bin_hist_elems(int64_t max_tiles, int64_t max_gaussians) {
-  return 128 * max_tiles + std::min(int64_t(1) << 22, max_tiles * (max_gaussians / 64 + 1));
+  return std::max(max_tiles, std::min(128 * max_tiles, int64_t(1) << 28)) +
+         std::min(int64_t(1) << 22, max_tiles * (max_gaussians / 64 + 1));
 }
 
 void launch_binning(int n, int nv, const CamsK& cams, int64_t total_tiles, Workspace& ws, hipStream_t st) {
@@ -494,7 +498,7 @@ void launch_binning(int n, int nv, const CamsK& cams, int64_t total_tiles, Works
   // 20 views 0.166 ms with chunks of 512, 0.183 with 256, 0.23 with 1,024.
   int64_t chunk = ((int64_t)nv * n / 2048 + 63) / 64 * 64;
   chunk = std::min<int64_t>(std::max<int64_t>(chunk, 64), 512);
-  const int64_t max_chunks = ws.cap_bin / total_tiles;  // >= 128
+  const int64_t max_chunks = ws.cap_bin / total_tiles;  // >= 1
   chunk = std::max(chunk, ((n + max_chunks - 1) / max_chunks + 63) / 64 * 64);
   const int chunks = (int)((n + chunk - 1) / chunk);
   const auto grid = [&](int w) { return (unsigned)(((int64_t)chunks * nv * w + kNumXcd - 1) / kNumXcd * kNumXcd); };

@@ -481,3 +481,22 @@ def test_infinities_spread_no_further_by_quadrant_than_by_subtile(of):
     for p, q in zip(ga.planes(), gb.planes()):
         same = torch.equal(torch.isfinite(p), torch.isfinite(q))
         assert same
+
+
+def test_a_context_for_very_many_tiles_stays_small():
+    """max_tiles of 2^26: beside 12 bytes per tile (ranges, totals) the binning's histogram takes 1 GB, not 128
+    counts per tile (34 GB), and a render in such a context is the same as in one made to measure."""
+    from paper_2411_14847_amd import Context
+    scene, cams, _ = synth.tiny_scene(6, 1500, 489, 327, sh_degree=0, log_scale_mu=-2.2)
+    g = to_gpu(scene)
+    small = make_ctx(scene.n, cams, keys_per_gaussian=700)
+    want = small.render_fwd(g, cams, BG)[0]
+    small.sync()
+    free, _ = torch.cuda.mem_get_info()
+    ctx = Context(max_gaussians=scene.n, max_views=1, max_keys=700 * scene.n, max_tiles=1 << 26)
+    took = free - torch.cuda.mem_get_info()[0]
+    log(f"  context for 2^26 tiles: {took / 2**30:.2f} GB")
+    got = ctx.render_fwd(g, cams, BG)[0]
+    ctx.sync()
+    assert torch.equal(got.rgb, want.rgb) and torch.equal(got.n_contrib, want.n_contrib)
+    assert took < 3 << 30
