@@ -495,8 +495,12 @@ void launch_binning(int n, int nv, const CamsK& cams, int64_t total_tiles, Works
   // Gaussians per chunk: about 2,048 chunks over the call, at most 512 Gaussians each, and a
   // histogram (tiles x chunks) within its buffer.  More chunks balance the scatter but lengthen the
   // row scan: one view of 200k Gaussians takes 35 us in all with 1,563 chunks and 47 with 3,125;
-  // 20 views 0.166 ms with chunks of 512, 0.183 with 256, 0.23 with 1,024.
+  // 20 views 0.166 ms with chunks of 512, 0.183 with 256, 0.23 with 1,024.  And no more than about 64
+  // counts per Gaussian where it has many tiles: 32 views of 3840x2160 in 16x16 tiles with 2k Gaussians took
+  // 2.28 ms in chunks of 64, 1,000 counts each (2.09 with sorted keys), 2.13 in chunks of 512; 20k 3.70,
+  // 3.50; one view with 20k 197 us, 181.
   int64_t chunk = ((int64_t)nv * n / 2048 + 63) / 64 * 64;
+  chunk = std::max(chunk, (total_tiles / nv / 64 + 63) / 64 * 64);
   chunk = std::min<int64_t>(std::max<int64_t>(chunk, 64), 512);
   const int64_t max_chunks = ws.cap_bin / total_tiles;  // >= 1
   chunk = std::max(chunk, ((n + max_chunks - 1) / max_chunks + 63) / 64 * 64);

@@ -500,3 +500,26 @@ def test_a_context_for_very_many_tiles_stays_small():
     ctx.sync()
     assert torch.equal(got.rgb, want.rgb) and torch.equal(got.n_contrib, want.n_contrib)
     assert took < 3 << 30
+
+
+@pytest.mark.parametrize("n", [63, 319, 321, 1500])
+@pytest.mark.parametrize("log_scale", [-4.0, -1.5])
+def test_tile_lists_in_chunks_set_by_the_views_tiles(n, log_scale):
+    """Views of 17,672 tiles take 320 Gaussians to a chunk whatever their number (69 windows): lists and
+    ranges of narrow and wide footprints bit-exact against the oracle."""
+    scene, _ = synth.frustum_scene(70 + n, n, 0, log_scale, 0.5)
+    cams = [synth.make_camera(np.eye(3), (0.02 * v, 0.0, 0.0), 3000, 1500) for v in range(2)]
+    g = to_gpu(scene)
+    ctx = make_ctx(scene.n, cams, keys_per_gaussian=17_700)
+    ctx.render_fwd(g, cams, BG)
+    ctx.sync()
+    for v, cam in enumerate(cams):
+        p = oracle.project(scene, cam, (16, 16))
+        assert not np.any(p.flags & oracle.FLAG_RADIUS)
+        k, val, r = oracle.keys(p, cam, (16, 16))
+        TX, TY = oracle.tiles_of(cam, (16, 16))
+        log(f"[lists] n {n} log-scale {log_scale} view {v}: {k.size} keys on {TX * TY} tiles")
+        gk, gv, gr = ctx.debug_keys(v, k.size + 16, TX * TY)
+        np.testing.assert_array_equal(gk, k)
+        np.testing.assert_array_equal(gv, val)
+        np.testing.assert_array_equal(gr, r)
