@@ -97,7 +97,7 @@ typedef struct {
 } dass_grads;
 
 /* Render options.  tile_w, tile_h in {16, 32, 64} pixels (a NULL opts means 16x16): the
- * tile is the key bin of the binning and sort; the blend splits it into 16x16 sub-tiles.  The
+ * tile is the bin of the depth-ordered lists; the blend splits it into 16x16 sub-tiles.  The
  * images are the same for every tile size; n_contrib and the keys depend on it. */
 #define DASS_FLAG_COUNT_PAIRS 1u /* render_fwd also counts evaluated / blended (pixel, entry)
                                     pairs (read with dass_debug_pair_counts); slower */
@@ -107,8 +107,11 @@ typedef struct {
                                     relative to the smaller sub-tile's origin */
 typedef struct {
   int32_t tile_w, tile_h;
-  int32_t batch;  /* list entries the blend stages in LDS at a time: 64, 128 or 256 (0 means
-                     128); only the speed depends on it */
+  int32_t batch;  /* list entries a wave of the blend stages in LDS at a time: 64, 128 or 256 (0
+                     means 128); only the speed depends on it.  Read by the calls whose sub-tiles
+                     are blended by a wave each (more than 10,240 of 16x16, for the adjoint 3,600 to
+                     4,096, or 8x8 ones); those blended by quadrant stage 256, the feature render
+                     of 16x16 sub-tiles 128 */
   uint32_t flags; /* DASS_FLAG_* bits */
 } dass_opts;
 
@@ -260,8 +263,9 @@ dass_status dass_render_fwd_l1(dass_ctx ctx, const dass_gaussians* g, const dass
  * channels of |render - target| (Sec. 3.4; err may be NULL); *loss (device float, may be
  * NULL) += L.  lambda in [0, 1]; lambda = 0 is dass_l1_loss_grad (scratch may then be NULL).
  * dl_drgb[v] and err[v] may take the place of render[v] or target[v] of the same view.
- * scratch: host array of n_views device pointers to 9 H W floats each, caller-owned and
- * overwritten.  Host arrays of n_views device pointers otherwise as dass_l1_loss_grad.
+ * scratch: host array of n_views device pointers to 9 H W floats each, caller-owned; what it
+ * holds after the call is unspecified (small calls keep maps there, large ones leave it as it
+ * is).  Host arrays of n_views device pointers otherwise as dass_l1_loss_grad.
  * Errors: DASS_E_INVALID (lambda outside [0, 1], NULL arrays or entries, bad sizes). */
 dass_status dass_fidelity_loss_grad(dass_ctx ctx, const dass_camera* cams, int32_t n_views,
                                     const float* const* render, const float* const* target,
@@ -276,9 +280,8 @@ dass_status dass_fidelity_loss_grad(dass_ctx ctx, const dass_camera* cams, int32
  * loaded on that GPU and held until the process ends; its address is looked up once per GPU
  * when a context is created there.  The views' pixels (sum of width * height) must not exceed
  * DASS_NOALLOC_MAX_PIXELS: DASS_E_INVALID otherwise, before anything is enqueued.  Calls no
- * allocator.  Every call on one GPU shares that GPU's scratch, which keeps the last call's
- * maps: calls that overlap on one GPU (different streams, or threads without ordering) race;
- * calls ordered on one stream do not. */
+ * allocator.  Every call on one GPU shares that GPU's scratch: calls that overlap on one GPU
+ * (different streams, or threads without ordering) race; calls ordered on one stream do not. */
 #define DASS_NOALLOC_MAX_PIXELS (1 << 21)
 dass_status dass_fidelity_loss_grad_noalloc(dass_ctx ctx, const dass_camera* cams, int32_t n_views,
                                             const float* const* render, const float* const* target,
@@ -335,7 +338,8 @@ dass_status dass_hash_field_fwd(dass_ctx ctx, const dass_hash_field* field, cons
 /* Reverse-mode adjoint of dass_hash_field_fwd with the same arguments: given d_dpos [3][ld] and
  * d_drot [4][ld] (dL/d of the outputs), accumulates dL/d(table, w1, b1, w2, b2) into `grads`.
  * Queries outside [0, n) add nothing.  The weight gradients are summed per workgroup and then
- * over workgroups in a fixed order; table gradients use float atomics (order-nondeterministic).
+ * over workgroups in a fixed order; table gradients are summed in double by atomics within a
+ * workgroup (order-nondeterministic in the doubles' last places).
  * Errors as dass_hash_field_fwd, plus DASS_E_INVALID for a NULL grads and DASS_E_CAPACITY for
  * m > max_gaussians (the per-query workspace reserved by the context). */
 dass_status dass_hash_field_bwd(dass_ctx ctx, const dass_hash_field* field, const float* mean,
@@ -462,7 +466,8 @@ dass_status dass_debug_keys(dass_ctx ctx, int32_t view, uint64_t* keys, uint32_t
  * `reps` times between two HIP events on `stream`, and writes the mean milliseconds per
  * fwd+bwd into ms[c] (host array; -1 for a candidate whose tiles or keys exceed the
  * context's budgets) and into *best (host) the index of the first candidate, in the given
- * order of preference, whose time is within 1% of the fastest.  out, dl_drgb and grads
+ * order of preference, whose time is within 1% of the fastest (candidates that differ in a batch
+ * the call does not read are alike, and the first is preferred).  out, dl_drgb and grads
  * are as for render_fwd / render_bwd; grads is accumulated into (scratch for the caller).
  * Synchronises the stream (not for graph capture) and leaves no state for render_bwd.
  * DASS_E_CAPACITY if no candidate fits. */

@@ -360,7 +360,10 @@ class Context:
             raise ValueError("offset buffers are (rows, ld) float32 tensors")
         if col < 0 or col + m > t.shape[1]:
             raise ValueError(f"columns [{col}, {col + m}) outside a buffer of {t.shape[1]}")
-        return C.c_void_p(C.c_void_p(_ptr(t)).value + 4 * col)
+        p = _ptr(t)
+        if not p:
+            raise TypeError("an offset buffer without elements")
+        return p + 4 * col
 
     def hash_field_fwd(self, field: "HashField", mean: torch.Tensor, n: int, idx: Optional[torch.Tensor],
                        m: int, dpos: torch.Tensor, drot: torch.Tensor, col: int = 0, stream=None):

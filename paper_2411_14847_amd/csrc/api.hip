@@ -237,9 +237,11 @@ dass_status make_cams(dass_ctx ctx, const dass_camera* cams, int nv, int tw, int
                 (long long)ctx->ws.cap_tiles);
   int64_t max_view_tiles = 1;
   for (int v = 0; v < nv; v++) max_view_tiles = std::max(max_view_tiles, (int64_t)out.c[v].TX * out.c[v].TY);
+  // (view, tile of the view) in 32 bits: no more tiles than the kernels' int indices of tiles and sub-tiles hold
   const int local_bits = bit_width((uint64_t)(max_view_tiles - 1));
   if (local_bits > 31 || local_bits + bit_width((uint64_t)(nv - 1)) > 32)
-    return fail(ctx, DASS_E_CAPACITY, "%lld tiles per view do not fit a 32-bit tile key", (long long)max_view_tiles);
+    return fail(ctx, DASS_E_CAPACITY, "%lld tiles per view are too many for 32-bit tile indices",
+                (long long)max_view_tiles);
   return DASS_OK;
 }
 

@@ -191,15 +191,14 @@ struct Workspace {
   int64_t cap_vn = 0;     // max views * max gaussians
   int64_t cap_keys = 0;
   int64_t cap_tiles = 0;
-  int sort_blocks = 0;
   // per (view, gaussian), view-major, unsorted
   Rec* rec_u = nullptr;
   uint2* rect_u = nullptr;         // (x0 | y0 << 16, x1 | y1 << 16)
   uint32_t* dkey[2] = {nullptr, nullptr};  // depth keys
   uint32_t* dval[2] = {nullptr, nullptr};
-  // per sorted position p (view-major, depth order)
-  uint2* rect_s = nullptr;
-  uint32_t* gid_s = nullptr;       // gid of sorted position p (dval[1])
+  // per position of a view's depth order, view-major
+  uint2* rect_s = nullptr;         // (before the binning: the depth sort's spare values)
+  uint32_t* gid_s = nullptr;       // the Gaussian there (dval[1])
   uint32_t* depth_hist = nullptr;  // depth sort: digit counts per view and block
   uint32_t* far = nullptr;         // [2 DASS_MAX_VIEWS] the view has depths whose key needs more than 27
                                    // bits: set by the projection and cleared by the depth sort; the

@@ -362,7 +362,7 @@ __global__ __launch_bounds__(256) void k_preprocess(SceneK sc, CamsK cams, int n
 
 // ---------------------------------------------------------------------------------------------
 // Adjoint.  Per Gaussian: for every view where it is visible, read the per-view 2D gradient
-// (du, dv, dA, dB, dC, do, dr, dg, db) at its sorted position, chain it back through the
+// sums in its row of (view, Gaussian) (moments of dL/d(exponent), do, dr, dg, db), chain them back through the
 // conic inverse, the EWA projection, the pixel mean, the colour and the opacity; quantities
 // linear in the view (dSigma, dlogit) are summed over views first and chained once.
 // ---------------------------------------------------------------------------------------------

@@ -550,7 +550,7 @@ __global__ __launch_bounds__(kLanes) void k_blend_bwd(ViewsIO io, int nv, int to
 // reads the next two from LDS meanwhile.  Pixels see the operations of the kernels above in the same
 // order, so the images, n_contrib and, up to the order of the sums, the gradients are the same.
 // Entries one by one -> two at a time, us forward / backward: one view of 2k Gaussians at 128x128 21 -> 17
-// / 40 -> 34; 20 views of 7k at 128x128 116 -> 90 / 179 -> 166.
+// / 40 -> 34; 20 views of 12k (7k and 5k appended) at 128x128 116 -> 90 / 179 -> 168.
 constexpr int kQB = 256;  // threads per workgroup = entries per batch
 constexpr float kLogNone = -1000.f;  // log2 of no opacity (alpha 0)
 
@@ -914,12 +914,14 @@ __global__ __launch_bounds__(kQB) void k_blend_bwd_q(ViewsIO io, int nv, int tot
 // (their 64 sums).  The bound of six also keeps the sums in place: without it the compiler moves them
 // between two register files around each product.  20 views of 200k Gaussians at 1352x1014, 16 channels:
 // 1805 us with multiply-adds, 1700 with four quadrants to a wave, 1710 with four 4x4x1 products of 4
-// channels, 1655 so; the walk's vector instructions, as many as the colour forward's 980 us, and the
-// matrix products, 24 % of the time, hardly overlap.
+// channels, 1655 so.  Of the SIMDs' quad-cycles 52 % issue vector instructions (6.3e8 beside the products,
+// the colour forward 6.8e8, in 79 % of its own), the matrix cores are busy in 28 %, and at least a fifth
+// has neither: the waves, 5.4 to a SIMD where the forward has 6.9, wait 44 % of their time for the
+// staging's loads and the barriers of the two.
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 constexpr int kFeatThreads = 128;  // = entries per batch
-static_assert(kFeatMaxC == 16, "four 4-channel products take the channels");
+static_assert(kFeatMaxC == 16, "a product takes 16 channels");
 
 __global__ __launch_bounds__(kFeatThreads, 6) void k_blend_feat_h(ViewsIO io, int nv, int total_blocks, int per, FeatIO fo,
                                                                const uint2* __restrict__ ranges,
